@@ -125,30 +125,23 @@ def prepare(case, seed):
         return dict(case=case, server=server, requests=_requests(case, seed))
     src, dst = _pairs(case["graph"], case["n"], case["pairs"], seed)
     if case["kind"] == "build":
-        return dict(case=case, src=src, dst=dst)
+        # col has room for every pair; what the graph's entries do not fill stays -1
+        out = [torch.full((size,), -1, dtype=torch.int32, device=DEV)
+               for size in (case["n"] + 1, 2 * case["pairs"], case["n"])]
+        return dict(case=case, src=src, dst=dst, out=out)
     return dict(case=case, graph=tc.tc_build_csr(case["n"], src, dst), seed=seed)
 
 
 # ---- one pass --------------------------------------------------------------
 
 
-class _Borrowed:
-    """A device array of a graph, as torch can view it in place."""
-
-    def __init__(self, graph, ptr, count):
-        self.graph = graph
-        self.__cuda_array_interface__ = dict(shape=(count,), typestr="<i4", data=(ptr, False), version=2)
-
-
-def _csr_views(graph):
-    """(row_ptr, col) of a graph as device tensors (the tc_graph_csr entry point)."""
+def _read_into(graph, row, col, deg):
+    """The CSR into the caller's device tensors (the tc_graph_read entry point)."""
     import ctypes
     from paper_1011_0468_amd import _native
-    row, col = ctypes.c_void_p(), ctypes.c_void_p()
-    _native.check(_native.load().tc_graph_csr(graph.handle, ctypes.byref(row), ctypes.byref(col)))
-    info = graph.info()
-    return [torch.as_tensor(_Borrowed(graph, p.value, count), device=DEV)
-            for p, count in ((row, info["n"] + 1), (col, 2 * info["m"]))]
+    ptrs = [ctypes.c_void_p(t.data_ptr()) for t in (row, col, deg)]
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    _native.check(_native.load().tc_graph_read(graph.handle, *ptrs, 1, stream))
 
 
 def _fields(counts):
@@ -159,8 +152,8 @@ def run(state):
     case = state["case"]
     kind = case["kind"]
     if kind == "build":
-        row, col = _csr_views(tc.tc_build_csr(case["n"], state["src"], state["dst"]))
-        return dict(row_ptr=row, col=col)
+        _read_into(tc.tc_build_csr(case["n"], state["src"], state["dst"]), *state["out"])
+        return dict(zip(("row_ptr", "col", "deg"), state["out"]))
     if kind == "serve":
         server = state["server"]
         for n, src, dst, p, seed in state["requests"]:
@@ -282,7 +275,9 @@ def exact(case, seed):
     if kind == "build":
         start = torch.zeros(n + 1, dtype=torch.long, device=DEV)
         start[1:] = torch.bincount(row, minlength=n).cumsum(0)
-        return dict(row_ptr=start, col=col)
+        cols = torch.full((2 * case["pairs"],), -1, dtype=torch.int32, device=DEV)
+        cols[:len(col)] = col.to(torch.int32)
+        return dict(row_ptr=start.to(torch.int32), col=cols, deg=start.diff().to(torch.int32))
     if kind in ("count", "noalloc"):
         if case["pairs"] * min(1.0, 2 * case["p"]) > 3 << 23:
             return None
