@@ -65,16 +65,6 @@ constexpr int kU = 4;
 // orientation
 // ---------------------------------------------------------------------------
 
-// A byte that orders degrees: the degree itself below 16, above it 8 steps
-// per octave (exponent and the three bits after the leading one), so
-// class(d) < class(d') implies d < d', and equal classes below 16 mean equal
-// degrees.  At most 16 + 8 * 26 + 7 = 231.
-__device__ __forceinline__ uint32_t deg_class(int32_t d) {
-    if (d < 16) return d > 0 ? (uint32_t)d : 0u;
-    const int e = 31 - __builtin_clz((uint32_t)d);  // >= 4
-    return 16u + 8u * (uint32_t)(e - 4) + (((uint32_t)d >> (e - 3)) & 7u);
-}
-
 __global__ void k_deg_class(int64_t n, const int32_t* __restrict__ degp, uint8_t* __restrict__ cls) {
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
         cls[x] = (uint8_t)deg_class(degp[x]);
@@ -1866,6 +1856,10 @@ __global__ void __launch_bounds__(256) k_heavy_mfma_u(int32_t ntiles, const int4
 
 }  // namespace
 
+void degree_classes(int64_t n, const int32_t* deg, uint8_t* cls, hipStream_t s) {
+    TC_LAUNCH("deg_class", k_deg_class, dim3(grid_for(n, 256)), dim3(256), 0, s, n, deg, cls);
+}
+
 // Heavy-vertex bound: heavy vertices have deg > c m'^(1/2) with c = a/b and the
 // degrees sum to 2m', so h < 2 m'^(1/2) / c <= 2 b m^(1/2) / a (all n if a = 0).
 static int64_t heavy_bound(int64_t n, int64_t m, int32_t a, int32_t b) {
@@ -2062,7 +2056,7 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     DevBuf<uint64_t> ubits(NW, s);
     DevBuf<int32_t> upre(NW + 1, s);
     DevBuf<uint8_t> cls(n, s);
-    TC_LAUNCH("deg_class", k_deg_class, dim3(grid_for(n, 256)), dim3(256), 0, s, n, degp, cls.get());
+    degree_classes(n, degp, cls.get(), s);
     // the counted graph's own neighbour classes when it is the built graph
     const uint8_t* ncls = !sampled && !un ? g->ncls : nullptr;
     TC_LAUNCH("orient_bits", k_orient_bits, dim3(grid_for(NW, 16)), dim3(256), 0, s, v_src, v_col, E2, E2_dev,
@@ -2293,8 +2287,7 @@ void neighbour_classes(tc_graph_s* g, hipStream_t s) {
     const int64_t E2 = 2 * g->m;
     if (E2 == 0) return;
     DevBuf<uint8_t> cls(g->n, s);
-    TC_LAUNCH("deg_class", k_deg_class, dim3(grid_for(g->n, 256)), dim3(256), 0, s, g->n, (const int32_t*)g->deg,
-              cls.get());
+    degree_classes(g->n, g->deg, cls.get(), s);
     g->ncls = (uint8_t*)dev_alloc((size_t)E2, s);
     TC_LAUNCH("neighbour_class", k_neighbour_class, dim3(grid_for(E2, 256)), dim3(256), 0, s, E2,
               (const int32_t*)g->col, (const uint8_t*)cls.get(), g->ncls);

@@ -104,4 +104,21 @@ __device__ __forceinline__ bool rank_below(int32_t du, int32_t u, int32_t dv, in
     return du < dv || (du == dv && u < v);
 }
 
+// A byte that orders degrees: the degree itself below 16, above it 8 steps
+// per octave (exponent and the three bits after the leading one), so
+// class(d) < class(d') implies d < d', and equal classes below 16 mean equal
+// degrees.  At most 16 + 8 * 26 + 7 = 231.
+__device__ __forceinline__ uint32_t deg_class(int32_t d) {
+    if (d < 16) return d > 0 ? (uint32_t)d : 0u;
+    const int e = 31 - __builtin_clz((uint32_t)d);  // >= 4
+    return 16u + 8u * (uint32_t)(e - 4) + (((uint32_t)d >> (e - 3)) & 7u);
+}
+
+// The largest degree of class c.
+__device__ __forceinline__ int32_t class_max_degree(uint32_t c) {
+    if (c < 16) return (int32_t)c;
+    const uint32_t e = (c - 16) / 8 + 4;
+    return (int32_t)(((8u + ((c - 16) & 7u) + 1u) << (e - 3)) - 1u);
+}
+
 }  // namespace tc

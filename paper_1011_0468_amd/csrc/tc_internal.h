@@ -175,6 +175,8 @@ int64_t build_csr_bytes(int64_t n, int64_t num_pairs);
 // that the orientation of the graph itself reads it in order instead of
 // gathering it per entry (tc_count.hip)
 void neighbour_classes(tc_graph_s* g, hipStream_t s);
+// cls[x] = degree class of vertex x (a byte that orders degrees, tc_device.h)
+void degree_classes(int64_t n, const int32_t* deg, uint8_t* cls, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Sampling (tc_sample.hip)

@@ -145,55 +145,134 @@ __global__ void __launch_bounds__(256) k_rp_clear_ends(int64_t E2, const int32_t
     Y[(int64_t)src[e1 - 1] * 64 + lane] = 0;
 }
 
-// q[b] = sum over CSR entries (i, j) of Y[i][b] Y[j][b] = 2 * the sum over the
-// entries with j > i (A is symmetric without loops), so only those entries
-// gather the 256-byte row Y[j]; the entry indices are wave-uniform and kept in
-// scalar registers (read from lanes of one coalesced load), so a skipped
-// entry issues no load.
+// The neighbour's degree class of entry e: stored with a graph of
+// tc_build_csr, gathered from the class array (a byte per vertex) otherwise.
+template <bool NCLS>
+__device__ __forceinline__ uint32_t rp_class(const uint8_t* __restrict__ cls, const uint8_t* __restrict__ ncls,
+                                             int64_t e, int32_t j) {
+    return NCLS ? (uint32_t)ncls[e] : (uint32_t)cls[j];
+}
+
+// q[b] = sum over CSR entries (i, j) of Y[i][b] Y[j][b] = 2 * the sum over one
+// entry of each undirected edge (A is symmetric without loops): the one in the
+// row of the end with the smaller (degree class, id).  Bound by the 256-byte
+// gathers of Y[j], one per edge: pointing every edge at its end of larger
+// degree sends them to the few rows of the hubs, which the L2s and the
+// Infinity Cache hold, where the order of the ids alone sends half of them to
+// rows that only memory holds.  R-MAT s22 (64 M edges, 16 GB of rows a
+// sweep): 2.40 -> 1.72 ms a sweep with the queue below.
+// The entries that count are queued per wave in LDS, so that the gathers run
+// over full batches of 64 without a branch per entry, kRpUnroll in flight.
+// Y below 4 GiB is read with buffer loads, whose scalar offset is the row's
+// byte offset straight from a lane (WIDE: 64-bit addresses): with the
+// addresses in scalar arithmetic the kernel took 16 scalar instructions an
+// edge and was bound by them.
+constexpr int kRpQueue = 128;
+
+template <bool WIDE>
+__device__ __forceinline__ int32_t rp_row(const int32_t* __restrict__ Y, __amdgpu_buffer_rsrc_t rs, int32_t v,
+                                          int32_t off, int k, int lane) {
+    if constexpr (WIDE) return Y[(int64_t)__builtin_amdgcn_readlane(v, k) * 64 + lane];
+    else return __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, __builtin_amdgcn_readlane(off, k), 0);
+}
+
+// The products of up to 64 queued entries, entry k on lane k (FULL: all 64).
+template <bool WIDE, bool FULL>
+__device__ __forceinline__ void rp_batch(const int32_t* __restrict__ Y, __amdgpu_buffer_rsrc_t rs, int32_t vi,
+                                         int32_t vj, int cnt, int lane, int32_t& cur, int32_t& ycur, int64_t& acc) {
+    int32_t prev = __shfl_up(vi, 1, 64);
+    if (lane == 0) prev = cur;
+    uint64_t fresh = ballot64((FULL || lane < cnt) && vi != prev);  // entries that start a row
+    const int32_t oi = (int32_t)((uint32_t)vi << 8), oj = (int32_t)((uint32_t)vj << 8);
+    // not unrolled: the rounds of a batch would all be in flight at once, at 2 or 3 waves per SIMD
+#pragma unroll 1
+    for (int k0 = 0; k0 < (FULL ? 64 : cnt); k0 += kRpUnroll, fresh >>= kRpUnroll) {
+        int32_t yj[kRpUnroll], yi[kRpUnroll];
+#pragma unroll
+        for (int k = 0; k < kRpUnroll; ++k) {
+            yj[k] = FULL || k0 + k < cnt ? rp_row<WIDE>(Y, rs, vj, oj, k0 + k, lane) : 0;
+            if ((fresh >> k) & 1ull) yi[k] = rp_row<WIDE>(Y, rs, vi, oi, k0 + k, lane);
+        }
+#pragma unroll
+        for (int k = 0; k < kRpUnroll; ++k) {
+            if ((fresh >> k) & 1ull) ycur = yi[k];
+            acc += (int64_t)ycur * (int64_t)yj[k];
+        }
+    }
+    cur = __builtin_amdgcn_readlane(vi, FULL ? 63 : cnt - 1);
+}
+
+template <bool NCLS, bool WIDE>
 __global__ void __launch_bounds__(256) k_rp_dot(int64_t E2, const int32_t* __restrict__ src,
-                                                 const int32_t* __restrict__ col, const int32_t* __restrict__ Y,
-                                                 int64_t* __restrict__ q) {
+                                                 const int32_t* __restrict__ col, const uint8_t* __restrict__ cls,
+                                                 const uint8_t* __restrict__ ncls, const int32_t* __restrict__ Y,
+                                                 uint32_t ybytes, int64_t* __restrict__ q) {
+    __shared__ int2 queue[4][kRpQueue];
+    __shared__ int64_t red[4][64];
     const int lane = __lane_id();
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t w = (int64_t)blockIdx.x * 4 + wv;
     const int64_t e0 = w * kRpRange;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(Y), 0, WIDE ? 0 : (int)ybytes, 0x00020000);
+    int2* Q = queue[wv];
     int64_t acc = 0;
     if (e0 < E2) {
         const int64_t e1 = e0 + kRpRange < E2 ? e0 + kRpRange : E2;
         int32_t cur = -1, ycur = 0;
+        int head = 0, held = 0;  // queued entries: Q[head ..], held < 64 between rounds
         for (int64_t eb = e0; eb < e1; eb += 64) {
-            // 64 entries per coalesced load; entry k of the batch is read from lane k
             const int64_t el = eb + lane;
-            const int32_t vi = el < e1 ? src[el] : -1;
-            const int32_t vj = el < e1 ? col[el] : -1;
-            for (int k0 = 0; k0 < 64; k0 += kRpUnroll) {
-                int32_t ii[kRpUnroll], jj[kRpUnroll], yj[kRpUnroll];
-#pragma unroll
-                for (int k = 0; k < kRpUnroll; ++k) {
-                    ii[k] = __builtin_amdgcn_readlane(vi, k0 + k);
-                    jj[k] = __builtin_amdgcn_readlane(vj, k0 + k);
-                }
-#pragma unroll
-                for (int k = 0; k < kRpUnroll; ++k) yj[k] = jj[k] > ii[k] ? Y[(int64_t)jj[k] * 64 + lane] : 0;
-#pragma unroll
-                for (int k = 0; k < kRpUnroll; ++k) {
-                    if (jj[k] <= ii[k]) continue;  // lower entry, or past the range end (-1, -1)
-                    if (ii[k] != cur) {
-                        cur = ii[k];
-                        ycur = Y[(int64_t)cur * 64 + lane];
-                    }
-                    acc += (int64_t)ycur * (int64_t)yj[k];
-                }
+            const bool in = el < e1;
+            const int32_t vi = in ? src[el] : 0;
+            const int32_t vj = in ? col[el] : 0;
+            const uint32_t ci = in ? cls[vi] : 0u, cj = in ? rp_class<NCLS>(cls, ncls, el, vj) : 0u;
+            const bool up = in && (ci < cj || (ci == cj && vi < vj));
+            const uint64_t U = ballot64(up);
+            if (up) Q[(head + held + __popcll(U & lanes_below())) & (kRpQueue - 1)] = make_int2(vi, vj);
+            held += __popcll(U);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // a wave's LDS operations run in issue order
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (held >= 64) {
+                const int2 e = Q[(head + lane) & (kRpQueue - 1)];
+                head = (head + 64) & (kRpQueue - 1);
+                held -= 64;
+                rp_batch<WIDE, true>(Y, rs, e.x, e.y, 64, lane, cur, ycur, acc);
             }
         }
+        if (held > 0) {
+            const int2 e = lane < held ? Q[(head + lane) & (kRpQueue - 1)] : make_int2(0, 0);
+            rp_batch<WIDE, false>(Y, rs, e.x, e.y, held, lane, cur, ycur, acc);
+        }
     }
-    __shared__ int64_t red[4][64];
     red[wv][lane] = acc;
     __syncthreads();
     if (wv == 0) {
         const int64_t s = red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
         if (s) atomicAdd((unsigned long long*)&q[lane], (unsigned long long)(2 * s));
     }
+}
+
+// An upper bound of the sum over CSR entries (i, j) of deg_i * deg_j: deg_j
+// taken as the largest degree of its class (at most 1/8 too large), which is
+// read in order or from a table of a byte per vertex instead of gathered per
+// entry.  One partial per block, summed on the host.
+template <bool NCLS>
+__global__ void __launch_bounds__(256) k_rp_class_bound(const int32_t* __restrict__ src,
+                                                         const int32_t* __restrict__ col,
+                                                         const int32_t* __restrict__ deg,
+                                                         const uint8_t* __restrict__ cls,
+                                                         const uint8_t* __restrict__ ncls, int64_t E2,
+                                                         double* __restrict__ part) {
+    double s = 0.0;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E2; e += (int64_t)gridDim.x * blockDim.x)
+        s += (double)deg[src[e]] * (double)class_max_degree(rp_class<NCLS>(cls, ncls, e, NCLS ? 0 : col[e]));
+    s = wave_sum(s);
+    __shared__ double red[4];
+    if (__lane_id() == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
 // Half the sum over CSR entries (i, j) of deg_i * deg_j, in double (a bound
@@ -221,23 +300,34 @@ void rp_trace(const tc_graph_s* g, int32_t k, uint64_t seed, hipStream_t s, int6
     const int64_t n = g->n, E2 = 2 * g->m;
     for (int32_t l = 0; l < k; ++l) q_host[l] = 0;
     if (n == 0 || E2 == 0) return;
+    DevBuf<uint8_t> cls(n, s);
+    degree_classes(n, g->deg, cls.get(), s);
     {
         // |q_l| <= sum over entries (i, j) of |Y_il| |Y_jl| <= sum of deg_i deg_j; every q_l and their sum
-        // stay exact while k times that is below 2^62 (margin for the double rounding)
+        // stay exact while k times that is below 2^62 (margin for the double rounding).  A bound from the
+        // degree classes settles most graphs (R-MAT s22: 0.65 -> 0.25 ms); where it does not, the degrees themselves decide.
         unsigned blocks = ceil_div(E2, 256);
-        if (blocks > 1024) blocks = 1024;
+        if (blocks > 2048) blocks = 2048;
         DevBuf<double> part(blocks, s);
-        TC_LAUNCH("rp_bound", k_rp_bound, dim3(blocks), dim3(256), 0, s, (const int32_t*)g->src,
-                  (const int32_t*)g->col, (const int32_t*)g->deg, E2, part.get());
         std::vector<double> hpart(blocks);
-        check_hip(hipMemcpyAsync(hpart.data(), part.get(), sizeof(double) * blocks, hipMemcpyDeviceToHost, s),
-                  "bound");
-        check_hip(hipStreamSynchronize(s), "sync");
-        double hb = 0.0;
-        for (double v : hpart) hb += v;
-        hb *= 2.0;
-        if (hb * (double)k >= 4.611686018427387904e18)
-            fail(TC_ERR_OVERFLOW, "k * sum deg_i deg_j reaches 2^62: q could overflow int64");
+        auto total = [&] {
+            check_hip(hipMemcpyAsync(hpart.data(), part.get(), sizeof(double) * blocks, hipMemcpyDeviceToHost, s),
+                      "bound");
+            check_hip(hipStreamSynchronize(s), "sync");
+            double t = 0.0;
+            for (double v : hpart) t += v;
+            return t * (double)k;
+        };
+        const double limit = 4.611686018427387904e18;
+        TC_LAUNCH("rp_bound", g->ncls ? k_rp_class_bound<true> : k_rp_class_bound<false>, dim3(blocks), dim3(256), 0, s,
+                  (const int32_t*)g->src, (const int32_t*)g->col, (const int32_t*)g->deg, (const uint8_t*)cls.get(),
+                  (const uint8_t*)g->ncls, E2, part.get());
+        if (!(total() * (1.0 + 1e-9) < limit)) {
+            TC_LAUNCH("rp_bound", k_rp_bound, dim3(blocks), dim3(256), 0, s, (const int32_t*)g->src,
+                      (const int32_t*)g->col, (const int32_t*)g->deg, E2, part.get());
+            if (2.0 * total() >= limit)
+                fail(TC_ERR_OVERFLOW, "k * sum deg_i deg_j reaches 2^62: q could overflow int64");
+        }
     }
     const uint64_t salt = [&] {
         uint64_t z = seed ^ 0x52505F5452414345ull;  // "RP_TRACE"
@@ -249,13 +339,17 @@ void rp_trace(const tc_graph_s* g, int32_t k, uint64_t seed, hipStream_t s, int6
     const int32_t nchunks = (k + 63) / 64;
     const int64_t waves = (E2 + kRpRange - 1) / kRpRange;
     const unsigned wblocks = (unsigned)((waves + 3) / 4);
+    const bool wide = n * 256 >= ((int64_t)1 << 32);  // rows past the reach of a buffer load's offset
+    const auto dot = wide ? (g->ncls ? k_rp_dot<true, true> : k_rp_dot<false, true>)
+                          : (g->ncls ? k_rp_dot<true, false> : k_rp_dot<false, false>);
     for (int32_t c = 0; c < nchunks; ++c) {
         fill_i64(qd.get(), 0, 64, s);
         TC_LAUNCH("rp_clear", k_rp_clear_ends, dim3(wblocks), dim3(256), 0, s, E2, (const int32_t*)g->src, Y.get());
         TC_LAUNCH("rp_spmm", k_rp_spmm, dim3(wblocks), dim3(256), 0, s, E2, (const int32_t*)g->row_ptr,
                   (const int32_t*)g->src, (const int32_t*)g->col, (uint64_t)c, salt, Y.get());
-        TC_LAUNCH("rp_dot", k_rp_dot, dim3(wblocks), dim3(256), 0, s, E2, (const int32_t*)g->src,
-                  (const int32_t*)g->col, (const int32_t*)Y.get(), qd.get());
+        TC_LAUNCH("rp_dot", dot, dim3(wblocks), dim3(256), 0, s, E2, (const int32_t*)g->src, (const int32_t*)g->col,
+                  (const uint8_t*)cls.get(), (const uint8_t*)g->ncls, (const int32_t*)Y.get(), (uint32_t)(n * 256),
+                  qd.get());
         int64_t hq[64];
         check_hip(hipMemcpyAsync(hq, qd.get(), sizeof(hq), hipMemcpyDeviceToHost, s), "q");
         check_hip(hipStreamSynchronize(s), "sync");
