@@ -14,15 +14,20 @@
 //
 //   1. per vertex, its number of triples: C(d, 2) (thread per vertex), or
 //      the sum of its neighbours' degrees with, per list entry, the exclusive
-//      prefix of that sum along the list (one wave per list);
-//   2. their exclusive prefix (int64);
-//   3. one thread per sample: index r = high half of h * |U| (h a 64-bit
-//      counter hash of the sample number), its vertex by binary search over
-//      the prefix, the pair by colex unranking or the list entry by binary
+//      prefix of that sum along the list (one block per list);
+//   2. their exclusive prefix (int64) with a bucket index;
+//   3. the sample numbers partitioned by the top byte of their hash (large
+//      calls), so that samples close in U are drawn close in time;
+//   4. one thread per sample: index r = high half of h * |U| (h a 64-bit
+//      counter hash of the sample number), its vertex by a search of the
+//      prefix, the pair by colex unranking or the list entry by binary
 //      search over the entry prefix, and the closing edge by binary search in
 //      the shorter sorted list.
 #include "tc_internal.h"
 #include "tc_device.h"
+#include "tc_prefix.h"
+
+#include <vector>
 
 namespace tc {
 
@@ -37,43 +42,64 @@ uint64_t host_mix64(uint64_t z) {
 
 __device__ __forceinline__ bool ext_kind(int hybrid, int64_t deg, int64_t m) { return hybrid && deg * deg > m; }
 
-// per vertex of the wedge kind: C(d, 2); extension kind: 0 (k_tri_ext fills it)
-__global__ void k_tri_counts(int64_t n, const int32_t* __restrict__ deg, int64_t m, int hybrid,
-                             int64_t* __restrict__ cnt) {
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t d = deg[x];
-        cnt[x] = ext_kind(hybrid, d, m) ? 0 : d * (d - 1) / 2;
+// per vertex of the wedge kind: C(d, 2); the vertices of the extension kind
+// are appended to list, in any order (count at *listed), for k_tri_ext
+__global__ void __launch_bounds__(256) k_tri_counts(int64_t n, const int32_t* __restrict__ deg, int64_t m, int hybrid,
+                                                     int64_t* __restrict__ cnt, int32_t* __restrict__ list,
+                                                     int32_t* __restrict__ listed) {
+    const int lane = __lane_id();
+    const int64_t n64 = (n + 63) / 64 * 64;
+    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n64; x += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t d = x < n ? deg[x] : 0;
+        const bool ext = ext_kind(hybrid, d, m);
+        if (x < n && !ext) cnt[x] = d * (d - 1) / 2;
+        const uint64_t b = ballot64(ext);
+        if (!b) continue;
+        int32_t at = 0;
+        if (lane == 0) at = atomicAdd(listed, (int32_t)__popcll(b));
+        at = __shfl(at, 0, 64);
+        if (ext) list[at + __popcll(b & lanes_below())] = (int32_t)x;
     }
 }
 
-// extension-kind lists, one wave per list (64 consecutive vertices per step):
-// EP[e] = sum of deg(N(u)[i]) over the entries i before e in u's list, and
-// cnt[u] = the whole sum
-__global__ void __launch_bounds__(256) k_tri_ext(int64_t n, const int32_t* __restrict__ rp,
-                                                  const int32_t* __restrict__ col, const int32_t* __restrict__ deg,
-                                                  int64_t m, int hybrid, int64_t* __restrict__ cnt,
-                                                  int64_t* __restrict__ EP) {
-    const int lane = __lane_id();
-    const int64_t gw = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * 4;
-    for (int64_t x0 = gw * 64; x0 < n; x0 += nw * 64) {
-        const int64_t x = x0 + lane;
-        const int64_t d = x < n ? deg[x] : 0;
-        uint64_t todo = ballot64(x < n && ext_kind(hybrid, d, m));
-        while (todo) {
-            const int l = __builtin_ctzll(todo);
-            todo &= todo - 1;
-            const int32_t rs = rp[x0 + l], re = rp[x0 + l + 1];  // wave-uniform
-            int64_t carry = 0;
-            for (int32_t e0 = rs; e0 < re; e0 += 64) {
-                const int32_t e = e0 + lane;
-                const int64_t v = e < re ? (int64_t)deg[col[e]] : 0;
-                const int64_t inc = wave_inclusive_sum(v);
-                if (e < re) EP[e] = carry + inc - v;
-                carry += __shfl(inc, 63, 64);
+// extension-kind lists, one block per list: EP[e] = sum of deg(N(u)[i]) over
+// the entries i before e in u's list, and cnt[u] = the whole sum.  A list is a
+// serial chain of prefix sums, and the longest holds 10^5 entries: 8192 of
+// them per round, their gathers all in flight (64 per round, a wave per
+// list, took 2.4 ms on R-MAT s22 where this takes 0.5).
+constexpr int kExtThreads = 1024, kExtItems = 8;
+__global__ void __launch_bounds__(kExtThreads) k_tri_ext(const int32_t* __restrict__ list,
+                                                          const int32_t* __restrict__ listed,
+                                                          const int32_t* __restrict__ rp,
+                                                          const int32_t* __restrict__ col,
+                                                          const int32_t* __restrict__ deg, int64_t* __restrict__ cnt,
+                                                          int64_t* __restrict__ EP) {
+    __shared__ int64_t tmp[kExtThreads / 64 + 1];
+    const int32_t lists = listed[0];
+    for (int32_t i = blockIdx.x; i < lists; i += gridDim.x) {  // block-uniform
+        const int32_t u = list[i];
+        const int32_t rs = rp[u], re = rp[u + 1];
+        int64_t carry = 0;
+        for (int64_t e0 = rs; e0 < re; e0 += kExtThreads * kExtItems) {
+            const int64_t e = e0 + (int64_t)threadIdx.x * kExtItems;
+            int32_t v[kExtItems];
+            int64_t sum = 0;
+#pragma unroll
+            for (int k = 0; k < kExtItems; ++k) v[k] = e + k < re ? col[e + k] : -1;
+#pragma unroll
+            for (int k = 0; k < kExtItems; ++k) v[k] = v[k] >= 0 ? deg[v[k]] : 0;
+#pragma unroll
+            for (int k = 0; k < kExtItems; ++k) sum += v[k];
+            int64_t total;
+            int64_t pre = carry + block_exclusive_sum<kExtThreads>(sum, tmp, &total);
+#pragma unroll
+            for (int k = 0; k < kExtItems; ++k) {
+                if (e + k < re) EP[e + k] = pre;
+                pre += v[k];
             }
-            if (lane == 0) cnt[x0 + l] = carry;
+            carry += total;
         }
+        if (threadIdx.x == 0) cnt[u] = carry;
     }
 }
 
@@ -122,12 +148,36 @@ void scan64(const int64_t* in, int64_t* out, int64_t N, hipStream_t s) {
 
 namespace {
 
-// y in the sorted list of x
-__device__ __forceinline__ bool in_list(const int32_t* __restrict__ rp, const int32_t* __restrict__ col, int32_t x,
-                                        int32_t y) {
-    int32_t lo = rp[x];
-    const int32_t end = rp[x + 1];
+// y in the sorted list col[lo .. end) of ids below n (scale = 1 / n).  Every
+// step of a binary search of a long list reads another cache line, so lists
+// past one line are entered where y would be if their ids were spread evenly
+// (as relabelled graphs' are: off by about the root of the length) and the
+// range is widened from there by doubling: 6.6 -> 5.5 ms for the samples on
+// R-MAT s22, and at most twice the steps on any list.
+__device__ __forceinline__ bool in_list(const int32_t* __restrict__ col, int32_t lo, int32_t end, int32_t y,
+                                        float scale) {
     int32_t hi = end;
+    if (end - lo > 32) {
+        int32_t g = lo + (int32_t)((float)(end - lo) * ((float)y * scale));
+        g = g < end - 1 ? g : end - 1;  // >= lo
+        int32_t step = 16;
+        if (col[g] < y) {
+            lo = g + 1;
+            while (hi - lo > step && col[lo + step] < y) {
+                lo += step + 1;
+                step *= 2;
+            }
+            hi = hi - lo > step ? lo + step : hi;
+        } else {
+            hi = g;
+            while (hi - lo > step && col[hi - 1 - step] >= y) {
+                hi -= step + 1;
+                step *= 2;
+            }
+            if (hi - lo > step) lo = hi - step;
+        }
+        // the first entry >= y lies in [lo, hi]
+    }
     while (lo < hi) {
         const int32_t mid = lo + ((hi - lo) >> 1);
         if (col[mid] < y) lo = mid + 1;
@@ -136,32 +186,81 @@ __device__ __forceinline__ bool in_list(const int32_t* __restrict__ rp, const in
     return lo < end && col[lo] == y;
 }
 
-__device__ __forceinline__ bool adjacent(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                         const int32_t* __restrict__ deg, int32_t x, int32_t y) {
-    return deg[x] <= deg[y] ? in_list(rp, col, x, y) : in_list(rp, col, y, x);
+__device__ __forceinline__ bool adjacent(const int32_t* __restrict__ rp, const int32_t* __restrict__ col, int32_t x,
+                                         int32_t y, float scale) {
+    const int32_t xs = rp[x], xe = rp[x + 1], ys = rp[y], ye = rp[y + 1];
+    return xe - xs <= ye - ys ? in_list(col, xs, xe, y, scale) : in_list(col, ys, ye, x, scale);
 }
 
-// acc[0] += sum of the closed samples' weights, acc[1] += closed samples
-__global__ void __launch_bounds__(256) k_tri_sample(int64_t s, uint64_t salt, int64_t n,
-                                                     const int64_t* __restrict__ CU, const int32_t* __restrict__ rp,
-                                                     const int32_t* __restrict__ col,
-                                                     const int32_t* __restrict__ deg, const int64_t* __restrict__ EP,
-                                                     int64_t m, int hybrid, unsigned long long* __restrict__ acc) {
-    const int64_t size = CU[n];
-    int64_t wsum = 0, closed = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; size > 0 && i < s;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t h = mix64(mix64((uint64_t)i) ^ salt);
-        const int64_t r = (int64_t)__umul64hi(h, (uint64_t)size);
-        int64_t lo = 0, hi = n - 1;  // the largest u with CU[u] <= r
-        while (lo < hi) {
-            const int64_t mid = lo + ((hi - lo + 1) >> 1);
-            if (CU[mid] <= r) lo = mid;
-            else hi = mid - 1;
+// the 64-bit hash of sample i: its element of U is the high half of h * |U|
+__device__ __forceinline__ uint64_t sample_hash(int64_t i, uint64_t salt) { return mix64(mix64((uint64_t)i) ^ salt); }
+
+// ---- partition of the samples by the top byte of their hash ----------------
+// Samples in hash order touch prefixes, lists and list prefixes all over the
+// graph (a new cache line per search step); after the partition a wave's
+// samples lie in one 256th of U.  Counts per byte, their bases, then the
+// sample numbers (relative to i0) at their places, in any order inside a part.
+constexpr int kParts = 256, kPartTile = 8192;
+
+__global__ void __launch_bounds__(256) k_tri_part_count(int64_t i0, int64_t s, uint64_t salt,
+                                                         int32_t* __restrict__ cnt) {
+    __shared__ int32_t c[kParts];
+    c[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < s; i += (int64_t)gridDim.x * 256)
+        atomicAdd(&c[sample_hash(i0 + i, salt) >> 56], 1);
+    __syncthreads();
+    if (c[threadIdx.x]) atomicAdd(&cnt[threadIdx.x], c[threadIdx.x]);
+}
+
+__global__ void __launch_bounds__(256) k_tri_part_place(int64_t i0, int64_t s, uint64_t salt,
+                                                         int32_t* __restrict__ at, int32_t* __restrict__ order) {
+    __shared__ int32_t c[kParts];
+    for (int64_t t0 = (int64_t)blockIdx.x * kPartTile; t0 < s; t0 += (int64_t)gridDim.x * kPartTile) {
+        c[threadIdx.x] = 0;
+        __syncthreads();
+        int32_t part[kPartTile / 256], rank[kPartTile / 256];
+#pragma unroll
+        for (int k = 0; k < kPartTile / 256; ++k) {
+            const int64_t i = t0 + 256 * k + threadIdx.x;
+            part[k] = i < s ? (int32_t)(sample_hash(i0 + i, salt) >> 56) : -1;
+            rank[k] = i < s ? atomicAdd(&c[part[k]], 1) : 0;
         }
-        const int32_t u = (int32_t)lo;
+        __syncthreads();
+        const int32_t mine = c[threadIdx.x];
+        c[threadIdx.x] = mine ? atomicAdd(&at[threadIdx.x], mine) : 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPartTile / 256; ++k)
+            if (part[k] >= 0) order[c[part[k]] + rank[k]] = (int32_t)(t0 + 256 * k + threadIdx.x);
+        __syncthreads();
+    }
+}
+
+// Sums of the samples, spread over lines of 128 bytes.
+constexpr int kAccLines = 64, kAccStride = 16;
+
+// Sum of the closed samples' weights and closed samples, over
+// the samples i0 + order[i] (order null: i0 + i), i < s.  Bound by random
+// reads: per sample the index, the prefix, the two ends' ids and row starts
+// and the steps of the closing search.  Each XCD takes a contiguous eighth, so
+// that with the partition its samples' lists and prefixes stay in its L2.
+__global__ void __launch_bounds__(256) k_tri_sample(int64_t i0, int64_t s, const int32_t* __restrict__ order,
+                                                     uint64_t salt, PrefixIndex<int64_t> P,
+                                                     const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
+                                                     const int64_t* __restrict__ EP, int64_t m, int hybrid,
+                                                     unsigned long long* __restrict__ acc) {
+    const int64_t* CU = P.pre;
+    const int64_t size = CU[P.n];
+    const float scale = 1.0f / (float)P.n;
+    int64_t wsum = 0, closed = 0;
+    const int64_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
+    const int64_t end = s * (xcd + 1) / 8;
+    for (int64_t i = s * xcd / 8 + slot * 256 + threadIdx.x; size > 0 && i < end; i += slots * 256) {
+        const int64_t r = (int64_t)__umul64hi(sample_hash(i0 + (order ? order[i] : i), salt), (uint64_t)size);
+        const int32_t u = (int32_t)find_item(P, r);
         const int64_t k = r - CU[u];
-        const int32_t du = deg[u];
+        const int32_t us = rp[u], du = rp[u + 1] - us;
         int32_t x, y, z;
         bool cl;
         if (!ext_kind(hybrid, du, m)) {
@@ -169,12 +268,12 @@ __global__ void __launch_bounds__(256) k_tri_sample(int64_t s, uint64_t salt, in
             while (b > 1 && b * (b - 1) / 2 > k) --b;
             while ((b + 1) * b / 2 <= k) ++b;
             const int64_t a = k - b * (b - 1) / 2;
-            x = col[rp[u] + a];
+            x = col[us + a];
             y = u;
-            z = col[rp[u] + b];
-            cl = adjacent(rp, col, deg, x, z);
+            z = col[us + b];
+            cl = adjacent(rp, col, x, z, scale);
         } else {
-            int32_t elo = rp[u], ehi = rp[u + 1] - 1;  // the largest entry e of u's list with EP[e] <= k
+            int32_t elo = us, ehi = us + du - 1;  // the largest entry e of u's list with EP[e] <= k
             while (elo < ehi) {
                 const int32_t mid = elo + ((ehi - elo + 1) >> 1);
                 if (EP[mid] <= k) elo = mid;
@@ -184,22 +283,39 @@ __global__ void __launch_bounds__(256) k_tri_sample(int64_t s, uint64_t salt, in
             x = u;
             y = v;
             z = col[rp[v] + (k - EP[elo])];
-            cl = z != u && adjacent(rp, col, deg, u, z);
+            cl = z != u && adjacent(rp, col, u, z, scale);
         }
         if (cl) {
-            const int ne = (int)ext_kind(hybrid, deg[x], m) + (int)ext_kind(hybrid, deg[y], m) +
-                           (int)ext_kind(hybrid, deg[z], m);
-            wsum += 60 / (3 + ne);
+            const auto ext = [&](int32_t w) { return (int)ext_kind(hybrid, rp[w + 1] - rp[w], m); };
+            wsum += hybrid ? 60 / (3 + ext(x) + ext(y) + ext(z)) : 20;
             closed += 1;
         }
     }
+    // one atomic per block and sum, over kAccLines lines: per wave on one line
+    // they took 200 of 330 us at 2^19 samples on R-MAT s15
+    __shared__ int64_t red[4][2];
     wsum = wave_sum(wsum);
     closed = wave_sum(closed);
-    if (__lane_id() == 0 && (wsum || closed)) {
-        atomicAdd(&acc[0], (unsigned long long)wsum);
-        atomicAdd(&acc[1], (unsigned long long)closed);
+    if (__lane_id() == 0) {
+        red[threadIdx.x >> 6][0] = wsum;
+        red[threadIdx.x >> 6][1] = closed;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const int64_t t = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
+        if (t) atomicAdd(&acc[(blockIdx.x % kAccLines) * kAccStride + threadIdx.x], (unsigned long long)t);
     }
 }
+
+// Samples partitioned together, and the calls that are: R-MAT s22 with 2^25
+// samples takes 16.3 -> 6.4 ms; from 2^21 samples it is 1.0 to 1.1 times
+// faster on R-MAT s17 to s21 and from 2^23 1.2 to 1.4 times; at 2^20 and below
+// the two more launches cost what the locality gains (0.9 to 1.0 times), and
+// graphs below s17 fit the caches (0.9 times).
+constexpr int64_t kPartChunk = (int64_t)1 << 26;
+constexpr int64_t kPartSamples = (int64_t)1 << 21;
+constexpr int64_t kPartEntries = (int64_t)1 << 22;
+constexpr int64_t kIndexVertices = (int64_t)1 << 16;
 
 }  // namespace
 
@@ -208,27 +324,54 @@ void triple_sample(const tc_graph_s* g, int hybrid, int64_t num_samples, uint64_
     const int64_t n = g->n, m = g->m;
     *size = *wsum = *closed = 0;
     if (n == 0) return;
-    DevBuf<int64_t> cnt(n + 1, s), CU(n + 1, s), EP(2 * m > 0 ? 2 * m : 1, s);
-    DevBuf<unsigned long long> acc(2, s);
-    fill_i64(reinterpret_cast<int64_t*>(acc.get()), 0, 2, s);
+    // a search of few vertices is short by itself, and its index a launch more
+    const int kb = n >= kIndexVertices ? index_bits(n) : 0;
+    DevBuf<int64_t> cnt(n + 1, s), CU(n + 1, s), EP(hybrid ? 2 * m : 0, s);
+    DevBuf<int32_t> idx((size_t)1 << kb, s), list(hybrid ? n : 0, s);
+    DevBuf<unsigned long long> acc(kAccLines * kAccStride + 1, s);  // the sums, then the length of list
+    fill_i64(reinterpret_cast<int64_t*>(acc.get()), 0, kAccLines * kAccStride + 1, s);
+    int32_t* listed = reinterpret_cast<int32_t*>(acc.get() + kAccLines * kAccStride);
     const unsigned vg = (unsigned)std::min<int64_t>((n + 255) / 256, 65536);
-    TC_LAUNCH("tri_counts", k_tri_counts, dim3(vg), dim3(256), 0, s, n, (const int32_t*)g->deg, m, hybrid, cnt.get());
+    TC_LAUNCH("tri_counts", k_tri_counts, dim3(vg), dim3(256), 0, s, n, (const int32_t*)g->deg, m, hybrid, cnt.get(),
+              list.get(), listed);
     if (hybrid)
-        TC_LAUNCH("tri_ext", k_tri_ext, dim3(vg), dim3(256), 0, s, n, (const int32_t*)g->row_ptr,
-                  (const int32_t*)g->col, (const int32_t*)g->deg, m, hybrid, cnt.get(), EP.get());
+        TC_LAUNCH("tri_ext", k_tri_ext, dim3((unsigned)std::min<int64_t>(n, (int64_t)num_cus() * 2)),
+                  dim3(kExtThreads), 0, s, (const int32_t*)list.get(), (const int32_t*)listed,
+                  (const int32_t*)g->row_ptr, (const int32_t*)g->col, (const int32_t*)g->deg, cnt.get(), EP.get());
     scan64(cnt.get(), CU.get(), n, s);
+    if (kb)
+        TC_LAUNCH("tri_index", k_bucket_index<int64_t>, dim3(vg), dim3(256), 0, s, n, (const int64_t*)CU.get(), kb,
+                  idx.get());
+    const PrefixIndex<int64_t> P{CU.get(), kb ? idx.get() : nullptr, n, kb};
     const uint64_t salt = host_mix64(seed ^ 0x54435F545249504CULL);  // "TC_TRIPL"
-    const unsigned sg = (unsigned)std::min<int64_t>((num_samples + 255) / 256, (int64_t)num_cus() * 32);
-    TC_LAUNCH("tri_sample", k_tri_sample, dim3(sg > 0 ? sg : 1), dim3(256), 0, s, num_samples, salt, n,
-              (const int64_t*)CU.get(), (const int32_t*)g->row_ptr, (const int32_t*)g->col, (const int32_t*)g->deg,
-              (const int64_t*)EP.get(), m, hybrid, acc.get());
-    int64_t h[3];
-    check_hip(hipMemcpyAsync(h, CU.get() + n, sizeof(int64_t), hipMemcpyDeviceToHost, s), "size");
-    check_hip(hipMemcpyAsync(h + 1, acc.get(), 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s), "acc");
+    const bool part = num_samples >= kPartSamples && 2 * m >= kPartEntries;
+    const int64_t chunk = part ? std::min(num_samples, kPartChunk) : num_samples;
+    DevBuf<int32_t> order(part ? chunk : 0, s), at(kParts + 1, s);
+    for (int64_t i0 = 0; i0 < num_samples; i0 += chunk) {
+        const int64_t c = std::min(chunk, num_samples - i0);
+        if (part) {
+            fill_i32(at.get(), 0, kParts, s);
+            TC_LAUNCH("tri_part", k_tri_part_count, dim3((unsigned)num_cus() * 8), dim3(256), 0, s, i0, c, salt,
+                      at.get());
+            scan_exclusive_i32(at.get(), at.get(), kParts, s);
+            TC_LAUNCH("tri_part", k_tri_part_place, dim3(ceil_div(c, kPartTile)), dim3(256), 0, s, i0, c, salt,
+                      at.get(), order.get());
+        }
+        const int64_t sg = std::min<int64_t>((c + 2047) / 2048, (int64_t)num_cus()) * 8;  // a multiple of the XCDs
+        TC_LAUNCH("tri_sample", k_tri_sample, dim3((unsigned)sg), dim3(256), 0, s, i0, c,
+                  part ? (const int32_t*)order.get() : (const int32_t*)nullptr, salt, P, (const int32_t*)g->row_ptr,
+                  (const int32_t*)g->col, (const int64_t*)EP.get(), m, hybrid, acc.get());
+    }
+    std::vector<int64_t> h(1 + kAccLines * kAccStride);
+    check_hip(hipMemcpyAsync(h.data(), CU.get() + n, sizeof(int64_t), hipMemcpyDeviceToHost, s), "size");
+    check_hip(hipMemcpyAsync(h.data() + 1, acc.get(), sizeof(int64_t) * kAccLines * kAccStride, hipMemcpyDeviceToHost,
+                             s), "acc");
     check_hip(hipStreamSynchronize(s), "sync");
     *size = h[0];
-    *wsum = h[1];
-    *closed = h[2];
+    for (int l = 0; l < kAccLines; ++l) {
+        *wsum += h[(size_t)(1 + l * kAccStride)];
+        *closed += h[(size_t)(2 + l * kAccStride)];
+    }
 }
 
 }  // namespace tc
