@@ -376,7 +376,6 @@ tc_graph_s* graph_from_pairs(int64_t n, int64_t num_pairs, const int32_t* src, c
     tc_graph_s* g = new tc_graph_s();
     try {
         if (build_csr(n, num_pairs, ds, dd, s, g)) fail(TC_ERR_INVALID, "vertex id outside [0, n)");
-        g->max_deg = max_degree(g, s);
     } catch (...) {
         (void)hipStreamSynchronize(s);
         graph_release(g);

@@ -70,14 +70,6 @@ __global__ void k_deg_class(int64_t n, const int32_t* __restrict__ degp, uint8_t
         cls[x] = (uint8_t)deg_class(degp[x]);
 }
 
-// the degree class of every entry's neighbour, gathered from the class array
-// (one byte per vertex: a quarter of the degrees' footprint)
-__global__ void k_neighbour_class(int64_t E2, const int32_t* __restrict__ col, const uint8_t* __restrict__ cls,
-                                  uint8_t* __restrict__ ncls) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E2; e += (int64_t)gridDim.x * blockDim.x)
-        ncls[e] = cls[col[e]];
-}
-
 // Per CSR entry (u, v) of a kept edge: "up" if (deg u, u) < (deg v, v).  Each
 // kept undirected edge has exactly one up entry, in the row of its
 // lower-ranked end.  The neighbour's degree class comes from ncls (one byte
@@ -2281,16 +2273,6 @@ void counts_from_slots(const int64_t* hacc, tc_counts* out) {
     res.model_bytes_small = hacc[kBytesSmall];
     res.model_bytes_large = hacc[kBytesLarge];
     *out = res;
-}
-
-void neighbour_classes(tc_graph_s* g, hipStream_t s) {
-    const int64_t E2 = 2 * g->m;
-    if (E2 == 0) return;
-    DevBuf<uint8_t> cls(g->n, s);
-    degree_classes(g->n, g->deg, cls.get(), s);
-    g->ncls = (uint8_t*)dev_alloc((size_t)E2, s);
-    TC_LAUNCH("neighbour_class", k_neighbour_class, dim3(grid_for(E2, 256)), dim3(256), 0, s, E2,
-              (const int32_t*)g->col, (const uint8_t*)cls.get(), g->ncls);
 }
 
 int64_t count_bytes(int64_t n, int64_t m, int32_t maxd, int sampled, const CountConfig& cfg) {

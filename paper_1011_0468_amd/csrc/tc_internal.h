@@ -166,15 +166,12 @@ void fill_u8(uint8_t* p, uint8_t v, int64_t N, hipStream_t s);
 // CSR build (tc_csr.hip)
 // ---------------------------------------------------------------------------
 
-// Build into g (allocations through dev_alloc).  Returns 0 or 1 if an id is out of range.
+// Build into g, the neighbours' degree classes and max_deg included
+// (allocations through dev_alloc; synchronises s).  Returns 0 or 1 if an id is out of range.
 int build_csr(int64_t n, int64_t num_pairs, const int32_t* src_dev, const int32_t* dst_dev,
               hipStream_t s, tc_graph_s* g);
 // Sum of the sizes of every allocation build_csr makes (region_bytes each).
 int64_t build_csr_bytes(int64_t n, int64_t num_pairs);
-// g->ncls of a built graph: the degree class of every entry's neighbour, so
-// that the orientation of the graph itself reads it in order instead of
-// gathering it per entry (tc_count.hip)
-void neighbour_classes(tc_graph_s* g, hipStream_t s);
 // cls[x] = degree class of vertex x (a byte that orders degrees, tc_device.h)
 void degree_classes(int64_t n, const int32_t* deg, uint8_t* cls, hipStream_t s);
 

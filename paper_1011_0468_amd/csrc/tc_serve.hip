@@ -168,7 +168,7 @@ int64_t group_bytes(const std::vector<const tc_request*>& rs) {
         }
     }
     const int64_t E2 = 2 * P, NW = (E2 + 63) / 64;
-    int64_t b = 2 * rb(4 * P) + build_csr_bytes(nU, P) + rb(4);          // staging, build, max degree
+    int64_t b = 2 * rb(4 * P) + build_csr_bytes(nU, P);  // staging, build
     b += rb(4 * nU) + rb(4 * (K + 1)) + 3 * rb(8 * K) + rb(8 * kCountSlots * K);  // comp, off, salts, thrs, m', results
     b += rb(4 * (nU + 1)) + rb(4 * nU) + rb(8 * NW) + rb(4 * (NW + 1)) + scan_scratch_bytes(NW) + 2 * rb(4 * E2);
     b += count_union_bytes(nU, P, maxd, (int32_t)K, hsum, ubytes, ntiles, cfg);
@@ -180,7 +180,7 @@ int64_t request_bytes(const tc_request* r) {
     const CountConfig cfg;  // requests run with the library defaults
     if (r->graph) return count_bytes(r->graph->n, r->graph->m, r->graph->max_deg, sampled, cfg);
     const int64_t n = r->n, P = r->num_pairs;
-    int64_t b = 2 * region_bytes(4 * P) + build_csr_bytes(n, P) + region_bytes(4);  // staging, build, max degree
+    int64_t b = 2 * region_bytes(4 * P) + build_csr_bytes(n, P);  // staging, build
     // the built graph has m <= P edges and degrees <= min(n - 1, 2P)
     const int32_t maxd = (int32_t)std::max<int64_t>(0, std::min<int64_t>(n - 1, 2 * P));
     return b + count_bytes(n, P, maxd, sampled, cfg);
