@@ -60,6 +60,16 @@ constexpr int kTinyPositions = 64;
 constexpr int kLdsDcap = 1024;
 // Strips of 64 positions per super-strip of the closure loop.
 constexpr int kU = 4;
+// Hubs: the vertices of the highest degree classes, at most kHubs, numbered
+// from 0; kNoHub is every other vertex's number.  A set of them is a bitmap of
+// 8 KB of LDS, and a list of numbers half the bytes of a list of ids.
+constexpr int kHubs = 65535;
+constexpr int32_t kNoHub = 65535;
+// Vertices per block of the passes that number the hubs, at least.
+constexpr int64_t kHubChunk = 4096;
+constexpr int kHubTail = 8;
+// Edges per vertex of the counted graph from which hubs are numbered.
+constexpr double kBitDegree = 4.0;
 
 // ---------------------------------------------------------------------------
 // orientation
@@ -68,6 +78,82 @@ constexpr int kU = 4;
 __global__ void k_deg_class(int64_t n, const int32_t* __restrict__ degp, uint8_t* __restrict__ cls) {
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
         cls[x] = (uint8_t)deg_class(degp[x]);
+}
+
+int64_t hub_chunk(int64_t n) { return std::max(kHubChunk, (n + 1023) / 1024); }
+
+// k_deg_class, and the number of vertices of every class added into hist[256].
+__global__ void __launch_bounds__(256) k_deg_class_hist(int64_t n, int64_t chunk, const int32_t* __restrict__ degp,
+                                                         uint8_t* __restrict__ cls, int32_t* __restrict__ hist) {
+    __shared__ int32_t cnt[256];
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t x1 = min(n, (blockIdx.x + 1) * chunk);
+    for (int64_t x = blockIdx.x * chunk + threadIdx.x; x < x1; x += 256) {
+        const uint32_t c = deg_class(degp[x]);
+        cls[x] = (uint8_t)c;
+        atomicAdd(&cnt[c], 1);
+    }
+    __syncthreads();
+    if (cnt[threadIdx.x]) atomicAdd(&hist[threadIdx.x], cnt[threadIdx.x]);
+}
+
+// The lowest class c >= 1 such that at most kHubs vertices are of class c or
+// above (hist: vertices per class): the hubs' classes.  One wave; 256 if none.
+__device__ __forceinline__ uint32_t hub_class(const int32_t* __restrict__ hist, int lane) {
+    // lane l holds classes 255 - 4 l .. 252 - 4 l, highest first
+    int64_t above = 0, own[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        own[k] = hist[255 - 4 * lane - k];
+        above += own[k];
+    }
+    int64_t run = wave_inclusive_sum(above) - above;  // vertices of the classes before this lane's
+    uint32_t low = 256;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        run += own[k];
+        const uint32_t c = (uint32_t)(255 - 4 * lane - k);
+        if (run <= kHubs && c >= 1) low = c;
+    }
+    // the sums only grow, so the classes that fit are the highest ones
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) low = min(low, (uint32_t)__shfl_xor((int)low, d, 64));
+    return low;
+}
+
+// num[x] = the number of vertex x among the hubs (any order, hubs counted in
+// *nhub), kNoHub if it is none.
+__global__ void __launch_bounds__(256) k_hub_ids(int64_t n, int64_t chunk, const uint8_t* __restrict__ cls,
+                                                  const int32_t* __restrict__ hist, int32_t* __restrict__ nhub,
+                                                  uint16_t* __restrict__ num) {
+    __shared__ int32_t wsum[4], base_s;
+    const int lane = __lane_id(), w = threadIdx.x >> 6;
+    const uint32_t c0 = hub_class(hist, lane);
+    const int64_t x0 = blockIdx.x * chunk, x1 = min(n, x0 + chunk);
+    int32_t mine = 0;
+    for (int64_t x = x0 + threadIdx.x; x < x1; x += 256) mine += cls[x] >= c0 ? 1 : 0;
+    mine = wave_sum(mine);
+    if (lane == 0) wsum[w] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) base_s = atomicAdd(nhub, wsum[0] + wsum[1] + wsum[2] + wsum[3]);
+    __syncthreads();
+    int32_t at = base_s;
+    for (int64_t xb = x0; xb < x1; xb += 256) {  // block-uniform
+        const int64_t x = xb + threadIdx.x;
+        const bool hub = x < x1 && cls[x] >= c0;
+        const uint64_t b = ballot64(hub);
+        __syncthreads();  // the sums of the round before have been read
+        if (lane == 0) wsum[w] = (int32_t)__popcll(b);
+        __syncthreads();
+        int32_t pre = at, tot = 0;
+        for (int i = 0; i < 4; ++i) {
+            pre += i < w ? wsum[i] : 0;
+            tot += wsum[i];
+        }
+        if (x < x1) num[x] = (uint16_t)(hub ? pre + (int32_t)__popcll(b & lanes_below()) : kNoHub);
+        at += tot;
+    }
 }
 
 // Per CSR entry (u, v) of a kept edge: "up" if (deg u, u) < (deg v, v).  Each
@@ -205,11 +291,11 @@ __device__ __forceinline__ int32_t up_before(int64_t e, int64_t E2, const uint64
 
 // Per vertex, everything the light phase needs of it: the start of its up
 // list, rpO[x] (x <= n), and d+(x), from the orientation bits at its row
-// start; the heavy flag; code = d+(x) if x is a light source (light,
-// d+ >= 2), else 0 (in a union of components, m' is that of x's component:
-// mk[comp[x]]); rowQ[x] = (start of
-// N+(x), code ? d+ : ~d+, deg, 0), what the anchor work gathers of a vertex in
-// one 16-byte load; rpD[x], the first slot of x's v-major descriptors: the
+// start; the heavy flag; rowQ[x] = (start of N+(x), d+ if x is a light source
+// (light, d+ >= 2) and ~d+ otherwise, deg, hub number: num[x], or x itself where
+// num is null), what the anchor work gathers of a vertex in
+// one 16-byte load (in a union of components, m' is that of x's component:
+// mk[comp[x]]); rpD[x], the first slot of x's v-major descriptors: the
 // in-degrees d- = deg - d+ of the vertices before x, that is x's row start in
 // the counted graph (row) minus its start in the up lists (rpO); and
 // cw[x] = rpD[x] << 32 (see claim_vmajor).  Also clears the counts of the
@@ -219,8 +305,8 @@ __global__ void k_vertex_prep(int64_t n, int64_t E2, const uint64_t* __restrict_
                               const int32_t* __restrict__ upre, const int32_t* __restrict__ degp,
                               const int32_t* __restrict__ mp_dev, const int32_t* __restrict__ comp,
                               const int64_t* __restrict__ mk, int32_t ha, int32_t hb, const int32_t* __restrict__ row,
-                              int32_t* __restrict__ rpO, int32_t* __restrict__ dplus, int32_t* __restrict__ heavy,
-                              int32_t* __restrict__ code, int32_t* __restrict__ rpD, int4* __restrict__ rowQ,
+                              const uint16_t* __restrict__ num, int32_t* __restrict__ rpO,
+                              int32_t* __restrict__ heavy, int32_t* __restrict__ rpD, int4* __restrict__ rowQ,
                               unsigned long long* __restrict__ cw, int32_t* __restrict__ wide,
                               int32_t* __restrict__ sentinel) {
     const int64_t mp = comp ? 0 : mp_dev[0];
@@ -234,13 +320,10 @@ __global__ void k_vertex_prep(int64_t n, int64_t E2, const uint64_t* __restrict_
         rpD[x] = dslot;
         if (x == n) break;
         const int32_t dp = up_before(row[x + 1], E2, ubits, upre) - r;
-        dplus[x] = dp;
         const int32_t dg = degp[x];
         const bool hv = dg > 0 && is_heavy(dg, comp ? mk[comp[x]] : mp, ha, hb);
         heavy[x] = hv ? 1 : 0;
-        const int32_t c = !hv && dp >= 2 ? dp : 0;
-        code[x] = c;
-        rowQ[x] = make_int4(r, c ? c : ~dp, dg, 0);
+        rowQ[x] = make_int4(r, !hv && dp >= 2 ? dp : ~dp, dg, num ? (int32_t)num[x] : (int32_t)x);
         cw[x] = (unsigned long long)(uint32_t)dslot << 32;
     }
 }
@@ -381,7 +464,8 @@ __device__ __forceinline__ void add_gather(int64_t gsum, int64_t* acc) {
 // descriptors of its pairs and its Wu.
 template <int G>
 __device__ __forceinline__ void work_groups(uint64_t mask, const int4& q, int64_t x0, int lane,
-                                            const int4* __restrict__ rowQ, int32_t* __restrict__ colO, int32_t vcap,
+                                            const int4* __restrict__ rowQ, int32_t* __restrict__ colO,
+                                            uint16_t* __restrict__ colH, int32_t vcap,
                                             int2* __restrict__ packU, int2* __restrict__ packD,
                                             unsigned long long* __restrict__ cw, int64_t* __restrict__ Wu,
                                             int64_t* __restrict__ Gx, int64_t& gsum) {
@@ -411,11 +495,12 @@ __device__ __forceinline__ void work_groups(uint64_t mask, const int4& q, int64_
         int32_t idx = lane;
         bitonic_lanes<G>(key, idx, lane);
         // rowQ of the vertex that lands on this lane, from the lane that loaded it
-        const int4 qv = make_int4(__shfl(qw.x, idx, 64), __shfl(qw.y, idx, 64), 0, 0);  // (start, code) are what pair_desc reads
+        const int4 qv = make_int4(__shfl(qw.x, idx, 64), __shfl(qw.y, idx, 64), 0, colH ? __shfl(qw.w, idx, 64) : 0);
         int64_t wu = 0, gl = 0;
         if (in) {
             const int32_t v = (int32_t)(uint32_t)key;
             colO[rs + pos] = v;
+            if (colH) colH[rs + pos] = (uint16_t)qv.w;
             int2 pk = pair_desc(rs, d, pos, qv, true, vcap, wu, gl);
             if (pk.y < 0) {
                 packD[claim_vmajor(cw, v, -pk.y)] = make_int2(pk.x, -pk.y);
@@ -441,7 +526,7 @@ __device__ __forceinline__ void work_groups(uint64_t mask, const int4& q, int64_
 template <int B>
 __device__ __forceinline__ void strip_work(const uint64_t (&vk)[B], int32_t k0, int32_t rs, int32_t d, bool sorted,
                                            int lane, const int4* __restrict__ rowQ, int32_t* __restrict__ colO,
-                                           int32_t vcap, int2* __restrict__ packU, int2* __restrict__ packD,
+                                           uint16_t* __restrict__ colH, int32_t vcap, int2* __restrict__ packU, int2* __restrict__ packD,
                                            unsigned long long* __restrict__ cw, int64_t& wu, int64_t& gsum) {
     int4 qv[B];
 #pragma unroll
@@ -467,6 +552,7 @@ __device__ __forceinline__ void strip_work(const uint64_t (&vk)[B], int32_t k0, 
             }
             packU[rs + k] = pk[b];
             if (sorted) colO[rs + k] = (int32_t)(uint32_t)vk[b];
+            if (colH) colH[rs + k] = (uint16_t)qv[b].w;
         }
     }
 }
@@ -477,7 +563,8 @@ __device__ __forceinline__ void strip_work(const uint64_t (&vk)[B], int32_t k0, 
 // descriptors' rowQ gathers after the sort find their lines in the cache.
 template <int R>
 __device__ __forceinline__ void work_wide_list(int32_t rs, int32_t d, int lane, const int4* __restrict__ rowQ,
-                                               int32_t* __restrict__ colO, int32_t vcap, int2* __restrict__ packU,
+                                               int32_t* __restrict__ colO, uint16_t* __restrict__ colH,
+                                               int32_t vcap, int2* __restrict__ packU,
                                                int2* __restrict__ packD, unsigned long long* __restrict__ cw,
                                                int64_t& wu, int64_t& gsum) {
     int32_t w[R];
@@ -499,7 +586,7 @@ __device__ __forceinline__ void work_wide_list(int32_t rs, int32_t d, int lane, 
         uint64_t vk[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) vk[b] = key[r0 + b];
-        strip_work<B>(vk, 64 * r0, rs, d, true, lane, rowQ, colO, vcap, packU, packD, cw, wu, gsum);
+        strip_work<B>(vk, 64 * r0, rs, d, true, lane, rowQ, colO, colH, vcap, packU, packD, cw, wu, gsum);
     }
 }
 
@@ -509,7 +596,8 @@ __device__ __forceinline__ void work_wide_list(int32_t rs, int32_t d, int lane, 
 template <int R>
 __device__ __forceinline__ void work_wide_lists(uint64_t mask, const int4& q, int64_t x0, int lane,
                                                 const int4* __restrict__ rowQ, int32_t* __restrict__ colO,
-                                                int32_t vcap, int2* __restrict__ packU, int2* __restrict__ packD,
+                                                uint16_t* __restrict__ colH, int32_t vcap,
+                                                int2* __restrict__ packU, int2* __restrict__ packD,
                                                 unsigned long long* __restrict__ cw, int64_t* __restrict__ Wu,
                                                 int64_t* __restrict__ Gx, int64_t& gsum) {
     while (mask) {
@@ -519,7 +607,7 @@ __device__ __forceinline__ void work_wide_lists(uint64_t mask, const int4& q, in
         const int32_t d = __builtin_amdgcn_readlane(q.y, l);
         int64_t wu = 0, gl = 0;
         if (d <= 64 * R) {
-            work_wide_list<R>(rs, d, lane, rowQ, colO, vcap, packU, packD, cw, wu, gl);
+            work_wide_list<R>(rs, d, lane, rowQ, colO, colH, vcap, packU, packD, cw, wu, gl);
         } else {
             for (int32_t k0 = 0; k0 < d; k0 += 256) {
                 uint64_t vk[4];
@@ -528,7 +616,7 @@ __device__ __forceinline__ void work_wide_lists(uint64_t mask, const int4& q, in
                     const int32_t k = k0 + 64 * b + lane;
                     vk[b] = k < d ? (uint32_t)colO[rs + k] : 0;
                 }
-                strip_work<4>(vk, k0, rs, d, false, lane, rowQ, colO, vcap, packU, packD, cw, wu, gl);
+                strip_work<4>(vk, k0, rs, d, false, lane, rowQ, colO, colH, vcap, packU, packD, cw, wu, gl);
             }
         }
         gsum += gl;
@@ -556,10 +644,13 @@ __device__ __forceinline__ void append_rows(uint64_t mask, int64_t x0, int lane,
 // groups of 4 to 64 and those of 65 to 128 entries in two registers per lane,
 // and writes Wu (the length u-major pairs stream) of all of them, 0 for the
 // longer lists, which it appends to the lists of k_work_wide's classes
-// (wide[c * (n + 1)] holds the count of class c, its vertices follow).
+// (wide[c * (n + 1)] holds the count of class c, its vertices follow).  Where
+// hubs are numbered (colH) it also writes the numbers of the other vertices'
+// lists (heavy, or of one entry), which nothing sorts.
 __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __restrict__ rowQ,
-                                                     int32_t* __restrict__ colO, int32_t vcap,
-                                                     int2* __restrict__ packU, int2* __restrict__ packD,
+                                                     int32_t* __restrict__ colO, uint16_t* __restrict__ colH,
+                                                     int32_t vcap, int2* __restrict__ packU,
+                                                     int2* __restrict__ packD,
                                                      unsigned long long* __restrict__ cw, int64_t* __restrict__ Wu,
                                                      int64_t* __restrict__ Gx, int32_t* __restrict__ wide,
                                                      int64_t* __restrict__ acc) {
@@ -572,12 +663,22 @@ __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __res
         const int4 q = x < n ? rowQ[x] : make_int4(0, 0, 0, 0);
         const int32_t d = q.y;
         if (x < n && !(d >= 2 && d <= 128)) Wu[x] = 0;
-        work_groups<4>(ballot64(d >= 2 && d <= 4), q, x0, lane, rowQ, colO, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_groups<8>(ballot64(d > 4 && d <= 8), q, x0, lane, rowQ, colO, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_groups<16>(ballot64(d > 8 && d <= 16), q, x0, lane, rowQ, colO, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_groups<32>(ballot64(d > 16 && d <= 32), q, x0, lane, rowQ, colO, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_groups<64>(ballot64(d > 32 && d <= 64), q, x0, lane, rowQ, colO, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_wide_lists<2>(ballot64(d > 64 && d <= 128), q, x0, lane, rowQ, colO, vcap, packU, packD, cw, Wu, Gx, gsum);
+        if (colH) {
+            if (d == ~1) colH[q.x] = (uint16_t)rowQ[colO[q.x]].w;
+            uint64_t rest = ballot64(d < ~1);
+            while (rest) {
+                const int l = __builtin_ctzll(rest);
+                rest &= rest - 1;
+                const int32_t rs = __builtin_amdgcn_readlane(q.x, l), len = ~__builtin_amdgcn_readlane(q.y, l);
+                for (int32_t k = lane; k < len; k += 64) colH[rs + k] = (uint16_t)rowQ[colO[rs + k]].w;
+            }
+        }
+        work_groups<4>(ballot64(d >= 2 && d <= 4), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_groups<8>(ballot64(d > 4 && d <= 8), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_groups<16>(ballot64(d > 8 && d <= 16), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_groups<32>(ballot64(d > 16 && d <= 32), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_groups<64>(ballot64(d > 32 && d <= 64), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_wide_lists<2>(ballot64(d > 64 && d <= 128), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
         append_rows(ballot64(d > 128 && d <= 256), x0, lane, wide + 1);
         append_rows(ballot64(d > 256 && d <= 512), x0, lane, wide + (n + 1) + 1);
         append_rows(ballot64(d > 512), x0, lane, wide + 2 * (n + 1) + 1);
@@ -591,7 +692,8 @@ __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __res
 // shorter classes keep their occupancy.  Writes Wu of its lists.
 template <int R>
 __global__ void __launch_bounds__(256) k_work_wide(const int32_t* __restrict__ L, const int4* __restrict__ rowQ,
-                                                    int32_t* __restrict__ colO, int32_t vcap,
+                                                    int32_t* __restrict__ colO, uint16_t* __restrict__ colH,
+                                                    int32_t vcap,
                                                     int2* __restrict__ packU, int2* __restrict__ packD,
                                                     unsigned long long* __restrict__ cw, int64_t* __restrict__ Wu,
                                                     int64_t* __restrict__ Gx, int64_t* __restrict__ acc) {
@@ -603,7 +705,7 @@ __global__ void __launch_bounds__(256) k_work_wide(const int32_t* __restrict__ L
          i += gridDim.x * 4) {
         const int32_t x = L[i];
         const int4 q = rowQ[x];  // wave-uniform
-        work_wide_lists<R>(1ull, q, x, lane, rowQ, colO, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_wide_lists<R>(1ull, q, x, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
     }
     if (!Gx) add_gather(gsum, acc);
 }
@@ -624,15 +726,21 @@ __device__ __forceinline__ int32_t cw_end(unsigned long long c) { return (int32_
 // Per-vertex part of the classification: the item counts of x's bin, and
 // x's contribution to the statistics st (sources, out, wedges, probes,
 // bytes_s, bytes_l, items_s, items_l) and to the largest block-bin d+.
-__device__ __forceinline__ void classify_vertex(int64_t x, const int32_t* __restrict__ code,
-                                                const int32_t* __restrict__ dplus, const int64_t* __restrict__ Wu,
+// The bins of the launches, one item count each (then its prefix): tiny,
+// small, bits (the anchor's keys are hubs, see k_light_bits; null where no hubs
+// are numbered), large, huge.
+struct ItemBins {
+    int32_t *tiny, *small, *bits, *large, *huge;
+};
+
+__device__ __forceinline__ void classify_vertex(int64_t x, const int32_t* __restrict__ rpO,
+                                                const int32_t* __restrict__ heavy, const int4* __restrict__ rowQ,
+                                                const int64_t* __restrict__ Wu,
                                                 const unsigned long long* __restrict__ cw,
-                                                const int32_t* __restrict__ rpD, int32_t small_dmax,
-                                                int32_t* __restrict__ ntn, int32_t* __restrict__ nsm,
-                                                int32_t* __restrict__ nlg, int32_t* __restrict__ nhg,
+                                                const int32_t* __restrict__ rpD, int32_t small_dmax, ItemBins bin,
                                                 int64_t (&st)[8], int64_t& dmax) {
-    const int32_t c = code[x];
-    const int32_t dp = dplus[x];
+    const int32_t dp = rpO[x + 1] - rpO[x];
+    const int32_t c = !heavy[x] && dp >= 2 ? dp : 0;  // d+ of a light source
     if (c > 0) { st[0] += 1; st[1] += c; st[2] += (int64_t)c * (c - 1) / 2; }
     const unsigned long long c2 = cw[x];
     const int64_t wu = Wu[x], wv = cw_len(c2);
@@ -643,15 +751,18 @@ __device__ __forceinline__ void classify_vertex(int64_t x, const int32_t* __rest
                           8 * (int64_t)(cv > 0 ? nv : 0) + 4 * (wu + wv);
     st[3] += wu + wv;
     const bool small = dp <= small_dmax;
-    const bool huge = dp > kLdsDcap;
+    // every key ranks above its anchor, so a hub's keys are hubs
+    const bool bits = !small && bin.bits && rowQ[x].w < kHubs;
+    const bool huge = !bits && dp > kLdsDcap;
     // tiny: at most kTinyKeys keys and descriptors and kTinyPositions
     // positions per item, so one item per group of kTinyLanes lanes
     const bool tiny = small && dp <= kTinyKeys && (cv == 0 || nv <= kTinyKeys) && wu <= kTinyPositions &&
                       wv <= kTinyPositions;
-    ntn[x] = tiny ? cu + cv : 0;
-    nsm[x] = small && !tiny ? cu + cv : 0;
-    nlg[x] = (!small && !huge) ? cu + cv : 0;
-    nhg[x] = huge ? cu + cv : 0;
+    bin.tiny[x] = tiny ? cu + cv : 0;
+    bin.small[x] = small && !tiny ? cu + cv : 0;
+    if (bin.bits) bin.bits[x] = bits ? cu + cv : 0;
+    bin.large[x] = (!small && !bits && !huge) ? cu + cv : 0;
+    bin.huge[x] = huge && !small ? cu + cv : 0;
     if (small) { st[4] += bytes; st[6] += cu + cv; }
     else {
         st[5] += bytes;
@@ -660,17 +771,16 @@ __device__ __forceinline__ void classify_vertex(int64_t x, const int32_t* __rest
     }
 }
 
-__global__ void __launch_bounds__(256) k_classify(int64_t n, const int32_t* __restrict__ code,
-                                                   const int32_t* __restrict__ dplus, const int64_t* __restrict__ Wu,
+__global__ void __launch_bounds__(256) k_classify(int64_t n, const int32_t* __restrict__ rpO,
+                                                   const int32_t* __restrict__ heavy, const int4* __restrict__ rowQ,
+                                                   const int64_t* __restrict__ Wu,
                                                    const unsigned long long* __restrict__ cw,
-                                                   const int32_t* __restrict__ rpD, int32_t small_dmax,
-                                                   int32_t* __restrict__ ntn, int32_t* __restrict__ nsm,
-                                                   int32_t* __restrict__ nlg, int32_t* __restrict__ nhg,
+                                                   const int32_t* __restrict__ rpD, int32_t small_dmax, ItemBins bin,
                                                    int64_t* __restrict__ part) {
     int64_t st[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // sources, out, wedges, probes, bytes_s, bytes_l, items_s, items_l
     int64_t dmax = 0;
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
-        classify_vertex(x, code, dplus, Wu, cw, rpD, small_dmax, ntn, nsm, nlg, nhg, st, dmax);
+        classify_vertex(x, rpO, heavy, rowQ, Wu, cw, rpD, small_dmax, bin, st, dmax);
     __shared__ int64_t red[4][9];
     const int wv_ = threadIdx.x >> 6;
 #pragma unroll
@@ -729,15 +839,13 @@ __device__ __forceinline__ void flush_comp_stats(int32_t c, int64_t (&st)[8], in
 }
 
 __global__ void __launch_bounds__(256) k_classify_union(int64_t n, const int32_t* __restrict__ comp,
-                                                         const int32_t* __restrict__ code,
-                                                         const int32_t* __restrict__ dplus,
+                                                         const int32_t* __restrict__ rpO,
+                                                         const int32_t* __restrict__ heavy,
                                                          const int64_t* __restrict__ Wu,
                                                          const int64_t* __restrict__ Gx,
                                                          const unsigned long long* __restrict__ cw,
                                                          const int32_t* __restrict__ rpD, int32_t small_dmax,
-                                                         int32_t* __restrict__ ntn, int32_t* __restrict__ nsm,
-                                                         int32_t* __restrict__ nlg, int32_t* __restrict__ nhg,
-                                                         int64_t* __restrict__ acc) {
+                                                         ItemBins bin, int64_t* __restrict__ acc) {
     const int64_t windows = (n + 255) / 256;
     const int64_t per = (windows + gridDim.x - 1) / gridDim.x;
     const int64_t w0 = (int64_t)blockIdx.x * per;
@@ -754,8 +862,8 @@ __global__ void __launch_bounds__(256) k_classify_union(int64_t n, const int32_t
         }
         const int64_t x = xs + threadIdx.x;
         if (x < n) {
-            classify_vertex(x, code, dplus, Wu, cw, rpD, small_dmax, ntn, nsm, nlg, nhg, st, dmax);
-            if (code[x] > 0) gth += Gx[x];
+            classify_vertex(x, rpO, heavy, nullptr, Wu, cw, rpD, small_dmax, bin, st, dmax);
+            if (!heavy[x] && rpO[x + 1] - rpO[x] >= 2) gth += Gx[x];
         }
     }
     if (cur >= 0) flush_comp_stats(cur, st, gth, dmax, acc);
@@ -763,25 +871,24 @@ __global__ void __launch_bounds__(256) k_classify_union(int64_t n, const int32_t
 
 // items of anchor x: (x, r) for the u-major ranges r of N+(x), then (~x, r)
 // for the ranges r of x's v-major descriptors
-// The item lists of all four bins in one pass: an anchor's items go to the
-// list of its bin (tiny, small, large or huge, exclusive) at its bin's prefix.
-__global__ void k_items(int64_t n, const int32_t* __restrict__ ntn, const int32_t* __restrict__ nsm,
-                        const int32_t* __restrict__ nlg, const int32_t* __restrict__ nhg,
-                        const int32_t* __restrict__ tbase, const int32_t* __restrict__ sbase,
-                        const int32_t* __restrict__ lbase, const int32_t* __restrict__ hbase,
-                        const int32_t* __restrict__ dplus, const int64_t* __restrict__ Wu,
+// The item lists of all five bins in one pass: an anchor's items go to the
+// list of its bin (exclusive) at its bin's prefix; the large bin's items
+// follow the bits bin's in one list.
+__global__ void k_items(int64_t n, ItemBins base, const int32_t* __restrict__ rpO, const int64_t* __restrict__ Wu,
                         const unsigned long long* __restrict__ cw, const int32_t* __restrict__ rpD,
                         int2* __restrict__ items_t, int2* __restrict__ items_s, int2* __restrict__ items_l,
                         int2* __restrict__ items_h) {
+    const int32_t nbits = base.bits ? base.bits[n] : 0;
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
         int2* items;
         int32_t b;
-        if (ntn[x]) { items = items_t; b = tbase[x]; }
-        else if (nsm[x]) { items = items_s; b = sbase[x]; }
-        else if (nlg[x]) { items = items_l; b = lbase[x]; }
-        else if (nhg[x]) { items = items_h; b = hbase[x]; }
+        if ((b = base.tiny[x]) != base.tiny[x + 1]) items = items_t;
+        else if ((b = base.small[x]) != base.small[x + 1]) items = items_s;
+        else if (base.bits && (b = base.bits[x]) != base.bits[x + 1]) items = items_l;
+        else if ((b = base.large[x]) != base.large[x + 1]) items = items_l + nbits;
+        else if ((b = base.huge[x]) != base.huge[x + 1]) items = items_h;
         else continue;
-        const int32_t cu = items_of(Wu[x], dplus[x]);
+        const int32_t cu = items_of(Wu[x], rpO[x + 1] - rpO[x]);
         const unsigned long long c2 = cw[x];
         const int32_t cv = items_of(cw_len(c2), cw_end(c2) - rpD[x]);
         for (int32_t r = 0; r < cu; ++r) items[b++] = make_int2((int32_t)x, r);
@@ -789,11 +896,12 @@ __global__ void k_items(int64_t n, const int32_t* __restrict__ ntn, const int32_
     }
 }
 
-__global__ void k_heavy_list(int64_t n, const int32_t* __restrict__ heavy, const int32_t* __restrict__ hpos,
+// the heavy vertices (hpos: exclusive prefix of the heavy flags)
+__global__ void k_heavy_list(int64_t n, const int32_t* __restrict__ hpos,
                              int32_t hmax, int32_t* __restrict__ hlist, int64_t* __restrict__ acc) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && hpos[n] > hmax) acc[kHeavyOverflow] = 1;
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
-        if (heavy[x] && hpos[x] < hmax) hlist[hpos[x]] = (int32_t)x;
+        if (hpos[x + 1] > hpos[x] && hpos[x] < hmax) hlist[hpos[x]] = (int32_t)x;
 }
 
 // zero the first heavy_pad(h)^2 bytes of U and UT (h from device)
@@ -1390,6 +1498,7 @@ __global__ void __launch_bounds__(256) k_light_tiny(const int2* __restrict__ ite
 
 template <bool GLOBAL, bool UNION>
 __global__ void __launch_bounds__(256) k_light_large(const int2* __restrict__ items,
+                                                      const int32_t* __restrict__ skip_dev,
                                                       const int32_t* __restrict__ n_items_dev,
                                                       const int32_t* __restrict__ rpO, const int32_t* __restrict__ colO,
                                                       const int32_t* __restrict__ rpD,
@@ -1412,6 +1521,7 @@ __global__ void __launch_bounds__(256) k_light_large(const int2* __restrict__ it
     uint8_t* mark = reinterpret_cast<uint8_t*>(D + kJL) + 64 * kU * w;  // 64 kU bytes per wave
     for (int i = lane; i < 16 * kU; i += 64) reinterpret_cast<int32_t*>(mark)[i] = 0;  // flags stay zero between super-strips
     const int64_t n_items = n_items_dev[0];
+    if (skip_dev) items += skip_dev[0];  // the items before belong to another launch
     int64_t total = 0;
     int32_t cur = 0;  // component of the closures in total
     for (int64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
@@ -1450,6 +1560,127 @@ __global__ void __launch_bounds__(256) k_light_large(const int2* __restrict__ it
         __syncthreads();
     }
     flush_tl(acc, cur, total, lane);
+}
+
+// One block (4 waves) per item whose anchor is a hub: its keys, all hubs, are
+// bits of a bitmap in LDS, and a streamed entry that is no hub is no key.  Each
+// wave streams a quarter of the item's lists as hub numbers, kBitLanes lanes
+// to a list and eight consecutive numbers to a lane, every lane group taking
+// the wave's next list when its own ends.  R-MAT s22 with the paper's split
+// (6.7e9 probes in this bin): 6.9 ms with the hash tables, bound by the 65
+// vector and scalar instructions per 64 probes (hash, 16-byte read, four
+// compares into wave masks, the owners of the positions); 4.9 ms with bitmaps
+// over 4-byte entries, bound by the 34 GB of list lines that miss the L2s
+// (7 TB/s); 3.0 ms with the 2-byte numbers, and 0.8 ms for the anchors past the
+// hubs, which keep the tables.
+constexpr int kBitLanes = 4;
+constexpr int kBitDepth = 2;
+
+// Hits among the eight numbers of a lane, of which nv (any value) exist.
+// Numbers past them, and kNoHub, read a bit that is never set.
+__device__ __forceinline__ int32_t bit_hits(const uint32_t* bm, const uint32_t (&x)[4], int32_t nv) {
+    int32_t hits = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t h = k & 1 ? x[k >> 1] >> 16 : x[k >> 1] & 0xFFFFu;
+        const uint32_t v = k < nv ? h : (uint32_t)kNoHub;
+        hits += (int32_t)__builtin_amdgcn_ubfe(bm[v >> 5], v, 1);  // bit v mod 32
+    }
+    return hits;
+}
+
+__global__ void __launch_bounds__(256) k_light_bits(const int2* __restrict__ items,
+                                                     const int32_t* __restrict__ n_items_dev,
+                                                     const int32_t* __restrict__ rpO, const uint16_t* __restrict__ colH,
+                                                     const int32_t* __restrict__ rpD,
+                                                     const unsigned long long* __restrict__ cw,
+                                                     const int2* __restrict__ packU, const int2* __restrict__ packD,
+                                                     int64_t* __restrict__ acc) {
+    constexpr int G = kBitLanes, E = 8, STEP = E * G;
+    __shared__ __attribute__((aligned(16))) uint32_t bm[(kNoHub + 1) / 32];
+    const int t = threadIdx.x;
+    const int w = t >> 6;
+    const int lane = __lane_id();
+    const int gl = lane & (G - 1);
+    const uint64_t leaders = ~0ull / ((1ull << G) - 1);  // the first lane of every group
+    const uint64_t before = leaders & ((1ull << (lane - gl)) - 1);  // of the groups before this lane's
+    const int64_t n_items = n_items_dev[0];
+    int64_t total = 0;
+    for (int64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
+        const int2 item = items[it];
+        const bool kind_u = item.x >= 0;
+        const int32_t x = kind_u ? item.x : ~item.x;
+        const int32_t rs = rpO[x];
+        const int32_t d = rpO[x + 1] - rs;
+        const int2* L;
+        int32_t llen;
+        if (kind_u) { L = packU + rs; llen = d; }
+        else { const int32_t ds = rpD[x]; L = packD + ds; llen = cw_end(cw[x]) - ds; }
+        const int32_t j = item.y * kJL + w * 64 + lane;
+        int2 e = j < llen ? L[j] : make_int2(0, 0);  // lists of the wave, one per lane
+        __syncthreads();  // the item before is closed
+        for (int i = t; i < (kNoHub + 1) / 128; i += 256) reinterpret_cast<int4*>(bm)[i] = make_int4(0, 0, 0, 0);
+        // the lists that hold entries, moved together to the first lanes
+        const uint64_t some = ballot64(e.y > 0);
+        const int32_t nl = (int32_t)__popcll(some);
+        {
+            const int32_t lo = (int32_t)__popcll(some & lanes_below());
+            const int32_t to = 4 * (e.y > 0 ? lo : nl + lane - lo);
+            e.x = __builtin_amdgcn_ds_permute(to, e.x);
+            e.y = __builtin_amdgcn_ds_permute(to, e.y);
+        }
+        __syncthreads();
+        for (int32_t k = t; k < d; k += 256) {
+            const uint32_t v = colH[rs + k];
+            atomicOr(&bm[v >> 5], 1u << (v & 31));
+        }
+        __syncthreads();
+        int32_t next = 0;            // lists taken by the wave's groups
+        uint32_t cur = 0;            // this group's list: next number of this lane, and
+        int32_t rem = -E * gl;       // numbers of the list from there on (the same rem + E gl in the group)
+        auto step = [&](uint32_t (&v)[4], int32_t& nv) {  // false: nothing left
+            const uint64_t need = ballot64(rem + E * gl <= 0) & leaders;
+            if (need) {
+                const int32_t i = next + (int32_t)__popcll(need & before);
+                next += (int32_t)__popcll(need);
+                const int32_t s = __builtin_amdgcn_ds_bpermute(4 * i, e.x), n = __builtin_amdgcn_ds_bpermute(4 * i, e.y);
+                if (rem + E * gl <= 0) {
+                    cur = (uint32_t)s + E * gl;
+                    rem = i < nl ? n - E * gl : -STEP;
+                }
+            }
+            nv = rem;
+            if (nv > 0) __builtin_memcpy(v, colH + cur, 16);
+            cur += STEP;
+            rem -= STEP;
+            return ballot64(nv > 0) != 0;
+        };
+        // kBitDepth - 1 steps' loads are in flight during the probes of the oldest one
+        uint32_t v[kBitDepth][4];
+        int32_t nv[kBitDepth], hits = 0;
+#pragma unroll
+        for (int q = 0; q < kBitDepth; ++q) {
+            nv[q] = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[q][k] = 0;
+        }
+        bool on = true;
+#pragma unroll
+        for (int q = 0; q + 1 < kBitDepth; ++q) on = step(v[q], nv[q]);
+        while (on) {
+#pragma unroll
+            for (int q = 0; q < kBitDepth; ++q) {
+                constexpr int D = kBitDepth;
+                on = step(v[(q + D - 1) % D], nv[(q + D - 1) % D]);
+                hits += bit_hits(bm, v[q], nv[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q + 1 < kBitDepth; ++q) hits += bit_hits(bm, v[q], nv[q]);
+        total += hits;
+    }
+    total = wave_sum(total);
+    if (lane == 0 && total) atomicAdd((unsigned long long*)&acc[kTL], (unsigned long long)total);
 }
 
 // ---------------------------------------------------------------------------
@@ -1888,6 +2119,8 @@ static LightPlan light_plan(int64_t m, int32_t maxd, const CountConfig& cfg) {
     return pl;
 }
 
+static bool hub_lists_fit(int64_t n, int64_t m, const CountConfig& cfg);
+
 // Keys per rank tile for h heavy vertices: the largest of 1024, 512 and 256
 // that still gives every CU a tile (longer chunks take fewer rank atomics,
 // shorter ones more tiles when h is small).
@@ -1913,8 +2146,8 @@ static int resident_blocks(K kernel, size_t lds_bytes) {
 // starts are read back (one synchronisation), and each component with at
 // least three heavy vertices gets its own block, ranked (component, deg, id).
 static void count_union_heavy(const tc_graph_s* g, const CountUnion& un, const CountConfig& cfg, hipStream_t s,
-                              int64_t* acc, const DevBuf<int32_t>& heavy, const DevBuf<int32_t>& hpos,
-                              const int32_t* degp, const DevBuf<int32_t>& rpO, const DevBuf<int32_t>& colO) {
+                              int64_t* acc, const DevBuf<int32_t>& hpos, const int32_t* degp,
+                              const DevBuf<int32_t>& rpO, const DevBuf<int32_t>& colO) {
     (void)cfg;
     const int64_t n = g->n;
     const int32_t K = un.K;
@@ -1956,8 +2189,8 @@ static void count_union_heavy(const tc_graph_s* g, const CountUnion& un, const C
     DevBuf<int32_t> hlist(H, s), hidx(n, s), horder(H, s), hrank(H, s);
     const int32_t hm = (int32_t)H;
     const int32_t* h_dev = hpos.get() + n;
-    TC_LAUNCH("heavy_list", k_heavy_list, dim3(grid_for(n, 256)), dim3(256), 0, s, n, (const int32_t*)heavy.get(),
-              (const int32_t*)hpos.get(), hm, hlist.get(), acc);
+    TC_LAUNCH("heavy_list", k_heavy_list, dim3(grid_for(n, 256)), dim3(256), 0, s, n, (const int32_t*)hpos.get(), hm,
+              hlist.get(), acc);
     fill_i32(hrank.get(), 0, H, s);
     const int32_t chunk = rank_chunk(H);
     TC_LAUNCH("heavy_rank", k_heavy_rank, dim3((unsigned)std::min<int64_t>(
@@ -2048,7 +2281,28 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     DevBuf<uint64_t> ubits(NW, s);
     DevBuf<int32_t> upre(NW + 1, s);
     DevBuf<uint8_t> cls(n, s);
-    degree_classes(n, degp, cls.get(), s);
+    // Block anchors that are hubs are closed through bitmaps of hub numbers
+    // (all vertices of a small graph are hubs, by their own ids).  Numbering
+    // the hubs of a larger one takes 0.05 ms on R-MAT s22; where the counted
+    // graph has fewer than kBitDegree edges a vertex, block anchors are too few
+    // to pay for it (p = 0.1: none; p = 0.5: 1.14 -> 0.72 ms).
+    const LightPlan plan = light_plan(g->m, g->max_deg, cfg);
+    const double kept = sampled ? (double)thr / 9007199254740992.0 : 1.0;
+    const bool bits = !un && plan.dcap_lds && hub_lists_fit(n, g->m, cfg) &&
+                      (n <= kHubs || kept * (double)g->m >= kBitDegree * (double)n);
+    const bool numbered = bits && n > kHubs;
+    DevBuf<uint16_t> num(numbered ? n : 0, s);
+    if (numbered) {
+        DevBuf<int32_t> hist(257, s);
+        fill_i32(hist.get(), 0, 257, s);
+        const int64_t chunk = hub_chunk(n);
+        TC_LAUNCH("deg_class", k_deg_class_hist, dim3(ceil_div(n, chunk)), dim3(256), 0, s, n, chunk, degp, cls.get(),
+                  hist.get());
+        TC_LAUNCH("hub_ids", k_hub_ids, dim3(ceil_div(n, chunk)), dim3(256), 0, s, n, chunk, (const uint8_t*)cls.get(),
+                  (const int32_t*)hist.get(), hist.get() + 256, num.get());
+    } else {
+        degree_classes(n, degp, cls.get(), s);
+    }
     // the counted graph's own neighbour classes when it is the built graph
     const uint8_t* ncls = !sampled && !un ? g->ncls : nullptr;
     TC_LAUNCH("orient_bits", k_orient_bits, dim3(grid_for(NW, 16)), dim3(256), 0, s, v_src, v_col, E2, E2_dev,
@@ -2058,158 +2312,180 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     // up-list starts and d+ at every row start, and the per-vertex fields of
     // the light phase (classification of each vertex, its rowQ and v-major
     // slot counter), in one pass
-    DevBuf<int32_t> rpO(n + 1, s), dplus(n, s);
+    DevBuf<int32_t> rpO(n + 1, s);
     // up lists: m' <= m entries, then the sentinel -2 at index m, which the
     // closure's gathers read for positions past a range
     DevBuf<int32_t> colO(g->m + 1, s);
     const uint32_t sent = (uint32_t)g->m;
-    DevBuf<int32_t> heavy(n + 1, s), code(n, s), rpD(n + 1, s);
-    DevBuf<int4> rowQ(n, s);
-    DevBuf<int64_t> Wu(n, s), cw(n, s);
-    DevBuf<int32_t> wide(3 * (n + 1), s);  // vertices with d+ in (128, 256], (256, 512], > 512; counts first
-    unsigned long long* cwp = reinterpret_cast<unsigned long long*>(cw.get());
-    TC_LAUNCH("vertex_prep", k_vertex_prep, dim3(grid_for(n + 1, 256)), dim3(256), 0, s, n, E2,
-              (const uint64_t*)ubits.get(), (const int32_t*)upre.get(), degp, mp_dev, comp,
-              un ? un->mk : (const int64_t*)nullptr, cfg.heavy_num, cfg.heavy_den, v_row, rpO.get(), dplus.get(),
-              heavy.get(), code.get(), rpD.get(), rowQ.get(), cwp, wide.get(), colO.get() + sent);
+    DevBuf<int32_t> hpos(n + 1, s);  // heavy flags, then their prefix
+    {  // what only the light phase uses is freed before the heavy one
+        DevBuf<int32_t> rpD(n + 1, s);
+        DevBuf<int4> rowQ(n, s);
+        DevBuf<int64_t> Wu(n, s), cw(n, s);
+        DevBuf<int32_t> wide(3 * (n + 1), s);  // vertices with d+ in (128, 256], (256, 512], > 512; counts first
+        unsigned long long* cwp = reinterpret_cast<unsigned long long*>(cw.get());
+        TC_LAUNCH("vertex_prep", k_vertex_prep, dim3(grid_for(n + 1, 256)), dim3(256), 0, s, n, E2,
+                  (const uint64_t*)ubits.get(), (const int32_t*)upre.get(), degp, mp_dev, comp,
+                  un ? un->mk : (const int64_t*)nullptr, cfg.heavy_num, cfg.heavy_den, v_row,
+                  numbered ? (const uint16_t*)num.get() : (const uint16_t*)nullptr, rpO.get(), hpos.get(), rpD.get(),
+                  rowQ.get(), cwp, wide.get(), colO.get() + sent);
 
-    // one descriptor per up entry: the anchor work writes every entry of every
-    // light source's list, and only those lists are read
-    DevBuf<int2> packU(g->m, s);
-    compact_kept(v_col, v_src, E2, ubits.get(), upre.get(), colO.get(), nullptr, s, E2_dev);
+        // the hub numbers of the up lists' entries, and room for the ones that a
+        // load past a list's end reads
+        DevBuf<uint16_t> colH(bits ? (size_t)g->m + kHubTail : 0, s);
+        uint16_t* colh = bits ? colH.get() : nullptr;
+        // one descriptor per up entry: the anchor work writes every entry of every
+        // light source's list, and only those lists are read
+        DevBuf<int2> packU(g->m, s);
+        compact_kept(v_col, v_src, E2, ubits.get(), upre.get(), colO.get(), nullptr, s, E2_dev);
 
-    // 3. classification; anchor work (each light source's N+(u) in rank
-    //    order, one descriptor per pair); item lists
-    const int32_t vcap = cfg.vmajor_cap;
-    PhaseScope ph_light("light");
-    DevBuf<int64_t> Gx(un ? n : 0, s);  // per-list gather statistic (unions)
-    int64_t* gxp = un ? Gx.get() : nullptr;
-    DevBuf<int2> packD(vcap > 0 ? g->m : 1, s);  // v-major descriptors, rpD[v].. for vertex v
-    TC_LAUNCH("work", k_work_lanes, dim3(grid_for(n, 256)), dim3(256), 0, s, n, (const int4*)rowQ.get(),
-              colO.get(), vcap, packU.get(), packD.get(), cwp, Wu.get(), gxp, wide.get(), acc);
-    // longer lists by register class, persistent grids of one round of
-    // resident blocks; max_deg bounds every d+
-    auto launch_wide = [&](auto kernel, int c, int32_t lo, const char* name, std::atomic<int>& resident) {
-        if (g->max_deg <= lo) return;
-        int r = resident.load(std::memory_order_relaxed);
-        if (!r) {
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, kernel, 256, 0) != hipSuccess || r < 1) r = 1;
-            (void)hipGetLastError();
-            resident.store(r, std::memory_order_relaxed);
-        }
-        TC_LAUNCH(name, kernel, dim3((unsigned)(num_cus() * r)), dim3(256), 0, s,
-                  (const int32_t*)wide.get() + c * (n + 1) + 1, (const int4*)rowQ.get(), colO.get(), vcap,
-                  packU.get(), packD.get(), cwp, Wu.get(), gxp, acc);
-    };
-    static std::atomic<int> res_w[3];
-    launch_wide(k_work_wide<4>, 0, 128, "work_w4", res_w[0]);
-    launch_wide(k_work_wide<8>, 1, 256, "work_w8", res_w[1]);
-    launch_wide(k_work_wide<16>, 2, 512, "work_w16", res_w[2]);
-    DevBuf<int32_t> ntn(n + 1, s), nsm(n + 1, s), nlg(n + 1, s), nhg(n + 1, s);
-    const unsigned cgrid = std::min<unsigned>(grid_for(n, 256), kClassifyBlocks);
-    DevBuf<int64_t> cpart((size_t)cgrid * 9, s);
-    if (!un)
-        TC_LAUNCH("classify", k_classify, dim3(cgrid), dim3(256), 0, s, n, (const int32_t*)code.get(),
-                  (const int32_t*)dplus.get(), (const int64_t*)Wu.get(), (const unsigned long long*)cwp,
-                  (const int32_t*)rpD.get(), cfg.small_dmax, ntn.get(), nsm.get(), nlg.get(), nhg.get(),
-                  cpart.get());
-    else
-        TC_LAUNCH("classify", k_classify_union, dim3(cgrid), dim3(256), 0, s, n, comp, (const int32_t*)code.get(),
-                  (const int32_t*)dplus.get(), (const int64_t*)Wu.get(), (const int64_t*)gxp,
-                  (const unsigned long long*)cwp, (const int32_t*)rpD.get(), cfg.small_dmax, ntn.get(), nsm.get(),
-                  nlg.get(), nhg.get(), acc);
-    DevBuf<int32_t> sbase(n + 1, s), lbase(n + 1, s), hbase(n + 1, s), hpos(n + 1, s), tbase(n + 1, s);
-    {
-        const int32_t* in[4] = {nsm.get(), nlg.get(), nhg.get(), heavy.get()};
-        int32_t* out[4] = {sbase.get(), lbase.get(), hbase.get(), hpos.get()};
-        scan_exclusive_i32_x4(in, out, n, s);
-        scan_exclusive_i32(ntn.get(), tbase.get(), n, s);
-    }
-
-    // 4. light phase: three bins by anchor out-degree; each kernel is a
-    //    persistent grid that reads its item count from device memory
-    const int32_t maxd = g->max_deg;  // bounds every d+ of every sample
-    const LightPlan plan = light_plan(g->m, maxd, cfg);
-    // the item lists of the launched bins (a bin that is not launched has no items)
-    DevBuf<int2> items_t(items_max, s), items_s(items_max, s), items_l(plan.dcap_lds ? items_max : 0, s),
-        items_h(plan.dcap_global ? items_max : 0, s);
-    TC_LAUNCH("items", k_items, dim3(grid_for(n, 256)), dim3(256), 0, s, n, (const int32_t*)ntn.get(),
-              (const int32_t*)nsm.get(), (const int32_t*)nlg.get(), (const int32_t*)nhg.get(),
-              (const int32_t*)tbase.get(), (const int32_t*)sbase.get(), (const int32_t*)lbase.get(),
-              (const int32_t*)hbase.get(), (const int32_t*)dplus.get(), (const int64_t*)Wu.get(),
-              (const unsigned long long*)cwp, (const int32_t*)rpD.get(), items_t.get(), items_s.get(), items_l.get(),
-              items_h.get());
-    {
-        static const int resident[2] = {resident_blocks(k_light_tiny<false>, 0), resident_blocks(k_light_tiny<true>, 0)};
-        const int64_t blocks = (int64_t)num_cus() * std::min<int32_t>(cfg.light_blocks_per_cu, resident[un ? 1 : 0]);
-        auto kernel = un ? k_light_tiny<true> : k_light_tiny<false>;
-        TC_LAUNCH("light_tiny", kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const int2*)items_t.get(),
-                  (const int32_t*)tbase.get() + n, (const int32_t*)rpO.get(), (const int32_t*)colO.get(),
-                  (const int32_t*)rpD.get(), (const unsigned long long*)cwp, (const int2*)packU.get(),
-                  (const int2*)packD.get(), comp, acc);
-    }
-    {
-        const DevBuf<int2>& items = items_s;
-        // a persistent grid larger than what stays resident would run its last
-        // blocks in a second round: cap the blocks per CU at the resident count
-        // of the variant launched
-        static const int resident[2] = {resident_blocks(k_light_small<128, false>, 0),
-                                        resident_blocks(k_light_small<128, true>, 0)};
-        const int64_t blocks = (int64_t)num_cus() * std::min<int32_t>(cfg.light_blocks_per_cu, resident[un ? 1 : 0]);
-        auto kernel = un ? k_light_small<128, true> : k_light_small<128, false>;
-        TC_LAUNCH("light_small", kernel, dim3((unsigned)blocks), dim3(256), 0, s,
-                  (const int2*)items.get(), (const int32_t*)sbase.get() + n, (const int32_t*)rpO.get(),
-                  (const int32_t*)colO.get(), (const int32_t*)rpD.get(), (const unsigned long long*)cwp,
-                  (const int2*)packU.get(), (const int2*)packD.get(), sent, comp, acc);
-    }
-    auto launch_large = [&](const DevBuf<int2>& items, const DevBuf<int32_t>& base, int32_t dcap, bool global) {
-        // tab: 4 * next_pow2(d) <= 4 * dcap slots, P: kJL+1, D: kJL, flags: 4*64*kU (16-byte multiple)
-        const size_t per_block = (size_t)large_block_words(dcap);
-        const size_t lds_bytes = sizeof(int32_t) * per_block;
-        if (!global) {
-            // one round of resident blocks (LDS and registers permitting, at most 8 per CU)
-            // by variant and log2(dcap); every thread computes the same value
-            static std::atomic<int> resident[2][16];
-            int lgc = 0;
-            while ((1 << lgc) < dcap) ++lgc;
-            auto kernel = un ? k_light_large<false, true> : k_light_large<false, false>;
-            int r = resident[un ? 1 : 0][lgc].load(std::memory_order_relaxed);
+        // 3. classification; anchor work (each light source's N+(u) in rank
+        //    order, one descriptor per pair); item lists
+        const int32_t vcap = cfg.vmajor_cap;
+        PhaseScope ph_light("light");
+        DevBuf<int64_t> Gx(un ? n : 0, s);  // per-list gather statistic (unions)
+        int64_t* gxp = un ? Gx.get() : nullptr;
+        DevBuf<int2> packD(vcap > 0 ? g->m : 1, s);  // v-major descriptors, rpD[v].. for vertex v
+        TC_LAUNCH("work", k_work_lanes, dim3(grid_for(n, 256)), dim3(256), 0, s, n, (const int4*)rowQ.get(),
+                  colO.get(), colh, vcap, packU.get(), packD.get(), cwp, Wu.get(), gxp, wide.get(), acc);
+        // longer lists by register class, persistent grids of one round of
+        // resident blocks; max_deg bounds every d+
+        auto launch_wide = [&](auto kernel, int c, int32_t lo, const char* name, std::atomic<int>& resident) {
+            if (g->max_deg <= lo) return;
+            int r = resident.load(std::memory_order_relaxed);
             if (!r) {
-                r = resident_blocks(kernel, lds_bytes);
-                resident[un ? 1 : 0][lgc].store(r, std::memory_order_relaxed);
+                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, kernel, 256, 0) != hipSuccess || r < 1) r = 1;
+                (void)hipGetLastError();
+                resident.store(r, std::memory_order_relaxed);
             }
-            const int64_t per_cu = std::min(r, 8);
-            const int64_t blocks = (int64_t)num_cus() * per_cu;
-            TC_LAUNCH("light_large", kernel, dim3((unsigned)blocks), dim3(256), lds_bytes, s,
-                      (const int2*)items.get(), (const int32_t*)base.get() + n, (const int32_t*)rpO.get(),
-                      (const int32_t*)colO.get(), (const int32_t*)rpD.get(), (const unsigned long long*)cwp,
-                      (const int2*)packU.get(), (const int2*)packD.get(), dcap, (int32_t*)nullptr, sent, comp,
+            TC_LAUNCH(name, kernel, dim3((unsigned)(num_cus() * r)), dim3(256), 0, s,
+                      (const int32_t*)wide.get() + c * (n + 1) + 1, (const int4*)rowQ.get(), colO.get(), colh, vcap,
+                      packU.get(), packD.get(), cwp, Wu.get(), gxp, acc);
+        };
+        static std::atomic<int> res_w[3];
+        launch_wide(k_work_wide<4>, 0, 128, "work_w4", res_w[0]);
+        launch_wide(k_work_wide<8>, 1, 256, "work_w8", res_w[1]);
+        launch_wide(k_work_wide<16>, 2, 512, "work_w16", res_w[2]);
+        // item counts of the bins, then their prefixes in place
+        DevBuf<int32_t> tbase(n + 1, s), sbase(n + 1, s), lbase(n + 1, s), hbase(n + 1, s), bbase(bits ? n + 1 : 0, s);
+        const ItemBins bin{tbase.get(), sbase.get(), bits ? bbase.get() : nullptr, lbase.get(), hbase.get()};
+        const int32_t* nbits = bits ? bbase.get() + n : nullptr;
+        const unsigned cgrid = std::min<unsigned>(grid_for(n, 256), kClassifyBlocks);
+        DevBuf<int64_t> cpart((size_t)cgrid * 9, s);
+        if (!un)
+            TC_LAUNCH("classify", k_classify, dim3(cgrid), dim3(256), 0, s, n, (const int32_t*)rpO.get(),
+                      (const int32_t*)hpos.get(), (const int4*)rowQ.get(), (const int64_t*)Wu.get(),
+                      (const unsigned long long*)cwp, (const int32_t*)rpD.get(), cfg.small_dmax, bin, cpart.get());
+        else
+            TC_LAUNCH("classify", k_classify_union, dim3(cgrid), dim3(256), 0, s, n, comp,
+                      (const int32_t*)rpO.get(), (const int32_t*)hpos.get(), (const int64_t*)Wu.get(),
+                      (const int64_t*)gxp, (const unsigned long long*)cwp, (const int32_t*)rpD.get(), cfg.small_dmax, bin,
                       acc);
-        } else {
-            const int64_t blocks = (int64_t)num_cus();
-            DevBuf<int32_t> gscr((size_t)blocks * per_block, s);
-            auto kernel = un ? k_light_large<true, true> : k_light_large<true, false>;
-            TC_LAUNCH("light_huge", kernel, dim3((unsigned)blocks), dim3(256), 0, s,
-                      (const int2*)items.get(), (const int32_t*)base.get() + n, (const int32_t*)rpO.get(),
-                      (const int32_t*)colO.get(), (const int32_t*)rpD.get(), (const unsigned long long*)cwp,
-                      (const int2*)packU.get(), (const int2*)packD.get(), dcap, gscr.get(), sent, comp, acc);
+        {
+            int32_t* const each[6] = {tbase.get(), sbase.get(), lbase.get(), hbase.get(), hpos.get(), bbase.get()};
+            scan_exclusive_i32_each(each, bits ? 6 : 5, n, s);
         }
-    };
-    if (plan.dcap_lds) launch_large(items_l, lbase, plan.dcap_lds, false);
-    if (plan.dcap_global) launch_large(items_h, hbase, plan.dcap_global, true);
+
+        // 4. light phase: bins by anchor out-degree; each kernel is a
+        //    persistent grid that reads its item count from device memory
+        // the item lists of the launched bins (a bin that is not launched has no items)
+        DevBuf<int2> items_t(items_max, s), items_s(items_max, s), items_l(plan.dcap_lds ? items_max : 0, s),
+            items_h(plan.dcap_global ? items_max : 0, s);
+        TC_LAUNCH("items", k_items, dim3(grid_for(n, 256)), dim3(256), 0, s, n, bin, (const int32_t*)rpO.get(),
+                  (const int64_t*)Wu.get(), (const unsigned long long*)cwp, (const int32_t*)rpD.get(), items_t.get(),
+                  items_s.get(), items_l.get(), items_h.get());
+        {
+            static const int resident[2] = {resident_blocks(k_light_tiny<false>, 0), resident_blocks(k_light_tiny<true>, 0)};
+            const int64_t blocks = (int64_t)num_cus() * std::min<int32_t>(cfg.light_blocks_per_cu, resident[un ? 1 : 0]);
+            auto kernel = un ? k_light_tiny<true> : k_light_tiny<false>;
+            TC_LAUNCH("light_tiny", kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const int2*)items_t.get(),
+                      (const int32_t*)tbase.get() + n, (const int32_t*)rpO.get(), (const int32_t*)colO.get(),
+                      (const int32_t*)rpD.get(), (const unsigned long long*)cwp, (const int2*)packU.get(),
+                      (const int2*)packD.get(), comp, acc);
+        }
+        {
+            const DevBuf<int2>& items = items_s;
+            // a persistent grid larger than what stays resident would run its last
+            // blocks in a second round: cap the blocks per CU at the resident count
+            // of the variant launched
+            static const int resident[2] = {resident_blocks(k_light_small<128, false>, 0),
+                                            resident_blocks(k_light_small<128, true>, 0)};
+            const int64_t blocks = (int64_t)num_cus() * std::min<int32_t>(cfg.light_blocks_per_cu, resident[un ? 1 : 0]);
+            auto kernel = un ? k_light_small<128, true> : k_light_small<128, false>;
+            TC_LAUNCH("light_small", kernel, dim3((unsigned)blocks), dim3(256), 0, s,
+                      (const int2*)items.get(), (const int32_t*)sbase.get() + n, (const int32_t*)rpO.get(),
+                      (const int32_t*)colO.get(), (const int32_t*)rpD.get(), (const unsigned long long*)cwp,
+                      (const int2*)packU.get(), (const int2*)packD.get(), sent, comp, acc);
+        }
+        if (bits) {
+            static const int resident = resident_blocks(k_light_bits, 0);
+            TC_LAUNCH("light_bits", k_light_bits, dim3((unsigned)(num_cus() * std::min(resident, 8))), dim3(256), 0, s,
+                      (const int2*)items_l.get(), nbits, (const int32_t*)rpO.get(),
+                      (const uint16_t*)colh, (const int32_t*)rpD.get(), (const unsigned long long*)cwp,
+                      (const int2*)packU.get(), (const int2*)packD.get(), acc);
+        }
+        auto launch_large = [&](const DevBuf<int2>& items, const DevBuf<int32_t>& base, int32_t dcap, bool global) {
+            // tab: 4 * next_pow2(d) <= 4 * dcap slots, P: kJL+1, D: kJL, flags: 4*64*kU (16-byte multiple)
+            const size_t per_block = (size_t)large_block_words(dcap);
+            const size_t lds_bytes = sizeof(int32_t) * per_block;
+            if (!global) {
+                // one round of resident blocks (LDS and registers permitting, at most 8 per CU)
+                // by variant and log2(dcap); every thread computes the same value
+                static std::atomic<int> resident[2][16];
+                int lgc = 0;
+                while ((1 << lgc) < dcap) ++lgc;
+                auto kernel = un ? k_light_large<false, true> : k_light_large<false, false>;
+                int r = resident[un ? 1 : 0][lgc].load(std::memory_order_relaxed);
+                if (!r) {
+                    r = resident_blocks(kernel, lds_bytes);
+                    resident[un ? 1 : 0][lgc].store(r, std::memory_order_relaxed);
+                }
+                const int64_t per_cu = std::min(r, 8);
+                const int64_t blocks = (int64_t)num_cus() * per_cu;
+                TC_LAUNCH("light_large", kernel, dim3((unsigned)blocks), dim3(256), lds_bytes, s,
+                          (const int2*)items.get(), nbits, (const int32_t*)base.get() + n,
+                          (const int32_t*)rpO.get(), (const int32_t*)colO.get(), (const int32_t*)rpD.get(),
+                          (const unsigned long long*)cwp, (const int2*)packU.get(), (const int2*)packD.get(), dcap,
+                          (int32_t*)nullptr, sent, comp, acc);
+            } else {
+                const int64_t blocks = (int64_t)num_cus();
+                DevBuf<int32_t> gscr((size_t)blocks * per_block, s);
+                auto kernel = un ? k_light_large<true, true> : k_light_large<true, false>;
+                TC_LAUNCH("light_huge", kernel, dim3((unsigned)blocks), dim3(256), 0, s,
+                          (const int2*)items.get(), (const int32_t*)nullptr, (const int32_t*)base.get() + n,
+                          (const int32_t*)rpO.get(), (const int32_t*)colO.get(), (const int32_t*)rpD.get(),
+                          (const unsigned long long*)cwp, (const int2*)packU.get(), (const int2*)packD.get(), dcap,
+                          gscr.get(), sent, comp, acc);
+            }
+        };
+        // hubs by their own ids: every block anchor is in the bits bin
+        const bool all_bits = bits && !numbered;
+        if (plan.dcap_lds && !all_bits) launch_large(items_l, lbase, plan.dcap_lds, false);
+        if (plan.dcap_global && !all_bits) launch_large(items_h, hbase, plan.dcap_global, true);
+
+        {
+            PhaseScope ph_finish("finish");
+            if (!un)
+                TC_LAUNCH("finish", k_finish, dim3(1), dim3(576), 0, s, mp_dev, (const int32_t*)hpos.get() + n,
+                          (const int64_t*)cpart.get(), (int32_t)cgrid, acc);
+            else
+                TC_LAUNCH("finish_union", k_finish_union, dim3(ceil_div(K, 256)), dim3(256), 0, s, K, un->off, un->mk,
+                          (const int32_t*)hpos.get(), acc);
+        }
+    }
 
     // 5. heavy phase: sized by the bound, trimmed to the device's h inside the
     //    kernels (a union: one block per component, sized from the heavy
     //    counts read back here)
     if (un) {
-        count_union_heavy(g, *un, cfg, s, acc, heavy, hpos, degp, rpO, colO);
+        count_union_heavy(g, *un, cfg, s, acc, hpos, degp, rpO, colO);
     } else if (hmax >= 3) {
         PhaseScope ph("heavy");
         DevBuf<int32_t> hlist(hmax, s), hidx(n, s), horder(hmax, s);
         const int32_t* h_dev = hpos.get() + n;
         const int32_t hm = (int32_t)hmax;
-        TC_LAUNCH("heavy_list", k_heavy_list, dim3(grid_for(n, 256)), dim3(256), 0, s, n,
-                  (const int32_t*)heavy.get(), (const int32_t*)hpos.get(), hm, hlist.get(), acc);
+        TC_LAUNCH("heavy_list", k_heavy_list, dim3(grid_for(n, 256)), dim3(256), 0, s, n, (const int32_t*)hpos.get(),
+                  hm, hlist.get(), acc);
         DevBuf<int32_t> hrank(hmax, s);
         fill_i32(hrank.get(), 0, hmax, s);
         const int32_t chunk = rank_chunk(hmax);
@@ -2235,13 +2511,6 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
         TC_LAUNCH("heavy_mfma", k_heavy_mfma, dim3((unsigned)mblocks), dim3(256), 0, s, (const uint8_t*)U.get(),
                   (const uint8_t*)UT.get(), h_dev, hm, acc);
     }
-    PhaseScope ph_finish("finish");
-    if (!un)
-        TC_LAUNCH("finish", k_finish, dim3(1), dim3(576), 0, s, mp_dev, (const int32_t*)hpos.get() + n,
-                  (const int64_t*)cpart.get(), (int32_t)cgrid, acc);
-    else
-        TC_LAUNCH("finish_union", k_finish_union, dim3(ceil_div(K, 256)), dim3(256), 0, s, K, un->off, un->mk,
-                  (const int32_t*)hpos.get(), acc);
 }
 
 void count_enqueue(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t salt, const CountConfig& cfg,
@@ -2275,46 +2544,65 @@ void counts_from_slots(const int64_t* hacc, tc_counts* out) {
     *out = res;
 }
 
-int64_t count_bytes(int64_t n, int64_t m, int32_t maxd, int sampled, const CountConfig& cfg) {
+// Sums of the sizes of a count's allocations: those that both phases use, the
+// light phase's, and the heavy phase's, which takes the light one's place.
+struct CountBytes {
+    int64_t both = 0, light = 0, heavy = 0;
+};
+
+static int64_t heavy_phase_bytes(int64_t n, int64_t m, const CountConfig& cfg) {
+    const int64_t hmax = heavy_bound(n, m, cfg.heavy_num, cfg.heavy_den);
+    if (hmax < 3) return 0;
+    const int64_t hp = heavy_pad(hmax);
+    // list, order, rank, index, U, UT
+    return 3 * region_bytes(4 * hmax) + region_bytes(4 * n) + 2 * region_bytes(hp * hp);
+}
+
+// Whether the hub numbers fit the memory that a count takes anyhow: the heavy
+// phase's, which is not in use during the light one.
+static bool hub_lists_fit(int64_t n, int64_t m, const CountConfig& cfg) {
+    return region_bytes(2 * (m + kHubTail)) <= heavy_phase_bytes(n, m, cfg);
+}
+
+static CountBytes count_parts(int64_t n, int64_t m, int32_t maxd, int sampled, bool hubs, const CountConfig& cfg) {
     auto rb = region_bytes;
-    int64_t b = rb(8 * kCountSlots);  // acc of count_core
+    CountBytes c;
     const int64_t E2 = 2 * m;
-    if (n == 0 || E2 == 0) return b;
+    if (n == 0 || E2 == 0) return c;
     const int64_t NW = (E2 + 63) / 64;
+    int64_t b = 0;
     if (sampled)  // keep bits and prefix, rows, degrees, entries, staged entries
         b += rb(8 * NW) + rb(4 * (NW + 1)) + rb(4 * (n + 1)) + rb(4 * n) + 4 * rb(4 * E2) + scan_scratch_bytes(NW);
     b += rb(n) + rb(8 * NW) + rb(4 * (NW + 1)) + scan_scratch_bytes(NW);  // degree classes, orientation bits
-    b += rb(4 * (n + 1)) + rb(4 * n) + rb(4 * (m + 1));            // rpO, d+, up lists and their sentinel
-    b += 2 * rb(4 * (n + 1)) + rb(4 * n);                          // heavy, code, descriptor slots
-    b += rb(16 * n) + 2 * rb(8 * n) + rb(12 * (n + 1));            // rowQ, Wu, cw, wide-list vertices
+    b += n > kHubs ? rb(2 * n) + rb(4 * 257) : rb(2);              // hub numbers, class counts
+    b += 2 * rb(4 * (n + 1)) + rb(4 * (m + 1));                    // rpO, heavy prefix, up lists and their sentinel
+    c.both = b;
+    b = rb(4 * (n + 1)) + rb(16 * n) + 2 * rb(8 * n) + rb(12 * (n + 1));  // rpD, rowQ, Wu, cw, wide-list vertices
+    b += hubs && hub_lists_fit(n, m, cfg) ? rb(2 * (m + kHubTail)) : rb(2);
     b += rb(8 * m) + rb(8 * (cfg.vmajor_cap > 0 ? m : 1));         // packed descriptors
-    b += 9 * rb(4 * (n + 1)) + scan_x4_scratch_bytes(n) + scan_scratch_bytes(n);  // item counts and bases
-    b += rb(8 * (2 * n + E2 / kJL + 2));                                           // tiny item list
+    b += (hubs ? 5 : 4) * rb(4 * (n + 1)) + rb(4) + scan_each_scratch_bytes(6, n);  // item counts and their prefixes
     b += rb(8 * 9 * (int64_t)std::min<int64_t>((n + 255) / 256, kClassifyBlocks));  // classification partials
     const int64_t items_max = 2 * n + E2 / kJL + 2;
-    b += rb(8 * items_max);
+    b += 2 * rb(8 * items_max);
     const LightPlan plan = light_plan(m, maxd, cfg);
     b += plan.dcap_lds ? rb(8 * items_max) : rb(8);
     b += plan.dcap_global ? rb(8 * items_max) + rb(4 * (int64_t)num_cus() * large_block_words(plan.dcap_global)) : rb(8);
-    const int64_t hmax = heavy_bound(n, m, cfg.heavy_num, cfg.heavy_den);
-    if (hmax >= 3) {
-        const int64_t hp = heavy_pad(hmax);
-        b += 3 * rb(4 * hmax) + rb(4 * n) + 2 * rb(hp * hp);  // list, order, rank, index, U, UT
-    }
-    return b;
+    c.light = b;
+    c.heavy = heavy_phase_bytes(n, m, cfg);
+    return c;
+}
+
+int64_t count_bytes(int64_t n, int64_t m, int32_t maxd, int sampled, const CountConfig& cfg) {
+    const CountBytes c = count_parts(n, m, maxd, sampled, true, cfg);
+    return region_bytes(8 * kCountSlots) + c.both + std::max(c.light, c.heavy);  // acc of count_core first
 }
 
 int64_t count_union_bytes(int64_t n, int64_t m, int32_t maxd, int32_t K, int64_t h, int64_t ubytes, int64_t ntiles,
                           const CountConfig& cfg) {
     auto rb = region_bytes;
-    // the single count's allocations without its heavy phase
-    int64_t b = count_bytes(n, m, maxd, 0, cfg) - rb(8 * kCountSlots);
-    const int64_t hb = heavy_bound(n, m, cfg.heavy_num, cfg.heavy_den);
-    if (n > 0 && m > 0 && hb >= 3) {
-        const int64_t hp = heavy_pad(hb);
-        b -= 3 * rb(4 * hb) + rb(4 * n) + 2 * rb(hp * hp);
-    }
-    b += rb(8 * n) + rb(4 * (n + 1));  // per-list gather statistic; the zero row of an edgeless union
+    const CountBytes c = count_parts(n, m, maxd, 0, false, cfg);
+    int64_t b = c.both + c.light + rb(2);                  // the single count's without its heavy phase, and
+    b += region_bytes(8 * n) + region_bytes(4 * (n + 1));  // the per-list gather statistic, an edgeless union's zero row
     // heavy blocks: starts, block sizes and offsets, tile list, ranks, two matrices
     b += rb(4 * ((int64_t)K + 1)) + rb(4 * (int64_t)K) + 2 * rb(8 * ((int64_t)K + 1)) + rb(8 * (int64_t)K) +
          rb(16 * ntiles) + 3 * rb(4 * h) + rb(4 * n) + 2 * rb(ubytes);

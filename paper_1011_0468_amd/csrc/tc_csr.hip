@@ -811,7 +811,7 @@ int build_csr_t(const CsrPlan& c, int64_t n, int64_t P, const int32_t* src, cons
             TC_LAUNCH("csr_bins", k_csr_bins, dim3(ceil_div(c.bins, 256)), dim3(256), 0, s, (int)c.bins, c.ghist, cap,
                       (const int32_t*)binrows.get(), start, unit0, tile0, concat);
             int32_t* const four[4] = {start, unit0, tile0, concat};
-            scan_exclusive_i32_x4(four, four, c.bins, s);
+            scan_exclusive_i32_each(four, 4, c.bins, s);
             TC_LAUNCH("csr_units", k_csr_units, dim3(ceil_div(c.bins, 256)), dim3(256), 0, s, (int)c.bins, cap,
                       (const int32_t*)start, (const int32_t*)unit0, (const int32_t*)tile0, (const int32_t*)concat,
                       cursor, units.get(), segs.get(), tile_seg, info);
@@ -920,7 +920,7 @@ int64_t build_csr_bytes(int64_t n, int64_t num_pairs) {
     b += rb(4 * small_ints(c, N)) + rb(n);
     // the partition's scratch, then (in its place) the passes over larger windows
     int64_t part = rb(4 * c.ghist * c.bins) + rb(4 * c.gpart * c.parts) +
-                   std::max(two ? rb(K * N) : 0, scan_x4_scratch_bytes(c.bins));
+                   std::max(two ? rb(K * N) : 0, scan_each_scratch_bytes(4, c.bins));
     int64_t big = 0;
     if (const int64_t t = max_big_tiles(N))
         big = rb(KW * N) + rb(4 * (kRadix * t + 1)) + scan_scratch_bytes(kRadix * t);

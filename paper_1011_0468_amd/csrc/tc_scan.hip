@@ -12,7 +12,7 @@ constexpr int kScanTile = kScanThreads * kScanItems;
 
 // Up to kScanBatch arrays of one length scanned by the same launches:
 // blockIdx.y selects the array; its block sums sit at bsum + y * bstride.
-constexpr int kScanBatch = 4;
+constexpr int kScanBatch = 6;
 struct ScanArrays {
     const int32_t* in[kScanBatch];
     int32_t* out[kScanBatch];
@@ -127,18 +127,15 @@ void scan_exclusive_i32(const int32_t* in, int32_t* out, int64_t N, hipStream_t 
     scan_batch(a, 1, N, s);
 }
 
-void scan_exclusive_i32_x4(const int32_t* const in[4], int32_t* const out[4], int64_t N, hipStream_t s) {
-    static_assert(kScanBatch == 4, "four arrays per batch");
+void scan_exclusive_i32_each(int32_t* const arrays[], int K, int64_t N, hipStream_t s) {
+    if (K < 1 || K > kScanBatch) fail(TC_ERR_DEVICE, "scan of too many arrays");
     ScanArrays a{};
-    for (int k = 0; k < 4; ++k) {
-        a.in[k] = in[k];
-        a.out[k] = out[k];
-    }
-    scan_batch(a, 4, N, s);
+    for (int k = 0; k < K; ++k) a.in[k] = a.out[k] = arrays[k];
+    scan_batch(a, K, N, s);
 }
 
 int64_t scan_scratch_bytes(int64_t N) { return batch_scratch_bytes(1, N); }
-int64_t scan_x4_scratch_bytes(int64_t N) { return batch_scratch_bytes(4, N); }
+int64_t scan_each_scratch_bytes(int K, int64_t N) { return batch_scratch_bytes(K, N); }
 
 void fill_i32(int32_t* p, int32_t v, int64_t N, hipStream_t s) { fill_impl<int32_t>(p, v, N, s); }
 void fill_i64(int64_t* p, int64_t v, int64_t N, hipStream_t s) { fill_impl<int64_t>(p, v, N, s); }
