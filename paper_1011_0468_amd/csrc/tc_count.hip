@@ -65,11 +65,15 @@ constexpr int kU = 4;
 // 8 KB of LDS, and a list of numbers half the bytes of a list of ids.
 constexpr int kHubs = 65535;
 constexpr int32_t kNoHub = 65535;
-// Vertices per block of the passes that number the hubs, at least.
-constexpr int64_t kHubChunk = 4096;
+constexpr int64_t kHubChunk = 4096;  // vertices per block of the pass that numbers them
 constexpr int kHubTail = 8;
 // Edges per vertex of the counted graph from which hubs are numbered.
-constexpr double kBitDegree = 4.0;
+constexpr double kBitDegree = 6.0;
+// Edges of the counted graph from which v-major pairs are placed by partition
+// (three more launches): without and with it R-MAT s16 to s17 of 0.9 to 1.0 M
+// edges take 522 and 466, 495 and 447 us, samples of 0.45 to 0.5 M edges 353
+// and 352, 342 and 341, and smaller ones 5 to 10% longer with it.
+constexpr double kDeferPairs = 3 << 18;
 
 // ---------------------------------------------------------------------------
 // orientation
@@ -80,41 +84,40 @@ __global__ void k_deg_class(int64_t n, const int32_t* __restrict__ degp, uint8_t
         cls[x] = (uint8_t)deg_class(degp[x]);
 }
 
-int64_t hub_chunk(int64_t n) { return std::max(kHubChunk, (n + 1023) / 1024); }
-
-// k_deg_class, and the number of vertices of every class added into hist[256].
-__global__ void __launch_bounds__(256) k_deg_class_hist(int64_t n, int64_t chunk, const int32_t* __restrict__ degp,
+// k_deg_class, and the number of vertices of every class from cmin up added
+// into hist[256].
+__global__ void __launch_bounds__(256) k_deg_class_hist(int64_t n, uint32_t cmin, const int32_t* __restrict__ degp,
                                                          uint8_t* __restrict__ cls, int32_t* __restrict__ hist) {
     __shared__ int32_t cnt[256];
     cnt[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t x1 = min(n, (blockIdx.x + 1) * chunk);
-    for (int64_t x = blockIdx.x * chunk + threadIdx.x; x < x1; x += 256) {
+    for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < n; x += (int64_t)gridDim.x * 256) {
         const uint32_t c = deg_class(degp[x]);
         cls[x] = (uint8_t)c;
-        atomicAdd(&cnt[c], 1);
+        if (c >= cmin) atomicAdd(&cnt[c], 1);
     }
     __syncthreads();
     if (cnt[threadIdx.x]) atomicAdd(&hist[threadIdx.x], cnt[threadIdx.x]);
 }
 
-// The lowest class c >= 1 such that at most kHubs vertices are of class c or
-// above (hist: vertices per class): the hubs' classes.  One wave; 256 if none.
-__device__ __forceinline__ uint32_t hub_class(const int32_t* __restrict__ hist, int lane) {
+// The lowest class c >= cmin such that at most kHubs vertices are of class c
+// or above (hist: vertices per class): the hubs' classes.  256 if none; whole
+// wave.
+__device__ __forceinline__ uint32_t hub_class(const int32_t* __restrict__ hist, uint32_t cmin, int lane) {
     // lane l holds classes 255 - 4 l .. 252 - 4 l, highest first
-    int64_t above = 0, own[4];
+    int32_t above = 0, own[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         own[k] = hist[255 - 4 * lane - k];
         above += own[k];
     }
-    int64_t run = wave_inclusive_sum(above) - above;  // vertices of the classes before this lane's
+    int32_t run = wave_inclusive_sum(above) - above;  // vertices of the classes before this lane's
     uint32_t low = 256;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         run += own[k];
         const uint32_t c = (uint32_t)(255 - 4 * lane - k);
-        if (run <= kHubs && c >= 1) low = c;
+        if (run <= kHubs && c >= cmin) low = c;
     }
     // the sums only grow, so the classes that fit are the highest ones
 #pragma unroll
@@ -123,36 +126,39 @@ __device__ __forceinline__ uint32_t hub_class(const int32_t* __restrict__ hist, 
 }
 
 // num[x] = the number of vertex x among the hubs (any order, hubs counted in
-// *nhub), kNoHub if it is none.
-__global__ void __launch_bounds__(256) k_hub_ids(int64_t n, int64_t chunk, const uint8_t* __restrict__ cls,
+// *nhub), kNoHub if it is none.  A block takes kHubChunk vertices, 16 a thread.
+__global__ void __launch_bounds__(256) k_hub_ids(int64_t n, uint32_t cmin, const uint8_t* __restrict__ cls,
                                                   const int32_t* __restrict__ hist, int32_t* __restrict__ nhub,
                                                   uint16_t* __restrict__ num) {
-    __shared__ int32_t wsum[4], base_s;
-    const int lane = __lane_id(), w = threadIdx.x >> 6;
-    const uint32_t c0 = hub_class(hist, lane);
-    const int64_t x0 = blockIdx.x * chunk, x1 = min(n, x0 + chunk);
+    constexpr int E = 16;
+    static_assert(kHubChunk == 256 * E, "vertices of a block");
+    __shared__ int32_t tmp[5], first;
+    const uint32_t c0 = hub_class(hist, cmin, __lane_id());
+    const int64_t x0 = (int64_t)blockIdx.x * kHubChunk + (int64_t)threadIdx.x * E;
+    uint8_t c[E];
+    if (x0 + E <= n) {
+        __builtin_memcpy(c, cls + x0, E);
+    } else {
+#pragma unroll
+        for (int k = 0; k < E; ++k) c[k] = x0 + k < n ? cls[x0 + k] : 0;  // c0 >= 1
+    }
     int32_t mine = 0;
-    for (int64_t x = x0 + threadIdx.x; x < x1; x += 256) mine += cls[x] >= c0 ? 1 : 0;
-    mine = wave_sum(mine);
-    if (lane == 0) wsum[w] = mine;
+#pragma unroll
+    for (int k = 0; k < E; ++k) mine += c[k] >= c0 ? 1 : 0;
+    int32_t total;
+    int32_t at = block_exclusive_sum<256>(mine, tmp, &total);
+    if (threadIdx.x == 0) first = total ? atomicAdd(nhub, total) : 0;
     __syncthreads();
-    if (threadIdx.x == 0) base_s = atomicAdd(nhub, wsum[0] + wsum[1] + wsum[2] + wsum[3]);
-    __syncthreads();
-    int32_t at = base_s;
-    for (int64_t xb = x0; xb < x1; xb += 256) {  // block-uniform
-        const int64_t x = xb + threadIdx.x;
-        const bool hub = x < x1 && cls[x] >= c0;
-        const uint64_t b = ballot64(hub);
-        __syncthreads();  // the sums of the round before have been read
-        if (lane == 0) wsum[w] = (int32_t)__popcll(b);
-        __syncthreads();
-        int32_t pre = at, tot = 0;
-        for (int i = 0; i < 4; ++i) {
-            pre += i < w ? wsum[i] : 0;
-            tot += wsum[i];
-        }
-        if (x < x1) num[x] = (uint16_t)(hub ? pre + (int32_t)__popcll(b & lanes_below()) : kNoHub);
-        at += tot;
+    at += first;
+    uint16_t out[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) out[k] = (uint16_t)(c[k] >= c0 ? at++ : kNoHub);
+    if (x0 + E <= n) {
+        __builtin_memcpy(num + x0, out, sizeof(out));
+    } else {
+#pragma unroll
+        for (int k = 0; k < E; ++k)
+            if (x0 + k < n) num[x0 + k] = out[k];
     }
 }
 
@@ -344,7 +350,8 @@ __device__ __forceinline__ uint64_t rank_key(int32_t deg, int32_t w) {
 // is in rank order, only its entries after k can close (u, v) (a common
 // out-neighbour w of u and v ranks above v), and a pair with none gets (0, 0).
 // u-major: (start of N+(v), d+(v)).  v-major: (start of the streamed part of
-// N+(u), minus its length), placed by the caller through claim_vmajor.
+// N+(u), minus its length), placed by the caller through claim_vmajor, or (packD
+// null) left in packU as (v, minus the length) for k_vmajor_part.
 __device__ __forceinline__ int2 pair_desc(int32_t rs, int32_t d, int32_t k, int4 qv, bool sorted, int32_t vcap,
                                           int64_t& wu, int64_t& gsum) {
     const int32_t dv = qv.y >= 0 ? qv.y : ~qv.y;
@@ -503,8 +510,8 @@ __device__ __forceinline__ void work_groups(uint64_t mask, const int4& q, int64_
             if (colH) colH[rs + pos] = (uint16_t)qv.w;
             int2 pk = pair_desc(rs, d, pos, qv, true, vcap, wu, gl);
             if (pk.y < 0) {
-                packD[claim_vmajor(cw, v, -pk.y)] = make_int2(pk.x, -pk.y);
-                pk = make_int2(0, 0);
+                if (packD) packD[claim_vmajor(cw, v, -pk.y)] = make_int2(pk.x, -pk.y);
+                pk = packD ? make_int2(0, 0) : make_int2(v, pk.y);
             }
             packU[rs + pos] = pk;
         }
@@ -540,15 +547,15 @@ __device__ __forceinline__ void strip_work(const uint64_t (&vk)[B], int32_t k0, 
     for (int b = 0; b < B; ++b) {
         const int32_t k = k0 + 64 * b + lane;
         pk[b] = k < d ? pair_desc(rs, d, k, qv[b], sorted, vcap, wu, gsum) : make_int2(0, 0);
-        slot[b] = pk[b].y < 0 ? claim_vmajor(cw, (int32_t)(uint32_t)vk[b], -pk[b].y) : 0;
+        slot[b] = pk[b].y < 0 && packD ? claim_vmajor(cw, (int32_t)(uint32_t)vk[b], -pk[b].y) : 0;
     }
 #pragma unroll
     for (int b = 0; b < B; ++b) {
         const int32_t k = k0 + 64 * b + lane;
         if (k < d) {
             if (pk[b].y < 0) {
-                packD[slot[b]] = make_int2(pk[b].x, -pk[b].y);
-                pk[b] = make_int2(0, 0);
+                if (packD) packD[slot[b]] = make_int2(pk[b].x, -pk[b].y);
+                pk[b] = packD ? make_int2(0, 0) : make_int2((int32_t)(uint32_t)vk[b], pk[b].y);
             }
             packU[rs + k] = pk[b];
             if (sorted) colO[rs + k] = (int32_t)(uint32_t)vk[b];
@@ -645,7 +652,8 @@ __device__ __forceinline__ void append_rows(uint64_t mask, int64_t x0, int lane,
 // and writes Wu (the length u-major pairs stream) of all of them, 0 for the
 // longer lists, which it appends to the lists of k_work_wide's classes
 // (wide[c * (n + 1)] holds the count of class c, its vertices follow).  Where
-// hubs are numbered (colH) it also writes the numbers of the other vertices'
+// hubs are numbered (colH) or v-major pairs are placed later (packD null) it
+// also writes the numbers and the empty descriptors of the other vertices'
 // lists (heavy, or of one entry), which nothing sorts.
 __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __restrict__ rowQ,
                                                      int32_t* __restrict__ colO, uint16_t* __restrict__ colH,
@@ -663,14 +671,18 @@ __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __res
         const int4 q = x < n ? rowQ[x] : make_int4(0, 0, 0, 0);
         const int32_t d = q.y;
         if (x < n && !(d >= 2 && d <= 128)) Wu[x] = 0;
-        if (colH) {
-            if (d == ~1) colH[q.x] = (uint16_t)rowQ[colO[q.x]].w;
+        if (colH || !packD) {
+            auto other = [&](int32_t e) {  // entry e of such a list
+                if (colH) colH[e] = (uint16_t)rowQ[colO[e]].w;
+                if (!packD) packU[e] = make_int2(0, 0);
+            };
+            if (d == ~1) other(q.x);
             uint64_t rest = ballot64(d < ~1);
             while (rest) {
                 const int l = __builtin_ctzll(rest);
                 rest &= rest - 1;
                 const int32_t rs = __builtin_amdgcn_readlane(q.x, l), len = ~__builtin_amdgcn_readlane(q.y, l);
-                for (int32_t k = lane; k < len; k += 64) colH[rs + k] = (uint16_t)rowQ[colO[rs + k]].w;
+                for (int32_t k = lane; k < len; k += 64) other(rs + k);
             }
         }
         work_groups<4>(ballot64(d >= 2 && d <= 4), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
@@ -708,6 +720,96 @@ __global__ void __launch_bounds__(256) k_work_wide(const int32_t* __restrict__ L
         work_wide_lists<R>(1ull, q, x, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
     }
     if (!Gx) add_gather(gsum, acc);
+}
+
+// ---- v-major descriptors by partition ---------------------------------------
+// A claim per pair is a returning atomic on one of n addresses, and those run
+// at about 16 G/s whatever the kernel around them does.  Instead the anchor
+// work leaves the v-major pairs in packU; one pass puts them, as 8-byte
+// records, into parts of 2^vbits vertices (a part's place is its vertices'
+// descriptor slots, in a buffer of the same layout), and one block per part
+// then claims the slots in LDS.  R-MAT s22: the anchor work, 4.1 ms with
+// claims, takes 1.4, and the two passes 1.0 (p = 0.5: 1.8, 0.6 and 0.5).
+constexpr int kVParts = 512, kVBits = 13, kVTile = 8192, kVThreads = 512, kVLine = 32;
+constexpr int32_t kVCap = 1024;  // largest vmajor_cap: a streamed part is shorter than it
+static_assert(kVParts == 1 << 9 && kVCap == 1 << 10, "part, length and vertex fill the 32 bits of a record");
+
+// record: (start of the streamed part, part << 23 | length << 13 | vertex in the part)
+__global__ void __launch_bounds__(kVThreads) k_vmajor_part(const int32_t* __restrict__ mp_dev,
+                                                            const int2* __restrict__ packU, int vbits, int64_t n,
+                                                            const int32_t* __restrict__ rpD,
+                                                            int32_t* __restrict__ taken, int2* __restrict__ rec) {
+    constexpr int ITEMS = kVTile / kVThreads;
+    __shared__ __attribute__((aligned(16))) int2 stage[kVTile];
+    __shared__ int32_t cnt[kVParts], loc[kVParts], base[kVParts], tmp[kVThreads / 64 + 1];
+    const int t = threadIdx.x;
+    const int64_t mp = mp_dev[0];
+    for (int64_t e0 = (int64_t)blockIdx.x * kVTile; e0 < mp; e0 += (int64_t)gridDim.x * kVTile) {
+        cnt[t] = 0;  // kVParts == kVThreads
+        int2 r[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const int64_t e = e0 + k * kVThreads + t;
+            r[k] = e < mp ? packU[e] : make_int2(0, 0);
+        }
+        __syncthreads();
+        int32_t rk[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            rk[k] = -1;
+            if (r[k].y < 0) {
+                const uint32_t v = (uint32_t)r[k].x, p = v >> vbits;
+                rk[k] = atomicAdd(&cnt[p], 1);
+                r[k] = make_int2((int32_t)(e0 + k * kVThreads + t + 1),
+                                 (int32_t)(p << 23 | (uint32_t)-r[k].y << kVBits | (v & ((1u << vbits) - 1))));
+            }
+        }
+        __syncthreads();
+        const int32_t c = cnt[t];
+        int32_t total;
+        loc[t] = block_exclusive_sum<kVThreads>(c, tmp, &total);
+        if (c) base[t] = rpD[min((int64_t)t << vbits, n)] + atomicAdd(&taken[t * kVLine], c);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k)
+            if (rk[k] >= 0) stage[loc[(uint32_t)r[k].y >> 23] + rk[k]] = r[k];
+        __syncthreads();
+        for (int32_t j = t; j < total; j += kVThreads) {
+            const int2 x = stage[j];
+            const uint32_t p = (uint32_t)x.y >> 23;
+            rec[base[p] + (j - loc[p])] = x;
+        }
+        __syncthreads();
+    }
+}
+
+// cw and packD of one part's vertices from its records.
+__global__ void __launch_bounds__(1024) k_vmajor_place(int64_t n, int vbits, const int32_t* __restrict__ rpD,
+                                                        const int32_t* __restrict__ taken,
+                                                        const int2* __restrict__ rec, int2* __restrict__ packD,
+                                                        unsigned long long* __restrict__ cw) {
+    __shared__ unsigned long long c[1 << kVBits];
+    const int64_t v0 = (int64_t)blockIdx.x << vbits;
+    const int32_t nv = (int32_t)min((int64_t)1 << vbits, n - v0);
+    for (int32_t i = threadIdx.x; i < nv; i += 1024) c[i] = (unsigned long long)(uint32_t)rpD[v0 + i] << 32;
+    __syncthreads();
+    const int2* R = rec + rpD[v0];
+    const int32_t cnt = taken[blockIdx.x * kVLine];
+    constexpr int U = 4;
+    for (int32_t i0 = threadIdx.x; i0 < cnt; i0 += 1024 * U) {
+        int2 r[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) r[k] = i0 + 1024 * k < cnt ? R[i0 + 1024 * k] : make_int2(0, 0);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (i0 + 1024 * k >= cnt) break;
+            const uint32_t len = ((uint32_t)r[k].y >> kVBits) & (kVCap - 1);
+            const unsigned long long old = atomicAdd(&c[r[k].y & ((1 << kVBits) - 1)], (1ull << 32) | len);
+            packD[old >> 32] = make_int2(r[k].x, (int32_t)len);
+        }
+    }
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < nv; i += 1024) cw[v0 + i] = c[i];
 }
 
 __device__ __forceinline__ int32_t items_of(int64_t w, int32_t len) {
@@ -1224,7 +1326,7 @@ __device__ __forceinline__ void load_lists(const int2* __restrict__ L, int32_t c
         const int j = t * R + k;  // consecutive entries per thread
         const int2 e = j < cnt ? L[j] : make_int2(0, 0);
         st[k] = e.x;
-        ln[k] = e.y;
+        ln[k] = max(e.y, 0);  // negative: closed from the other side
     }
 }
 
@@ -2120,6 +2222,7 @@ static LightPlan light_plan(int64_t m, int32_t maxd, const CountConfig& cfg) {
 }
 
 static bool hub_lists_fit(int64_t n, int64_t m, const CountConfig& cfg);
+static bool vmajor_parts_fit(int64_t n, int64_t m, int32_t maxd, const CountConfig& cfg);
 
 // Keys per rank tile for h heavy vertices: the largest of 1024, 512 and 256
 // that still gives every CU a tile (longer chunks take fewer rank atomics,
@@ -2282,24 +2385,31 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     DevBuf<int32_t> upre(NW + 1, s);
     DevBuf<uint8_t> cls(n, s);
     // Block anchors that are hubs are closed through bitmaps of hub numbers
-    // (all vertices of a small graph are hubs, by their own ids).  Numbering
-    // the hubs of a larger one takes 0.05 ms on R-MAT s22; where the counted
-    // graph has fewer than kBitDegree edges a vertex, block anchors are too few
-    // to pay for it (p = 0.1: none; p = 0.5: 1.14 -> 0.72 ms).
+    // (all vertices of a small graph are hubs, by their own ids, which also
+    // saves the launches for the other block anchors).  Numbering the hubs of a
+    // larger one and naming the entries cost 2 to 5% of a count; where the
+    // counted graph has fewer than kBitDegree edges a vertex, block anchors are
+    // too few to pay for it.  A count of R-MAT s22 without and with hubs: p = 1
+    // 10.4 and 7.9 ms, p = 0.5 4.7 and 4.2, p = 0.25 2.37 and 2.38, p = 0.1 1.36
+    // and 1.41; of s20: p = 1 2.26 and 1.84, p = 0.5 1.23 and 1.22, p = 0.25
+    // 0.81 and 0.82.
     const LightPlan plan = light_plan(g->m, g->max_deg, cfg);
     const double kept = sampled ? (double)thr / 9007199254740992.0 : 1.0;
     const bool bits = !un && plan.dcap_lds && hub_lists_fit(n, g->m, cfg) &&
                       (n <= kHubs || kept * (double)g->m >= kBitDegree * (double)n);
     const bool numbered = bits && n > kHubs;
+    // v-major pairs placed by partition: see k_vmajor_part
+    const bool defer = !un && kept * (double)g->m >= kDeferPairs && vmajor_parts_fit(n, g->m, g->max_deg, cfg);
     DevBuf<uint16_t> num(numbered ? n : 0, s);
     if (numbered) {
         DevBuf<int32_t> hist(257, s);
         fill_i32(hist.get(), 0, 257, s);
-        const int64_t chunk = hub_chunk(n);
-        TC_LAUNCH("deg_class", k_deg_class_hist, dim3(ceil_div(n, chunk)), dim3(256), 0, s, n, chunk, degp, cls.get(),
-                  hist.get());
-        TC_LAUNCH("hub_ids", k_hub_ids, dim3(ceil_div(n, chunk)), dim3(256), 0, s, n, chunk, (const uint8_t*)cls.get(),
-                  (const int32_t*)hist.get(), hist.get() + 256, num.get());
+        // a block anchor's degree is above small_dmax, and its keys' as well
+        const uint32_t cmin = deg_class(cfg.small_dmax + 1);
+        TC_LAUNCH("deg_class", k_deg_class_hist, dim3(std::min(grid_for(n, 256), 512u)), dim3(256), 0, s, n, cmin, degp,
+                  cls.get(), hist.get());
+        TC_LAUNCH("hub_ids", k_hub_ids, dim3(ceil_div(n, kHubChunk)), dim3(256), 0, s, n, cmin,
+                  (const uint8_t*)cls.get(), (const int32_t*)hist.get(), hist.get() + 256, num.get());
     } else {
         degree_classes(n, degp, cls.get(), s);
     }
@@ -2346,8 +2456,9 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
         DevBuf<int64_t> Gx(un ? n : 0, s);  // per-list gather statistic (unions)
         int64_t* gxp = un ? Gx.get() : nullptr;
         DevBuf<int2> packD(vcap > 0 ? g->m : 1, s);  // v-major descriptors, rpD[v].. for vertex v
+        int2* claims = defer ? nullptr : packD.get();  // where the anchor work places v-major pairs itself
         TC_LAUNCH("work", k_work_lanes, dim3(grid_for(n, 256)), dim3(256), 0, s, n, (const int4*)rowQ.get(),
-                  colO.get(), colh, vcap, packU.get(), packD.get(), cwp, Wu.get(), gxp, wide.get(), acc);
+                  colO.get(), colh, vcap, packU.get(), claims, cwp, Wu.get(), gxp, wide.get(), acc);
         // longer lists by register class, persistent grids of one round of
         // resident blocks; max_deg bounds every d+
         auto launch_wide = [&](auto kernel, int c, int32_t lo, const char* name, std::atomic<int>& resident) {
@@ -2360,12 +2471,26 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
             }
             TC_LAUNCH(name, kernel, dim3((unsigned)(num_cus() * r)), dim3(256), 0, s,
                       (const int32_t*)wide.get() + c * (n + 1) + 1, (const int4*)rowQ.get(), colO.get(), colh, vcap,
-                      packU.get(), packD.get(), cwp, Wu.get(), gxp, acc);
+                      packU.get(), claims, cwp, Wu.get(), gxp, acc);
         };
         static std::atomic<int> res_w[3];
         launch_wide(k_work_wide<4>, 0, 128, "work_w4", res_w[0]);
         launch_wide(k_work_wide<8>, 1, 256, "work_w8", res_w[1]);
         launch_wide(k_work_wide<16>, 2, 512, "work_w16", res_w[2]);
+        if (defer) {
+            int vbits = 0;
+            while ((n - 1) >> vbits >= kVParts) ++vbits;
+            DevBuf<int2> rec(g->m, s);
+            DevBuf<int32_t> taken(kVParts * kVLine, s);
+            fill_i32(taken.get(), 0, kVParts * kVLine, s);
+            TC_LAUNCH("vmajor_part", k_vmajor_part,
+                      dim3((unsigned)std::min<int64_t>(ceil_div(g->m, kVTile), (int64_t)num_cus() * 64)),
+                      dim3(kVThreads), 0, s, mp_dev, (const int2*)packU.get(), vbits, n, (const int32_t*)rpD.get(),
+                      taken.get(), rec.get());
+            TC_LAUNCH("vmajor_place", k_vmajor_place, dim3((unsigned)(((n - 1) >> vbits) + 1)), dim3(1024), 0, s, n,
+                      vbits, (const int32_t*)rpD.get(), (const int32_t*)taken.get(), (const int2*)rec.get(),
+                      packD.get(), cwp);
+        }
         // item counts of the bins, then their prefixes in place
         DevBuf<int32_t> tbase(n + 1, s), sbase(n + 1, s), lbase(n + 1, s), hbase(n + 1, s), bbase(bits ? n + 1 : 0, s);
         const ItemBins bin{tbase.get(), sbase.get(), bits ? bbase.get() : nullptr, lbase.get(), hbase.get()};
@@ -2564,7 +2689,32 @@ static bool hub_lists_fit(int64_t n, int64_t m, const CountConfig& cfg) {
     return region_bytes(2 * (m + kHubTail)) <= heavy_phase_bytes(n, m, cfg);
 }
 
-static CountBytes count_parts(int64_t n, int64_t m, int32_t maxd, int sampled, bool hubs, const CountConfig& cfg) {
+// Item counts and their prefixes, classification partials and item lists,
+// which take the place of the v-major partition's records.
+static int64_t item_bytes(int64_t n, int64_t m, int32_t maxd, bool hubs, const CountConfig& cfg) {
+    auto rb = region_bytes;
+    int64_t b = (hubs ? 5 : 4) * rb(4 * (n + 1)) + rb(4) + scan_each_scratch_bytes(6, n);
+    b += rb(8 * 9 * (int64_t)std::min<int64_t>((n + 255) / 256, kClassifyBlocks));
+    const int64_t items_max = 2 * n + 2 * m / kJL + 2;
+    b += 2 * rb(8 * items_max);
+    const LightPlan plan = light_plan(m, maxd, cfg);
+    b += plan.dcap_lds ? rb(8 * items_max) : rb(8);
+    if (!plan.dcap_global) return b + rb(8);
+    return b + rb(8 * items_max) + rb(4 * (int64_t)num_cus() * large_block_words(plan.dcap_global));
+}
+
+static int64_t vmajor_part_bytes(int64_t m) { return region_bytes(8 * m) + region_bytes(4 * kVParts * kVLine); }
+
+// Whether the v-major pairs can be placed by partition: the records hold what
+// they must, and what they take beyond the item lists' place fits the memory
+// that the heavy phase takes anyhow, next to the hub numbers.
+static bool vmajor_parts_fit(int64_t n, int64_t m, int32_t maxd, const CountConfig& cfg) {
+    if (cfg.vmajor_cap < 1 || cfg.vmajor_cap > kVCap || n > ((int64_t)kVParts << kVBits)) return false;
+    const int64_t over = std::max<int64_t>(0, vmajor_part_bytes(m) - item_bytes(n, m, maxd, false, cfg));
+    return region_bytes(2 * (m + kHubTail)) + over <= heavy_phase_bytes(n, m, cfg);
+}
+
+static CountBytes count_parts(int64_t n, int64_t m, int32_t maxd, int sampled, bool alone, const CountConfig& cfg) {
     auto rb = region_bytes;
     CountBytes c;
     const int64_t E2 = 2 * m;
@@ -2578,16 +2728,11 @@ static CountBytes count_parts(int64_t n, int64_t m, int32_t maxd, int sampled, b
     b += 2 * rb(4 * (n + 1)) + rb(4 * (m + 1));                    // rpO, heavy prefix, up lists and their sentinel
     c.both = b;
     b = rb(4 * (n + 1)) + rb(16 * n) + 2 * rb(8 * n) + rb(12 * (n + 1));  // rpD, rowQ, Wu, cw, wide-list vertices
-    b += hubs && hub_lists_fit(n, m, cfg) ? rb(2 * (m + kHubTail)) : rb(2);
+    b += alone && hub_lists_fit(n, m, cfg) ? rb(2 * (m + kHubTail)) : rb(2);
     b += rb(8 * m) + rb(8 * (cfg.vmajor_cap > 0 ? m : 1));         // packed descriptors
-    b += (hubs ? 5 : 4) * rb(4 * (n + 1)) + rb(4) + scan_each_scratch_bytes(6, n);  // item counts and their prefixes
-    b += rb(8 * 9 * (int64_t)std::min<int64_t>((n + 255) / 256, kClassifyBlocks));  // classification partials
-    const int64_t items_max = 2 * n + E2 / kJL + 2;
-    b += 2 * rb(8 * items_max);
-    const LightPlan plan = light_plan(m, maxd, cfg);
-    b += plan.dcap_lds ? rb(8 * items_max) : rb(8);
-    b += plan.dcap_global ? rb(8 * items_max) + rb(4 * (int64_t)num_cus() * large_block_words(plan.dcap_global)) : rb(8);
-    c.light = b;
+    const int64_t items = item_bytes(n, m, maxd, alone, cfg);
+    const bool parts = alone && vmajor_parts_fit(n, m, maxd, cfg);
+    c.light = b + (parts ? std::max(items, vmajor_part_bytes(m)) : items);
     c.heavy = heavy_phase_bytes(n, m, cfg);
     return c;
 }

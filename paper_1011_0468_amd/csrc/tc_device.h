@@ -108,7 +108,7 @@ __device__ __forceinline__ bool rank_below(int32_t du, int32_t u, int32_t dv, in
 // per octave (exponent and the three bits after the leading one), so
 // class(d) < class(d') implies d < d', and equal classes below 16 mean equal
 // degrees.  At most 16 + 8 * 26 + 7 = 231.
-__device__ __forceinline__ uint32_t deg_class(int32_t d) {
+__host__ __device__ __forceinline__ uint32_t deg_class(int32_t d) {
     if (d < 16) return d > 0 ? (uint32_t)d : 0u;
     const int e = 31 - __builtin_clz((uint32_t)d);  // >= 4
     return 16u + 8u * (uint32_t)(e - 4) + (((uint32_t)d >> (e - 3)) & 7u);

@@ -59,13 +59,22 @@ def test_list_lengths(gpu, core):
 def test_more_anchors_than_hubs(gpu):
     """Every vertex has a long list: most block anchors lie past the hub limit and keep the hash tables."""
     rng = np.random.RandomState(1)
-    n = 100000
-    near = (np.arange(n)[:, None] + rng.randint(1, 400, size=(n, 300))) % n
-    _check(gpu, (n, np.repeat(np.arange(n), 300).astype(np.int32), near.reshape(-1).astype(np.int32)),
+    n, k = 70000, 170
+    near = (np.arange(n)[:, None] + rng.randint(1, 400, size=(n, k))) % n
+    _check(gpu, (n, np.repeat(np.arange(n), k).astype(np.int32), near.reshape(-1).astype(np.int32)),
            splits=((1000, 1),))
 
 
 @pytest.mark.parametrize("split", [(1, 1), (1000, 1)])
 def test_unsorted_lists(gpu, split):
     """Out-lists above 1024 entries, which stay in id order and stream whole."""
-    _check(gpu, _dense_core(90000, 3000, 4000000, 3), splits=(split,))
+    _check(gpu, _dense_core(90000, 2100, 2200000, 3), splits=(split,))
+
+
+@pytest.mark.parametrize("n", [(1 << 13) * 3 + 5, 1 << 16, 300001])
+@pytest.mark.parametrize("p", [None, 0.9])
+def test_placed_by_partition(gpu, n, p):
+    """Enough edges for v-major pairs to be placed by partition: parts of several widths, hubs with many pairs."""
+    rng = np.random.RandomState(n)
+    e = (n * rng.rand(2, 2000000) ** 3).astype(np.int32)
+    _check(gpu, (n, e[0], e[1]), splits=((1, 1), (1000, 1)), p=p)
