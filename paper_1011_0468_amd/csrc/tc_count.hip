@@ -67,6 +67,11 @@ constexpr int kHubs = 65535;
 constexpr int32_t kNoHub = 65535;
 constexpr int64_t kHubChunk = 4096;  // vertices per block of the pass that numbers them
 constexpr int kHubTail = 8;
+// Edges up to which a count is mostly the latency of its launches.
+constexpr int64_t kSmallEdges = 1 << 19;
+// Heavy vertices (bound) and vertices up to which one block counts the heavy
+// triangles: 50 KB of LDS for their adjacency bits.
+constexpr int64_t kHeavySmall = 640, kHeavySmallN = 1 << 16;
 // Edges per vertex of the counted graph from which hubs are numbered.
 constexpr double kBitDegree = 6.0;
 // Edges of the counted graph from which v-major pairs are placed by partition
@@ -79,7 +84,11 @@ constexpr double kDeferPairs = 3 << 18;
 // orientation
 // ---------------------------------------------------------------------------
 
-__global__ void k_deg_class(int64_t n, const int32_t* __restrict__ degp, uint8_t* __restrict__ cls) {
+// cls[x] = degree class of vertex x; also clears the nacc result slots acc
+__global__ void k_deg_class(int64_t n, const int32_t* __restrict__ degp, uint8_t* __restrict__ cls,
+                            int64_t* __restrict__ acc, int32_t nacc) {
+    if (blockIdx.x == 0)
+        for (int32_t i = threadIdx.x; i < nacc; i += blockDim.x) acc[i] = 0;
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
         cls[x] = (uint8_t)deg_class(degp[x]);
 }
@@ -87,9 +96,12 @@ __global__ void k_deg_class(int64_t n, const int32_t* __restrict__ degp, uint8_t
 // k_deg_class, and the number of vertices of every class from cmin up added
 // into hist[256].
 __global__ void __launch_bounds__(256) k_deg_class_hist(int64_t n, uint32_t cmin, const int32_t* __restrict__ degp,
-                                                         uint8_t* __restrict__ cls, int32_t* __restrict__ hist) {
+                                                         uint8_t* __restrict__ cls, int32_t* __restrict__ hist,
+                                                         int64_t* __restrict__ acc, int32_t nacc) {
     __shared__ int32_t cnt[256];
     cnt[threadIdx.x] = 0;
+    if (blockIdx.x == 0)
+        for (int32_t i = threadIdx.x; i < nacc; i += 256) acc[i] = 0;
     __syncthreads();
     for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < n; x += (int64_t)gridDim.x * 256) {
         const uint32_t c = deg_class(degp[x]);
@@ -651,7 +663,11 @@ __device__ __forceinline__ void append_rows(uint64_t mask, int64_t x0, int lane,
 // groups of 4 to 64 and those of 65 to 128 entries in two registers per lane,
 // and writes Wu (the length u-major pairs stream) of all of them, 0 for the
 // longer lists, which it appends to the lists of k_work_wide's classes
-// (wide[c * (n + 1)] holds the count of class c, its vertices follow).  Where
+// (wide[c * (n + 1)] holds the count of class c, its vertices follow; one_class:
+// all to the last, which a small graph's one launch takes).  With `split` a
+// window's list classes are dealt to the four waves of a block: a small graph
+// has fewer windows than the chip has waves, and one wave's chain through all
+// classes took 23 us of a count of 16384 vertices.  Where
 // hubs are numbered (colH) or v-major pairs are placed later (packD null) it
 // also writes the numbers and the empty descriptors of the other vertices'
 // lists (heavy, or of one entry), which nothing sorts.
@@ -661,17 +677,20 @@ __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __res
                                                      int2* __restrict__ packD,
                                                      unsigned long long* __restrict__ cw, int64_t* __restrict__ Wu,
                                                      int64_t* __restrict__ Gx, int32_t* __restrict__ wide,
-                                                     int64_t* __restrict__ acc) {
+                                                     bool one_class, bool split, int64_t* __restrict__ acc) {
     const int lane = __lane_id();
-    const int64_t gw = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * 4;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t gw = split ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wv;
+    const int64_t nw = split ? (int64_t)gridDim.x : (int64_t)gridDim.x * 4;
+    // the list classes of this wave: bits 0 .. 5, and 6 for the vertices without a list to sort
+    const uint32_t mine = split ? (wv == 0 ? 0x43u : wv == 1 ? 0x0Cu : wv == 2 ? 0x10u : 0x20u) : 0x7Fu;
     int64_t gsum = 0;
     for (int64_t x0 = gw * 64; x0 < n; x0 += nw * 64) {
         const int64_t x = x0 + lane;
         const int4 q = x < n ? rowQ[x] : make_int4(0, 0, 0, 0);
         const int32_t d = q.y;
-        if (x < n && !(d >= 2 && d <= 128)) Wu[x] = 0;
-        if (colH || !packD) {
+        if ((mine & 0x40u) && x < n && !(d >= 2 && d <= 128)) Wu[x] = 0;
+        if ((mine & 0x40u) && (colH || !packD)) {
             auto other = [&](int32_t e) {  // entry e of such a list
                 if (colH) colH[e] = (uint16_t)rowQ[colO[e]].w;
                 if (!packD) packU[e] = make_int2(0, 0);
@@ -685,15 +704,19 @@ __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __res
                 for (int32_t k = lane; k < len; k += 64) other(rs + k);
             }
         }
-        work_groups<4>(ballot64(d >= 2 && d <= 4), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_groups<8>(ballot64(d > 4 && d <= 8), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_groups<16>(ballot64(d > 8 && d <= 16), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_groups<32>(ballot64(d > 16 && d <= 32), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_groups<64>(ballot64(d > 32 && d <= 64), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
-        work_wide_lists<2>(ballot64(d > 64 && d <= 128), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
-        append_rows(ballot64(d > 128 && d <= 256), x0, lane, wide + 1);
-        append_rows(ballot64(d > 256 && d <= 512), x0, lane, wide + (n + 1) + 1);
-        append_rows(ballot64(d > 512), x0, lane, wide + 2 * (n + 1) + 1);
+        const auto lists = [&](int bit, int32_t lo, int32_t hi) {
+            return ballot64((mine >> bit & 1u) && d > lo && d <= hi);
+        };
+        work_groups<4>(lists(0, 1, 4), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_groups<8>(lists(1, 4, 8), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_groups<16>(lists(2, 8, 16), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_groups<32>(lists(3, 16, 32), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_groups<64>(lists(4, 32, 64), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        work_wide_lists<2>(lists(5, 64, 128), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
+        if (!(mine & 0x40u)) continue;
+        append_rows(ballot64(!one_class && d > 128 && d <= 256), x0, lane, wide + 1);
+        append_rows(ballot64(!one_class && d > 256 && d <= 512), x0, lane, wide + (n + 1) + 1);
+        append_rows(ballot64(d > (one_class ? 128 : 512)), x0, lane, wide + 2 * (n + 1) + 1);
     }
     if (!Gx) add_gather(gsum, acc);
 }
@@ -1009,9 +1032,10 @@ __global__ void k_heavy_list(int64_t n, const int32_t* __restrict__ hpos,
 // zero the first heavy_pad(h)^2 bytes of U and UT (h from device)
 
 // m', h and the classification statistics (sums of the per-block partials;
-// the last one is a maximum).  One block of 576 threads.
-__global__ void __launch_bounds__(576) k_finish(const int32_t* mp, const int32_t* hp,
-                                                const int64_t* __restrict__ part, int32_t nparts, int64_t* acc) {
+// the last one is a maximum), by the first 576 threads of a block of at least
+// as many.
+__device__ __forceinline__ void finish_stats(const int32_t* mp, const int32_t* hp, const int64_t* __restrict__ part,
+                                             int32_t nparts, int64_t* acc) {
     // thread t folds statistic q = t % 9 of the blocks t / 9, t / 9 + 64, ..
     // (neighbouring threads read neighbouring words); then 64 values per q
     __shared__ int64_t red[64][9];
@@ -1019,18 +1043,20 @@ __global__ void __launch_bounds__(576) k_finish(const int32_t* mp, const int32_t
     const int q = t % 9, c = t / 9;
     // 8 independent loads in flight per thread and round (0 is neutral for
     // both the sums and the maximum of non-negative degrees)
-    int64_t v = 0;
-    for (int32_t b0 = c; b0 < nparts; b0 += 64 * 8) {
-        int64_t x[8];
+    if (c < 64) {
+        int64_t v = 0;
+        for (int32_t b0 = c; b0 < nparts; b0 += 64 * 8) {
+            int64_t x[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int32_t b = b0 + 64 * k;
-            x[k] = b < nparts ? part[(int64_t)b * 9 + q] : 0;
+            for (int k = 0; k < 8; ++k) {
+                const int32_t b = b0 + 64 * k;
+                x[k] = b < nparts ? part[(int64_t)b * 9 + q] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v = q == 8 ? (x[k] > v ? x[k] : v) : v + x[k];
         }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v = q == 8 ? (x[k] > v ? x[k] : v) : v + x[k];
+        red[c][q] = v;
     }
-    red[c][q] = v;
     __syncthreads();
     if (t < 9) {
         const int slot[9] = {kLightSources, kLightOut, kWedges, kProbes, kBytesSmall, kBytesLarge, kItemsSmall,
@@ -1043,6 +1069,11 @@ __global__ void __launch_bounds__(576) k_finish(const int32_t* mp, const int32_t
         acc[kMp] = mp[0];
         acc[kH] = hp[0];
     }
+}
+
+__global__ void __launch_bounds__(576) k_finish(const int32_t* mp, const int32_t* hp,
+                                                const int64_t* __restrict__ part, int32_t nparts, int64_t* acc) {
+    finish_stats(mp, hp, part, nparts, acc);
 }
 
 // m' and h of every component of a union: mk[k], and the heavy flags' prefix
@@ -2069,6 +2100,66 @@ __global__ void __launch_bounds__(256) k_heavy_mfma(const uint8_t* __restrict__ 
     if (lane == 0 && total) atomicAdd((unsigned long long*)&acc[kTH], (unsigned long long)total);
 }
 
+// The heavy phase of a small graph, and the end of its count, in one block: the
+// adjacency bits of the heavy vertices (numbered by hpos, the prefix of their
+// flags) in LDS, then for every heavy pair u -> v the common bits of their
+// rows.  Seven launches for a few hundred vertices took 40 of the 210 us of a
+// count of 16384 vertices and 95000 edges; with this, the scans of one launch
+// and one class of long lists and the anchor work of a window
+// dealt to four waves, it takes 165.
+__global__ void __launch_bounds__(1024) k_heavy_small(int64_t n, const int32_t* __restrict__ hpos, int32_t hmax,
+                                                       const int32_t* __restrict__ rpO,
+                                                       const int32_t* __restrict__ colO, const int32_t* mp,
+                                                       const int64_t* __restrict__ part, int32_t nparts, int64_t* acc) {
+    extern __shared__ uint32_t small_bits[];  // hmax rows of W words, then hmax vertices
+    const int t = threadIdx.x, w = t >> 6, lane = __lane_id();
+    const int32_t h = heavy_count(hpos + n, hmax);
+    const int32_t W = (h + 31) / 32;
+    int32_t* list = reinterpret_cast<int32_t*>(small_bits + (size_t)hmax * ((hmax + 31) / 32));
+    if (t == 0 && hpos[n] > hmax) acc[kHeavyOverflow] = 1;
+    for (int32_t i = t; i < h * W; i += 1024) small_bits[i] = 0;
+    for (int64_t x0 = t; x0 < n; x0 += 8 * 1024) {
+        int32_t a[8], b[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t x = min(x0 + 1024 * k, n - 1);
+            a[k] = hpos[x];
+            b[k] = hpos[x + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (x0 + 1024 * k < n && b[k] > a[k] && a[k] < hmax) list[a[k]] = (int32_t)(x0 + 1024 * k);
+    }
+    __syncthreads();
+    for (int32_t i = w; i < h; i += 16) {
+        const int32_t x = list[i];
+        for (int32_t q = rpO[x] + lane; q < rpO[x + 1]; q += 64) {
+            const int32_t j = hpos[colO[q]];  // every vertex above a heavy one is heavy
+            if (j < h) atomicOr(&small_bits[i * W + (j >> 5)], 1u << (j & 31));
+        }
+    }
+    __syncthreads();
+    int64_t total = 0;
+    const int l = lane & 31;
+    for (int32_t i = w; i < h; i += 16) {
+        for (int32_t k = 0; k < W; ++k) {
+            uint32_t rest = small_bits[i * W + k];  // wave-uniform
+            while (rest) {  // two of u's out-neighbours at a time, one per half wave
+                const int j0 = __builtin_ctz(rest);
+                rest &= rest - 1;
+                const int j1 = rest ? __builtin_ctz(rest) : -1;
+                rest &= rest - 1;
+                const int j = lane < 32 ? j0 : j1;
+                for (int32_t b = l; j >= 0 && b < W; b += 32)
+                    total += __builtin_popcount(small_bits[i * W + b] & small_bits[(32 * k + j) * W + b]);
+            }
+        }
+    }
+    total = wave_sum(total);
+    if (lane == 0 && total) atomicAdd((unsigned long long*)&acc[kTH], (unsigned long long)total);
+    finish_stats(mp, hpos + n, part, nparts, acc);
+}
+
 // ---- heavy blocks of a union of components --------------------------------
 // Component c's heavy vertices hold ranks [hs[c], hs[c+1]) and get their own
 // strictly upper-triangular block U_c of pc[c] x pc[c] bytes (pc = the count
@@ -2181,8 +2272,8 @@ __global__ void __launch_bounds__(256) k_heavy_mfma_u(int32_t ntiles, const int4
 
 }  // namespace
 
-void degree_classes(int64_t n, const int32_t* deg, uint8_t* cls, hipStream_t s) {
-    TC_LAUNCH("deg_class", k_deg_class, dim3(grid_for(n, 256)), dim3(256), 0, s, n, deg, cls);
+void degree_classes(int64_t n, const int32_t* deg, uint8_t* cls, hipStream_t s, int64_t* acc, int32_t nacc) {
+    TC_LAUNCH("deg_class", k_deg_class, dim3(grid_for(n, 256)), dim3(256), 0, s, n, deg, cls, acc, nacc);
 }
 
 // Heavy-vertex bound: heavy vertices have deg > c m'^(1/2) with c = a/b and the
@@ -2326,8 +2417,8 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     if (cfg.small_dmax > 128 || cfg.small_dmax < 1) fail(TC_ERR_INVALID, "small_dmax must be in [1, 128]");
     const int32_t K = un ? un->K : 1;
     const int32_t* comp = un ? un->comp : nullptr;
-    fill_i64(acc, 0, (int64_t)K * kCountSlots, s);
     if (n == 0 || E2 == 0) {
+        fill_i64(acc, 0, (int64_t)K * kCountSlots, s);
         if (un && K > 0 && n > 0) {  // m' = 0 and h = 0 for every component
             DevBuf<int32_t> zero(n + 1, s);
             fill_i32(zero.get(), 0, n + 1, s);
@@ -2345,6 +2436,7 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     if (!un && hp_max * hp_max > ((int64_t)16 << 30))
         fail(TC_ERR_OVERFLOW, "heavy block bound exceeds 16 GiB: raise the heavy threshold");
     const int64_t items_max = 2 * n + E2 / kJL + 2;
+    const bool heavy_small = !un && hmax <= kHeavySmall && n <= kHeavySmallN;
 
     // 1. the counted graph: the input CSR, or its sample compacted into buffers
     //    sized for the full graph (section 3.1 coin), so that every later pass
@@ -2407,11 +2499,11 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
         // a block anchor's degree is above small_dmax, and its keys' as well
         const uint32_t cmin = deg_class(cfg.small_dmax + 1);
         TC_LAUNCH("deg_class", k_deg_class_hist, dim3(std::min(grid_for(n, 256), 512u)), dim3(256), 0, s, n, cmin, degp,
-                  cls.get(), hist.get());
+                  cls.get(), hist.get(), acc, K * kCountSlots);
         TC_LAUNCH("hub_ids", k_hub_ids, dim3(ceil_div(n, kHubChunk)), dim3(256), 0, s, n, cmin,
                   (const uint8_t*)cls.get(), (const int32_t*)hist.get(), hist.get() + 256, num.get());
     } else {
-        degree_classes(n, degp, cls.get(), s);
+        degree_classes(n, degp, cls.get(), s, acc, K * kCountSlots);
     }
     // the counted graph's own neighbour classes when it is the built graph
     const uint8_t* ncls = !sampled && !un ? g->ncls : nullptr;
@@ -2456,9 +2548,12 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
         DevBuf<int64_t> Gx(un ? n : 0, s);  // per-list gather statistic (unions)
         int64_t* gxp = un ? Gx.get() : nullptr;
         DevBuf<int2> packD(vcap > 0 ? g->m : 1, s);  // v-major descriptors, rpD[v].. for vertex v
+        const bool one_class = g->m <= kSmallEdges;  // few long lists: one launch for all of them
         int2* claims = defer ? nullptr : packD.get();  // where the anchor work places v-major pairs itself
-        TC_LAUNCH("work", k_work_lanes, dim3(grid_for(n, 256)), dim3(256), 0, s, n, (const int4*)rowQ.get(),
-                  colO.get(), colh, vcap, packU.get(), claims, cwp, Wu.get(), gxp, wide.get(), acc);
+        const bool split = n <= (int64_t)num_cus() * 64 * 4;  // windows in waves would leave SIMDs idle
+        TC_LAUNCH("work", k_work_lanes, dim3(grid_for(n, split ? 64 : 256)), dim3(256), 0, s, n,
+                  (const int4*)rowQ.get(),
+                  colO.get(), colh, vcap, packU.get(), claims, cwp, Wu.get(), gxp, wide.get(), one_class, split, acc);
         // longer lists by register class, persistent grids of one round of
         // resident blocks; max_deg bounds every d+
         auto launch_wide = [&](auto kernel, int c, int32_t lo, const char* name, std::atomic<int>& resident) {
@@ -2474,9 +2569,11 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
                       packU.get(), claims, cwp, Wu.get(), gxp, acc);
         };
         static std::atomic<int> res_w[3];
-        launch_wide(k_work_wide<4>, 0, 128, "work_w4", res_w[0]);
-        launch_wide(k_work_wide<8>, 1, 256, "work_w8", res_w[1]);
-        launch_wide(k_work_wide<16>, 2, 512, "work_w16", res_w[2]);
+        if (!one_class) {
+            launch_wide(k_work_wide<4>, 0, 128, "work_w4", res_w[0]);
+            launch_wide(k_work_wide<8>, 1, 256, "work_w8", res_w[1]);
+        }
+        launch_wide(k_work_wide<16>, 2, one_class ? 128 : 512, "work_w16", res_w[2]);
         if (defer) {
             int vbits = 0;
             while ((n - 1) >> vbits >= kVParts) ++vbits;
@@ -2589,8 +2686,13 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
         if (plan.dcap_global && !all_bits) launch_large(items_h, hbase, plan.dcap_global, true);
 
         {
-            PhaseScope ph_finish("finish");
-            if (!un)
+            PhaseScope ph_finish(heavy_small ? "heavy" : "finish");
+            if (heavy_small) {
+                const size_t lds = sizeof(uint32_t) * (size_t)(hmax * ((hmax + 31) / 32) + hmax);
+                TC_LAUNCH("heavy_small", k_heavy_small, dim3(1), dim3(1024), lds, s, n, (const int32_t*)hpos.get(),
+                          (int32_t)hmax, (const int32_t*)rpO.get(), (const int32_t*)colO.get(), mp_dev,
+                          (const int64_t*)cpart.get(), (int32_t)cgrid, acc);
+            } else if (!un)
                 TC_LAUNCH("finish", k_finish, dim3(1), dim3(576), 0, s, mp_dev, (const int32_t*)hpos.get() + n,
                           (const int64_t*)cpart.get(), (int32_t)cgrid, acc);
             else
@@ -2604,7 +2706,7 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     //    counts read back here)
     if (un) {
         count_union_heavy(g, *un, cfg, s, acc, hpos, degp, rpO, colO);
-    } else if (hmax >= 3) {
+    } else if (hmax >= 3 && !heavy_small) {
         PhaseScope ph("heavy");
         DevBuf<int32_t> hlist(hmax, s), hidx(n, s), horder(hmax, s);
         const int32_t* h_dev = hpos.get() + n;

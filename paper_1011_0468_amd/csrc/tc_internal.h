@@ -172,8 +172,10 @@ int build_csr(int64_t n, int64_t num_pairs, const int32_t* src_dev, const int32_
               hipStream_t s, tc_graph_s* g);
 // Sum of the sizes of every allocation build_csr makes (region_bytes each).
 int64_t build_csr_bytes(int64_t n, int64_t num_pairs);
-// cls[x] = degree class of vertex x (a byte that orders degrees, tc_device.h)
-void degree_classes(int64_t n, const int32_t* deg, uint8_t* cls, hipStream_t s);
+// cls[x] = degree class of vertex x (a byte that orders degrees, tc_device.h);
+// clears acc[nacc] as well
+void degree_classes(int64_t n, const int32_t* deg, uint8_t* cls, hipStream_t s, int64_t* acc = nullptr,
+                    int32_t nacc = 0);
 
 // ---------------------------------------------------------------------------
 // Sampling (tc_sample.hip)
