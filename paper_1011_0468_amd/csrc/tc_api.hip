@@ -516,13 +516,16 @@ static void count_batch(const tc_graph_s* g, int sampled, uint64_t thr, const ui
         DevBuf<uint64_t> sd(K, s);
         check_hip(hipMemcpyAsync(sd.get(), salts + i0, sizeof(uint64_t) * (size_t)K, hipMemcpyHostToDevice, s),
                   "salts");
-        DevBuf<int32_t> comp((size_t)K * (size_t)npad, s), off((size_t)K + 1, s);
+        DevBuf<int32_t> comp((size_t)K * (size_t)(npad + kUnionAlign), s), off((size_t)K + 1, s);
         DevBuf<int64_t> mk(K, s), accs((size_t)K * kCountSlots, s);
         tc_graph_s* gu = new tc_graph_s();
         std::vector<int64_t> h((size_t)K * kCountSlots);
         try {
-            sample_union_replicas(g, K, sd.get(), thr, s, gu, comp.get(), off.get(), mk.get());
+            // a vertex of degree 1 is in no wedge, and with c >= 1 it is never heavy
+            // (deg^2 = 1 <= c^2 m'), so the union can do without it
             CountUnion un;
+            un.m_all = sample_union_replicas(g, K, sd.get(), thr, cfg.heavy_num >= cfg.heavy_den ? 2 : 1, s, gu,
+                                             comp.get(), off.get(), mk.get());
             un.K = K;
             un.comp = comp.get();
             un.off = off.get();

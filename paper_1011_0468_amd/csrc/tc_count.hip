@@ -67,8 +67,9 @@ constexpr int kHubs = 65535;
 constexpr int32_t kNoHub = 65535;
 constexpr int64_t kHubChunk = 4096;  // vertices per block of the pass that numbers them
 constexpr int kHubTail = 8;
-// Edges up to which a count is mostly the latency of its launches.
-constexpr int64_t kSmallEdges = 1 << 19;
+// Edges up to which one launch takes all long lists: 95000 to 150000 edges 4 to 8
+// us faster than three launches, 210000 edges of R-MAT 30 us slower.
+constexpr int64_t kSmallEdges = 5 << 15;
 // Heavy vertices (bound) and vertices up to which one block counts the heavy
 // triangles: 50 KB of LDS for their adjacency bits.
 constexpr int64_t kHeavySmall = 640, kHeavySmallN = 1 << 16;
@@ -2104,9 +2105,9 @@ __global__ void __launch_bounds__(256) k_heavy_mfma(const uint8_t* __restrict__ 
 // adjacency bits of the heavy vertices (numbered by hpos, the prefix of their
 // flags) in LDS, then for every heavy pair u -> v the common bits of their
 // rows.  Seven launches for a few hundred vertices took 40 of the 210 us of a
-// count of 16384 vertices and 95000 edges; with this, the scans of one launch
-// and one class of long lists and the anchor work of a window
-// dealt to four waves, it takes 165.
+// count of 16384 vertices and 95000 edges; with this, the scans of one launch,
+// one class of long lists and the anchor work of a window dealt to four waves
+// it takes 165.
 __global__ void __launch_bounds__(1024) k_heavy_small(int64_t n, const int32_t* __restrict__ hpos, int32_t hmax,
                                                        const int32_t* __restrict__ rpO,
                                                        const int32_t* __restrict__ colO, const int32_t* mp,
@@ -2485,7 +2486,7 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     // 10.4 and 7.9 ms, p = 0.5 4.7 and 4.2, p = 0.25 2.37 and 2.38, p = 0.1 1.36
     // and 1.41; of s20: p = 1 2.26 and 1.84, p = 0.5 1.23 and 1.22, p = 0.25
     // 0.81 and 0.82.
-    const LightPlan plan = light_plan(g->m, g->max_deg, cfg);
+    const LightPlan plan = light_plan(un ? un->m_all : g->m, g->max_deg, cfg);
     const double kept = sampled ? (double)thr / 9007199254740992.0 : 1.0;
     const bool bits = !un && plan.dcap_lds && hub_lists_fit(n, g->m, cfg) &&
                       (n <= kHubs || kept * (double)g->m >= kBitDegree * (double)n);
@@ -2547,7 +2548,9 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
         PhaseScope ph_light("light");
         DevBuf<int64_t> Gx(un ? n : 0, s);  // per-list gather statistic (unions)
         int64_t* gxp = un ? Gx.get() : nullptr;
-        DevBuf<int2> packD(vcap > 0 ? g->m : 1, s);  // v-major descriptors, rpD[v].. for vertex v
+        // v-major descriptors, rpD[v].. for vertex v: a slot per edge at its upper end, also of the edges whose
+        // lower end a union leaves out
+        DevBuf<int2> packD(vcap > 0 ? (un ? un->m_all : g->m) : 1, s);
         const bool one_class = g->m <= kSmallEdges;  // few long lists: one launch for all of them
         int2* claims = defer ? nullptr : packD.get();  // where the anchor work places v-major pairs itself
         const bool split = n <= (int64_t)num_cus() * 64 * 4;  // windows in waves would leave SIMDs idle

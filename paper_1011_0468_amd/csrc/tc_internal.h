@@ -235,6 +235,7 @@ struct CountUnion {
     const int32_t* comp = nullptr;  // [n]
     const int32_t* off = nullptr;   // [K + 1]
     const int64_t* mk = nullptr;    // [K]
+    int64_t m_all = 0;              // edges of all components, those left out of the union graph included
 };
 
 // The exact count of every component of the (unsampled) union graph g with
@@ -251,12 +252,14 @@ int64_t count_union_bytes(int64_t n, int64_t m, int32_t maxd, int32_t K, int64_t
 
 // Union of K independent samples of g (keep probability thr, salts[k] device
 // array): component k is g sampled with salts[k], its vertex x is union vertex
-// k * n_pad + x (n_pad = n rounded up to kUnionAlign).  Builds the union's CSR
-// into *out (allocations through dev_alloc, released by graph_release) and
-// the comp / off / mk arrays (owned by the caller's buffers: comp[K * n_pad],
-// off[K + 1], mk[K]).  Synchronises s once (to size the sampled CSR).
-void sample_union_replicas(const tc_graph_s* g, int32_t K, const uint64_t* salts, uint64_t thr, hipStream_t s,
-                           tc_graph_s* out, int32_t* comp, int32_t* off, int64_t* mk);
+// k * n_pad + x (n_pad = n rounded up to kUnionAlign), of which only those of
+// degree >= min_deg (1 or 2) are kept, with their degrees in the sample.
+// Builds the union's CSR into *out (allocations through dev_alloc, released by
+// graph_release) and the comp / off / mk arrays (owned by the caller's buffers:
+// comp[K * (n_pad + kUnionAlign)], off[K + 1], mk[K]: edges of the whole
+// samples).  Returns their sum.  Synchronises s once (to size the sampled CSR).
+int64_t sample_union_replicas(const tc_graph_s* g, int32_t K, const uint64_t* salts, uint64_t thr, int min_deg,
+                              hipStream_t s, tc_graph_s* out, int32_t* comp, int32_t* off, int64_t* mk);
 // Union of the components of the graph gU (vertex ranges off[k]..off[k+1]
 // given in comp / off, device), component k sampled with (thrs[k], salts[k])
 // on its local ids x - off[k]; writes the sampled CSR to *out and mk.

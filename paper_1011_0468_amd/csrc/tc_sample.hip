@@ -249,15 +249,22 @@ __global__ void k_rows_rep(const int32_t* __restrict__ row_ptr, int64_t n, int64
     }
 }
 
-// The id of union vertex x after dropping the isolated ones:
-// nzt[x / 64].z + (the kept vertices below x in its 64-vertex word), from one
-// 16-byte gather (see k_nz_table).
-__device__ __forceinline__ int32_t nz_id(const int4* __restrict__ nzt, int64_t x) {
-    const int4 t = nzt[x >> 6];
-    const uint64_t b = ((uint64_t)(uint32_t)t.y << 32) | (uint32_t)t.x;
-    const int r = (int)(x & 63);
-    return t.z + __popcll(r == 0 ? 0ull : (b & (~0ull >> (64 - r))));
-}
+// A word of 64 union vertices' table entry (see k_nz_table): their bits, and
+// what the count of bits below the word starts from.
+struct NzWord {
+    uint64_t bits;
+    int32_t base;
+    __device__ __forceinline__ NzWord(const int4* __restrict__ table, int64_t x) {
+        const int4 t = table[x >> 6];
+        bits = ((uint64_t)(uint32_t)t.y << 32) | (uint32_t)t.x;
+        base = t.z;
+    }
+    __device__ __forceinline__ bool has(int64_t x) const { return (bits >> (x & 63)) & 1ull; }
+    __device__ __forceinline__ int32_t rank(int64_t x) const {
+        const int r = (int)(x & 63);
+        return base + __popcll(r == 0 ? 0ull : (bits & (~0ull >> (64 - r))));
+    }
+};
 
 // Orders one wave's LDS accesses (a wave's LDS operations complete in issue
 // order; only the compiler must not move accesses across).
@@ -271,7 +278,10 @@ __device__ __forceinline__ void wave_lds_order() {
 constexpr int kRepWords = 8;
 
 // Kept entries of the replicated space, written with the union's final ids
-// (nz_id of the padded layout's id).  One wave per range of kRepWords words
+// (nzt's rank of the padded layout's id).  The rows of dropped vertices of
+// degree 1 (one entry each, onet) are left out, and the entries that point to
+// one get the first unused id of their component (spare[k]), whose degree 0
+// ranks below every vertex, as theirs did below the row's.  One wave per range of kRepWords words
 // of g: the range's entries are read once and held in registers, and for
 // every copy the kept entries of the whole range, which are consecutive in
 // that copy's output, are packed in LDS, relabelled by full-width table
@@ -283,6 +293,7 @@ __global__ void __launch_bounds__(256) k_compact_rep(const int32_t* __restrict__
                                                       int64_t E2, int64_t NWp, int32_t K, int64_t npad,
                                                       const uint64_t* __restrict__ bits,
                                                       const int32_t* __restrict__ wpre, const int4* __restrict__ nzt,
+                                                      const int4* __restrict__ onet, const int32_t* __restrict__ spare,
                                                       int32_t* __restrict__ col_out, int32_t* __restrict__ src_out) {
     constexpr int RW = kRepWords, CPL = 64 / RW;  // words per range, copies per load
     __shared__ int32_t pack[4][2][RW * 64];
@@ -331,9 +342,17 @@ __global__ void __launch_bounds__(256) k_compact_rep(const int32_t* __restrict__
                 }
                 if (cnt == 0) continue;
                 wave_lds_order();
+                const int32_t none = onet ? spare[k] : 0;
                 for (int32_t q = lane; q < cnt; q += 64) {
-                    col_out[base + q] = nz_id(nzt, pc[q]);
-                    src_out[base + q] = nz_id(nzt, ps[q]);
+                    const int32_t v = pc[q], u = ps[q];
+                    const NzWord wu(nzt, u), wv2(nzt, v);
+                    int32_t at = base + q;
+                    if (onet) {
+                        if (!wu.has(u)) continue;  // the row of a vertex of degree 1
+                        at -= NzWord(onet, u).rank(u);
+                    }
+                    col_out[at] = wv2.has(v) ? wv2.rank(v) : none;
+                    src_out[at] = wu.rank(u);
                 }
                 wave_lds_order();  // read before the next copy packs
             }
@@ -367,92 +386,105 @@ __global__ void __launch_bounds__(256) k_keep_comp(const int32_t* __restrict__ s
     }
 }
 
-// ---- dropping the isolated vertices of a union of samples -----------------
+// ---- dropping vertices of a union of samples -------------------------------
 // A vertex without kept edges takes part in no triangle and in no statistic
-// of the count, and an order-preserving relabelling keeps the (deg, id)
-// order, so the union keeps only the vertices of degree > 0: component k's
-// nz[k] of them take new ids off'[k] .. off'[k] + nz[k] - 1 in their old
-// order, and off'[k + 1] = off'[k] + nz[k] rounded up to kUnionAlign.
+// of the count, and one with a single edge neither, as long as it is not heavy:
+// it is no source (d+ >= 2) and no source's out-neighbour (whose degrees are no
+// smaller), and every other vertex keeps its degree.  An order-preserving
+// relabelling keeps the (deg, id) order, so the union keeps only the vertices
+// of degree >= min_deg: component k's nz[k] of them take new ids off'[k] ..
+// off'[k] + nz[k] - 1 in their old order, and off'[k + 1] = off'[k] + nz[k] + 1
+// rounded up to kUnionAlign, so that every component has an unused id.  64
+// seeds of Chung-Lu 2^20 at p = 0.05: 9.5 -> 7.4 ms without the vertices of degree 1.
 
-// one bit per union vertex (degree > 0), per-word counts
-__global__ void __launch_bounds__(256) k_nz_bits(int64_t nU, const int32_t* __restrict__ deg, uint64_t* __restrict__ nzb,
-                                                  int32_t* __restrict__ nzc) {
+// one bit per union vertex (degree >= min_deg), one per dropped vertex of
+// degree 1, and the counts of both per word
+__global__ void __launch_bounds__(256) k_nz_bits(int64_t nU, int min_deg, const int32_t* __restrict__ deg,
+                                                  uint64_t* __restrict__ nzb, int32_t* __restrict__ nzc,
+                                                  uint64_t* __restrict__ oneb, int32_t* __restrict__ onec) {
     const int lane = __lane_id();
     const int64_t nw = (nU + 63) / 64;
     const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     for (int64_t w = wave; w < nw; w += nwaves) {
         const int64_t x = w * 64 + lane;
-        const uint64_t b = ballot64(x < nU && deg[x] > 0);
+        const int32_t d = x < nU ? deg[x] : 0;
+        const uint64_t b = ballot64(d >= min_deg), o = ballot64(d > 0 && d < min_deg);
         if (lane == 0) {
             nzb[w] = b;
             nzc[w] = __popcll(b);
+            oneb[w] = o;
+            onec[w] = __popcll(o);
         }
     }
 }
 
-// new component offsets (one thread; K is small): off2[k], off2[K] = new n
-__global__ void k_nz_offsets(int32_t K, int64_t npad, const int32_t* __restrict__ nzpre, int32_t* __restrict__ off2) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// new component offsets off2[k] (off2[K] = new n) and unused ids spare[k] (one
+// thread; K is small); mk[k] = edges of component k in the padded layout
+__global__ void k_nz_offsets(int32_t K, int64_t npad, const int32_t* __restrict__ nzpre, const int32_t* __restrict__ rp,
+                             int32_t* __restrict__ off2, int32_t* __restrict__ spare, int64_t* __restrict__ mk) {
+    if (blockIdx.x != 0) return;
+    for (int32_t k = threadIdx.x; k < K; k += blockDim.x)
+        mk[k] = ((int64_t)rp[(k + 1) * npad] - (int64_t)rp[k * npad]) / 2;
+    if (threadIdx.x != 0) return;
     int64_t o = 0;
     const int64_t wpc = npad / 64;  // words per component
     for (int32_t k = 0; k < K; ++k) {
         off2[k] = (int32_t)o;
         const int64_t nz = (int64_t)nzpre[(k + 1) * wpc] - (int64_t)nzpre[k * wpc];
-        o += (nz + kUnionAlign - 1) / kUnionAlign * kUnionAlign;
+        spare[k] = (int32_t)(o + nz);
+        o += (nz + kUnionAlign) / kUnionAlign * kUnionAlign;
     }
     off2[K] = (int32_t)o;
 }
 
-// new id of union vertex x (degree > 0)
-__device__ __forceinline__ int32_t nz_newid(int64_t x, int64_t npad, const uint64_t* __restrict__ nzb,
-                                            const int32_t* __restrict__ nzpre, const int32_t* __restrict__ off2) {
-    const int64_t k = x / npad;
-    const int64_t w = x >> 6;
-    const int r = (int)(x & 63);
-    const uint64_t below = r == 0 ? 0ull : (nzb[w] & (~0ull >> (64 - r)));
-    return off2[k] + (nzpre[w] - nzpre[k * (npad / 64)]) + __popcll(below);
+// For the relabelling and placing gathers: nzt[w] = (bits of the kept vertices
+// 64 w .. 64 w + 63, new id of the first kept one at or after 64 w), onet[w] =
+// (bits of the dropped ones of degree 1, their number before 64 w)
+__global__ void k_nz_table(int64_t NV, int64_t npad, const uint64_t* __restrict__ nzb,
+                           const int32_t* __restrict__ nzpre, const int32_t* __restrict__ off2,
+                           const uint64_t* __restrict__ oneb, const int32_t* __restrict__ onepre,
+                           int4* __restrict__ nzt, int4* __restrict__ onet) {
+    const int64_t wpc = npad / 64;
+    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < NV; w += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t k = w / wpc;
+        const uint64_t b = nzb[w], o = oneb[w];
+        nzt[w] = make_int4((int32_t)(uint32_t)b, (int32_t)(uint32_t)(b >> 32),
+                           (int32_t)(off2[k] + nzpre[w] - nzpre[k * wpc]), 0);
+        onet[w] = make_int4((int32_t)(uint32_t)o, (int32_t)(uint32_t)(o >> 32), onepre[w], 0);
+    }
 }
 
 // row offsets, degrees and components of the kept vertices at their new ids;
-// the padding slots after each component's vertices get its end offset
-__global__ void k_nz_place(int64_t nU, int64_t npad, int32_t K, const int32_t* __restrict__ rp,
-                           const int32_t* __restrict__ deg, const uint64_t* __restrict__ nzb,
-                           const int32_t* __restrict__ nzpre, const int32_t* __restrict__ off2,
-                           int32_t* __restrict__ rp2, int32_t* __restrict__ deg2, int32_t* __restrict__ comp2) {
+// the unused ids after each component's vertices get its end offset.  If the
+// entries are odd in number, the last id's pair with itself fills E2.
+__global__ void k_nz_place(int64_t nU, int64_t npad, int32_t K, int64_t entries, const int32_t* __restrict__ rp,
+                           const int32_t* __restrict__ deg, const int4* __restrict__ nzt,
+                           const int4* __restrict__ onet, const int32_t* __restrict__ onepre,
+                           const int32_t* __restrict__ spare, const int32_t* __restrict__ off2,
+                           int32_t* __restrict__ rp2, int32_t* __restrict__ deg2, int32_t* __restrict__ comp2,
+                           int32_t* __restrict__ col, int32_t* __restrict__ src) {
     const int64_t nU2 = off2[K];
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < nU; x += (int64_t)gridDim.x * blockDim.x) {
-        if (deg[x] > 0) {
-            const int32_t y = nz_newid(x, npad, nzb, nzpre, off2);
-            rp2[y] = rp[x];
+        const NzWord w(nzt, x);
+        if (w.has(x)) {
+            const int32_t y = w.rank(x);
+            rp2[y] = rp[x] - NzWord(onet, x).rank(x);
             deg2[y] = deg[x];
             comp2[y] = (int32_t)(x / npad);
         }
     }
-    // padding slots: from each component's last kept vertex to the next component
     for (int64_t k = blockIdx.x * blockDim.x + threadIdx.x; k < K; k += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t wpc = npad / 64;
-        const int64_t nz = (int64_t)nzpre[(k + 1) * wpc] - (int64_t)nzpre[k * wpc];
-        const int32_t end = rp[(k + 1) * npad];
-        for (int64_t y = off2[k] + nz; y < off2[k + 1]; ++y) {
+        const int32_t end = rp[(k + 1) * npad] - onepre[(k + 1) * (npad / 64)];
+        for (int64_t y = spare[k]; y < off2[k + 1]; ++y) {
             rp2[y] = end;
             deg2[y] = 0;
             comp2[y] = (int32_t)k;
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) rp2[nU2] = rp[nU];
-}
-
-// nzt[w] = (keep-vertex bits of union vertices 64 w .. 64 w + 63, new id of
-// the first kept vertex at or after 64 w), for the relabelling gathers
-__global__ void k_nz_table(int64_t NV, int64_t npad, const uint64_t* __restrict__ nzb,
-                           const int32_t* __restrict__ nzpre, const int32_t* __restrict__ off2, int4* __restrict__ nzt) {
-    const int64_t wpc = npad / 64;
-    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < NV; w += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t k = w / wpc;
-        const uint64_t b = nzb[w];
-        nzt[w] = make_int4((int32_t)(uint32_t)b, (int32_t)(uint32_t)(b >> 32),
-                           (int32_t)(off2[k] + nzpre[w] - nzpre[k * wpc]), 0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        rp2[nU2] = (int32_t)entries;
+        if (entries & 1) col[entries] = src[entries] = (int32_t)(nU2 - 1);
     }
 }
 
@@ -540,8 +572,8 @@ static int32_t read_total(const int32_t* p, hipStream_t s) {
     return t;
 }
 
-void sample_union_replicas(const tc_graph_s* g, int32_t K, const uint64_t* salts, uint64_t thr, hipStream_t s,
-                           tc_graph_s* out, int32_t* comp, int32_t* off, int64_t* mk) {
+int64_t sample_union_replicas(const tc_graph_s* g, int32_t K, const uint64_t* salts, uint64_t thr, int min_deg,
+                              hipStream_t s, tc_graph_s* out, int32_t* comp, int32_t* off, int64_t* mk) {
     const int64_t n = g->n, E2 = 2 * g->m;
     const int64_t npad = (n + kUnionAlign - 1) / kUnionAlign * kUnionAlign;
     const int64_t nU = (int64_t)K * npad;
@@ -564,7 +596,7 @@ void sample_union_replicas(const tc_graph_s* g, int32_t K, const uint64_t* salts
         out->src = (int32_t*)dev_alloc(sizeof(int32_t), s);
         TC_LAUNCH("comp_edges", k_comp_edges, dim3(ceil_div(K, 256)), dim3(256), 0, s, K, (const int32_t*)off,
                   (const int32_t*)out->row_ptr, mk);
-        return;
+        return 0;
     }
     // 1. keep bits of every copy, their scan, the union's rows in the padded layout
     DevBuf<uint64_t> bits(NW, s);
@@ -575,38 +607,43 @@ void sample_union_replicas(const tc_graph_s* g, int32_t K, const uint64_t* salts
     DevBuf<int32_t> rp(nU + 1, s), deg(nU, s);
     TC_LAUNCH("rows_rep", k_rows_rep, dim3(grid_for(nU + 1, 256)), dim3(256), 0, s, (const int32_t*)g->row_ptr, n, npad,
               E2, NWp, K, (const uint64_t*)bits.get(), (const int32_t*)wpre.get(), rp.get(), deg.get());
-    // 2. the vertices of degree > 0 and the components' new offsets
+    // 2. the vertices that are kept and the components' new offsets
     const int64_t NV = nU / 64;  // nU is a multiple of kUnionAlign
-    DevBuf<uint64_t> nzb(NV, s);
-    DevBuf<int32_t> nzpre(NV + 1, s);
-    TC_LAUNCH("nz_bits", k_nz_bits, dim3(grid_for(NV, 4)), dim3(256), 0, s, nU, (const int32_t*)deg.get(), nzb.get(),
-              nzpre.get());
-    scan_exclusive_i32(nzpre.get(), nzpre.get(), NV, s);
-    TC_LAUNCH("nz_offsets", k_nz_offsets, dim3(1), dim3(64), 0, s, K, npad, (const int32_t*)nzpre.get(), off);
-    int32_t sizes[2] = {0, 0};  // 2m' of the union, new vertex count
+    DevBuf<uint64_t> nzb(NV, s), oneb(NV, s);
+    DevBuf<int32_t> nzpre(NV + 1, s), onepre(NV + 1, s), spare(K, s);
+    TC_LAUNCH("nz_bits", k_nz_bits, dim3(grid_for(NV, 4)), dim3(256), 0, s, nU, min_deg, (const int32_t*)deg.get(),
+              nzb.get(), nzpre.get(), oneb.get(), onepre.get());
+    int32_t* const both[2] = {nzpre.get(), onepre.get()};
+    scan_exclusive_i32_each(both, 2, NV, s);
+    TC_LAUNCH("nz_offsets", k_nz_offsets, dim3(1), dim3(64), 0, s, K, npad, (const int32_t*)nzpre.get(),
+              (const int32_t*)rp.get(), off, spare.get(), mk);
+    int32_t sizes[3] = {0, 0, 0};  // 2m' of the samples, new vertex count, dropped vertices of degree 1
     check_hip(hipMemcpyAsync(&sizes[0], wpre.get() + NW, sizeof(int32_t), hipMemcpyDeviceToHost, s), "sample total");
     check_hip(hipMemcpyAsync(&sizes[1], off + K, sizeof(int32_t), hipMemcpyDeviceToHost, s), "union vertices");
+    check_hip(hipMemcpyAsync(&sizes[2], onepre.get() + NV, sizeof(int32_t), hipMemcpyDeviceToHost, s), "dropped");
     check_hip(hipStreamSynchronize(s), "sync");
-    const int64_t total = sizes[0], nU2 = sizes[1];
+    const int64_t entries = (int64_t)sizes[0] - sizes[2], nU2 = sizes[1];
     // 3. the compacted union: rows at the new ids, kept entries relabelled
     out->n = nU2;
-    out->m = total / 2;
+    out->m = (entries + 1) / 2;
+    const size_t cap = (size_t)(out->m > 0 ? 2 * out->m : 1);
     out->row_ptr = (int32_t*)dev_alloc(sizeof(int32_t) * (size_t)(nU2 + 1), s);
     out->deg = (int32_t*)dev_alloc(sizeof(int32_t) * (size_t)(nU2 > 0 ? nU2 : 1), s);
-    out->col = (int32_t*)dev_alloc(sizeof(int32_t) * (size_t)(total > 0 ? total : 1), s);
-    out->src = (int32_t*)dev_alloc(sizeof(int32_t) * (size_t)(total > 0 ? total : 1), s);
-    TC_LAUNCH("nz_place", k_nz_place, dim3(grid_for(nU, 256)), dim3(256), 0, s, nU, npad, K, (const int32_t*)rp.get(),
-              (const int32_t*)deg.get(), (const uint64_t*)nzb.get(), (const int32_t*)nzpre.get(), (const int32_t*)off,
-              out->row_ptr, out->deg, comp);
-    DevBuf<int4> nzt(NV, s);
+    out->col = (int32_t*)dev_alloc(sizeof(int32_t) * cap, s);
+    out->src = (int32_t*)dev_alloc(sizeof(int32_t) * cap, s);
+    DevBuf<int4> nzt(NV, s), onet(NV, s);
     TC_LAUNCH("nz_table", k_nz_table, dim3(grid_for(NV, 256)), dim3(256), 0, s, NV, npad, (const uint64_t*)nzb.get(),
-              (const int32_t*)nzpre.get(), (const int32_t*)off, nzt.get());
+              (const int32_t*)nzpre.get(), (const int32_t*)off, (const uint64_t*)oneb.get(),
+              (const int32_t*)onepre.get(), nzt.get(), onet.get());
+    TC_LAUNCH("nz_place", k_nz_place, dim3(grid_for(nU, 256)), dim3(256), 0, s, nU, npad, K, entries,
+              (const int32_t*)rp.get(), (const int32_t*)deg.get(), (const int4*)nzt.get(), (const int4*)onet.get(),
+              (const int32_t*)onepre.get(), (const int32_t*)spare.get(), (const int32_t*)off, out->row_ptr, out->deg,
+              comp, out->col, out->src);
     TC_LAUNCH("compact_rep", k_compact_rep, dim3(grid_for((NWp + kRepWords - 1) / kRepWords, 4)), dim3(256), 0, s,
-              (const int32_t*)g->col,
-              (const int32_t*)g->src, E2, NWp, K, npad, (const uint64_t*)bits.get(), (const int32_t*)wpre.get(),
-              (const int4*)nzt.get(), out->col, out->src);
-    TC_LAUNCH("comp_edges", k_comp_edges, dim3(ceil_div(K, 256)), dim3(256), 0, s, K, (const int32_t*)off,
-              (const int32_t*)out->row_ptr, mk);
+              (const int32_t*)g->col, (const int32_t*)g->src, E2, NWp, K, npad, (const uint64_t*)bits.get(),
+              (const int32_t*)wpre.get(), (const int4*)nzt.get(), min_deg > 1 ? (const int4*)onet.get() : nullptr,
+              (const int32_t*)spare.get(), out->col, out->src);
+    return sizes[0] / 2;
 }
 
 void comp_from_offsets(int64_t n, int32_t K, const int32_t* off, int32_t* comp, hipStream_t s) {

@@ -331,6 +331,7 @@ void tc_server_s::run_fused(int lane, const std::vector<tc::Job>& jobs, char* ba
                 un.comp = comp.get();
                 un.off = offd.get();
                 un.mk = mk.get();
+                un.m_all = gs->m;
                 count_union(gs, un, cfg, s, accs.get());
                 std::vector<int64_t> h((size_t)K * kCountSlots);
                 check_hip(hipMemcpyAsync(h.data(), accs.get(), sizeof(int64_t) * h.size(), hipMemcpyDeviceToHost, s),
