@@ -230,7 +230,7 @@ tc_status tc_triple_estimate(tc_graph g, double p, uint64_t sample_seed, int32_t
    num_samples = 0; every field is 0 except m, draws1 when n < 2 or m = 0.
    d > 0 and finite and num_samples >= 0, else TC_ERR_INVALID;
    TC_ERR_OVERFLOW if num_samples > 2^28 or s1 > 2^40.  The device memory it
-   takes (through the allocator) is at most 72 num_samples + 49 (n + 1) bytes
+   takes (through the allocator) is at most 4 num_samples + 49 (n + 1) bytes
    plus 17 KiB and the scans' scratch. */
 typedef struct {
     int64_t draws1;      /* s1, the edge draws of pass 1 */

@@ -1,7 +1,9 @@
-// Device search of a position in a non-decreasing prefix through a bucket
-// index, shared by the estimators that draw elements by position.
+// Shared by the estimators that draw elements by position: the search of a
+// position in a non-decreasing prefix through a bucket index, the partition of
+// the draws into the order of the elements, the lookup of an edge, the sums.
 #pragma once
 
+#include "tc_internal.h"
 #include "tc_device.h"
 
 namespace tc {
@@ -110,6 +112,157 @@ __global__ void __launch_bounds__(256) k_bucket_index(int64_t n, const T* __rest
             const int64_t lb0 = __shfl(b0, src, 64), lb1 = __shfl(b1, src, 64);
             for (int64_t b = lb0 + lane; b < lb1; b += 64) idx[b] = (int32_t)(u0 + src);
         }
+    }
+}
+
+// y in the sorted list col[lo .. end) of ids below n (scale = 1 / n).  Every
+// step of a binary search of a long list reads another cache line, so lists
+// past one line are entered where y would be if their ids were spread evenly
+// (as relabelled graphs' are: off by about the root of the length) and the
+// range is widened from there by doubling: 2^25 triples on R-MAT s22 took 6.6 ->
+// 5.5 ms, and it is at most twice the steps on any list.
+__device__ __forceinline__ bool in_list(const int32_t* __restrict__ col, int32_t lo, int32_t end, int32_t y,
+                                        float scale) {
+    int32_t hi = end;
+    if (end - lo > 32) {
+        int32_t g = lo + (int32_t)((float)(end - lo) * ((float)y * scale));
+        g = g < end - 1 ? g : end - 1;  // >= lo
+        int32_t step = 16;
+        if (col[g] < y) {
+            lo = g + 1;
+            while (hi - lo > step && col[lo + step] < y) {
+                lo += step + 1;
+                step *= 2;
+            }
+            hi = hi - lo > step ? lo + step : hi;
+        } else {
+            hi = g;
+            while (hi - lo > step && col[hi - 1 - step] >= y) {
+                hi -= step + 1;
+                step *= 2;
+            }
+            if (hi - lo > step) lo = hi - step;
+        }
+        // the first entry >= y lies in [lo, hi]
+    }
+    while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (col[mid] < y) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo < end && col[lo] == y;
+}
+
+__device__ __forceinline__ bool adjacent(const int32_t* __restrict__ rp, const int32_t* __restrict__ col, int32_t x,
+                                         int32_t y, float scale) {
+    const int32_t xs = rp[x], xe = rp[x + 1], ys = rp[y], ye = rp[y + 1];
+    return xe - xs <= ye - ys ? in_list(col, xs, xe, y, scale) : in_list(col, ys, ye, x, scale);
+}
+
+// the 64-bit hash of sample i: its element of U is the high half of h * |U|
+__device__ __forceinline__ uint64_t sample_hash(int64_t i, uint64_t salt) { return mix64(mix64((uint64_t)i) ^ salt); }
+
+// ---- partition of the samples ---------------------------------------------
+// Samples in hash order touch prefixes, lists and list prefixes all over the
+// graph (a new cache line per search step); after the partition a wave's
+// samples lie in one 256th of U.  Counts per part, their bases, then the
+// sample numbers (relative to i0) at their places, in any order inside a part.
+constexpr int kParts = 256, kPartTile = 8192;
+
+// Part of a sample: the top byte of its hash, hence of its position in U.
+struct HashParts {
+    __device__ __forceinline__ void load() {}
+    __device__ __forceinline__ int32_t operator()(uint64_t hash) const { return (int32_t)(hash >> 56); }
+};
+
+template <typename Part>
+__global__ void __launch_bounds__(256) k_part_count(int64_t i0, int64_t s, uint64_t salt, Part part_of,
+                                                     int32_t* __restrict__ cnt) {
+    __shared__ int32_t c[kParts];
+    part_of.load();
+    c[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < s; i += (int64_t)gridDim.x * 256)
+        atomicAdd(&c[part_of(sample_hash(i0 + i, salt))], 1);
+    __syncthreads();
+    if (c[threadIdx.x]) atomicAdd(&cnt[threadIdx.x], c[threadIdx.x]);
+}
+
+// at[p]: the start of part p, raised to its end
+template <typename Part>
+__global__ void __launch_bounds__(256) k_part_place(int64_t i0, int64_t s, uint64_t salt, Part part_of,
+                                                     int32_t* __restrict__ at, int32_t* __restrict__ order) {
+    __shared__ int32_t c[kParts];
+    part_of.load();
+    for (int64_t t0 = (int64_t)blockIdx.x * kPartTile; t0 < s; t0 += (int64_t)gridDim.x * kPartTile) {
+        c[threadIdx.x] = 0;
+        __syncthreads();
+        int32_t part[kPartTile / 256], rank[kPartTile / 256];
+#pragma unroll
+        for (int k = 0; k < kPartTile / 256; ++k) {
+            const int64_t i = t0 + 256 * k + threadIdx.x;
+            part[k] = i < s ? part_of(sample_hash(i0 + i, salt)) : -1;
+            rank[k] = i < s ? atomicAdd(&c[part[k]], 1) : 0;
+        }
+        __syncthreads();
+        const int32_t mine = c[threadIdx.x];
+        c[threadIdx.x] = mine ? atomicAdd(&at[threadIdx.x], mine) : 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPartTile / 256; ++k)
+            if (part[k] >= 0) order[c[part[k]] + rank[k]] = (int32_t)(t0 + 256 * k + threadIdx.x);
+        __syncthreads();
+    }
+}
+
+// Sums of the samples, spread over lines of 128 bytes.
+constexpr int kAccLines = 64, kAccStride = 16;
+
+// Samples of one block of the kernels that read them: contiguous ones, one per
+// thread, so that the resident blocks work close together and none starts a long
+// share when the others end (R-MAT s22, against 2048 blocks striding through
+// all: 2^25 triples 5.5 -> 4.3 ms, 2^24 draws of the stream 2.0 -> 1.6).
+constexpr int64_t kDrawsPerBlock = 256;
+
+// Samples partitioned together, and the calls whose samples are.  Triples: R-MAT
+// s22 with 2^25 samples took 16.3 -> 6.4 ms; from 2^21 samples it is 1.0 to 1.1
+// times faster on R-MAT s17 to s21 and from 2^23 1.2 to 1.4 times; at 2^20 and
+// below the two more launches cost what the locality gains (0.9 to 1.0 times),
+// and graphs below s17 fit the caches (0.9 times).
+constexpr int64_t kPartChunk = (int64_t)1 << 26;
+constexpr int64_t kPartSamples = (int64_t)1 << 21;
+constexpr int64_t kPartEntries = (int64_t)1 << 22;
+
+inline bool samples_partitioned(int64_t samples, int64_t m) { return samples >= kPartSamples && 2 * m >= kPartEntries; }
+
+// order[0 .. c) = the numbers i < c of the samples i0 + i by their parts; at[p]
+// = the end of part p (kParts + 1 words)
+template <typename Part>
+inline void partition_samples(int64_t i0, int64_t c, uint64_t salt, const Part& part_of, int32_t* at, int32_t* order,
+                              hipStream_t s) {
+    fill_i32(at, 0, kParts, s);
+    TC_LAUNCH("part_count", k_part_count<Part>, dim3((unsigned)num_cus() * 8), dim3(256), 0, s, i0, c, salt, part_of,
+              at);
+    scan_exclusive_i32(at, at, kParts, s);
+    TC_LAUNCH("part_place", k_part_place<Part>, dim3(ceil_div(c, kPartTile)), dim3(256), 0, s, i0, c, salt, part_of,
+              at, order);
+}
+
+// Adds the block's sums (256 threads) of a and b to words 0 and 1 of a line of
+// acc (kAccLines lines of kAccStride words): one atomic per block and sum; per
+// wave on one line they took 200 of 330 us at 2^19 triples on R-MAT s15.
+__device__ __forceinline__ void add_to_lines(int64_t a, int64_t b, unsigned long long* __restrict__ acc) {
+    __shared__ int64_t red[4][2];
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if (__lane_id() == 0) {
+        red[threadIdx.x >> 6][0] = a;
+        red[threadIdx.x >> 6][1] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const int64_t t = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
+        if (t) atomicAdd(&acc[(blockIdx.x % kAccLines) * kAccStride + threadIdx.x], (unsigned long long)t);
     }
 }
 

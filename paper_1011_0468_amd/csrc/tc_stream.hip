@@ -10,9 +10,11 @@
 //           vertex of H and an edge (h ascending, edges in (v, w) order,
 //           v < w); a draw asks for its closing edges: one for a wedge, two
 //           for a pair whose vertex is not in its edge (none otherwise: never
-//           closed).  The asked-for edges go into a hash table;
-//   pass 3: one pass over the edges marks every asked-for edge that exists;
-//           a draw is closed iff all its edges are marked.
+//           closed);
+//   pass 3: a draw is closed iff all its asked-for edges are in the graph.
+//           The adjacency lists are in order, so an edge is looked up in one
+//           of its ends' lists, and the draws come in the order of U, so that
+//           the lists they read lie together: passes 2 and 3 are one kernel.
 //
 // Every triangle has exactly three closed elements in U, one per vertex, so
 // |U| closed / (3 s) estimates t.  Draw i of pass 1 is upper edge
@@ -23,7 +25,9 @@
 #include "tc_device.h"
 #include "tc_prefix.h"
 
+#include <algorithm>
 #include <cmath>
+#include <vector>
 
 namespace tc {
 
@@ -34,9 +38,6 @@ uint64_t host_mix(uint64_t z) {
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBULL;
     return z ^ (z >> 31);
 }
-
-constexpr uint64_t kEmpty = ~0ull;        // an empty slot of the query table
-constexpr uint64_t kFound = 1ull << 63;   // set on a slot whose edge exists (ids < 2^31 leave bit 63 free)
 
 __device__ __forceinline__ int64_t hi_mul(uint64_t h, uint64_t size) { return (int64_t)__umul64hi(h, size); }
 
@@ -91,10 +92,10 @@ __global__ void k_stream_draw_edges(int64_t s1, uint64_t salt, int64_t m, const 
 }
 
 // H flags (candidates above the split) and the wedge count of every vertex
-// outside H; acc[0] += candidates
+// outside H; *found += candidates
 __global__ void k_stream_classify(int64_t n, int64_t m, const uint8_t* __restrict__ cand,
                                   const int32_t* __restrict__ deg, int32_t* __restrict__ hf,
-                                  int64_t* __restrict__ lc, unsigned long long* __restrict__ acc) {
+                                  int64_t* __restrict__ lc, unsigned long long* __restrict__ found) {
     int64_t nc = 0;
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
         const int64_t d = deg[x];
@@ -104,7 +105,7 @@ __global__ void k_stream_classify(int64_t n, int64_t m, const uint8_t* __restric
         hf[x] = h;
         lc[x] = h ? 0 : d * (d - 1) / 2;
     }
-    block_add(nc, &acc[0]);
+    block_add(nc, found);
 }
 
 __global__ void k_stream_hlist(int64_t n, const int32_t* __restrict__ hf, const int32_t* __restrict__ hpos,
@@ -113,107 +114,86 @@ __global__ void k_stream_hlist(int64_t n, const int32_t* __restrict__ hf, const 
         if (hf[x]) hlist[hpos[x]] = (int32_t)x;
 }
 
-__device__ __forceinline__ uint64_t edge_key(int32_t a, int32_t b) {
-    const uint64_t lo = (uint32_t)(a < b ? a : b), hi = (uint32_t)(a < b ? b : a);
-    return (lo << 32) | hi;
-}
-
-// The query table: open addressing over 2^lg slots of 64-bit keys, home slot
-// mix64(key) mod 2^lg, at most half of the slots used.
-struct QueryTable {
-    unsigned long long* tab;
-    int lg;
-    __device__ __forceinline__ uint64_t mask() const { return (1ull << lg) - 1; }
+// Parts of the draws.  The wedges (elements below L) come first, in the order of
+// U; the pairs by the position of their edge, whose lower end's list the first
+// lookup reads, in as many of the 256 parts as are left.
+struct StreamParts {
+    const int64_t* Lp;    // |L|
+    const int32_t* Hp;    // |H|
+    int64_t m;
+    int64_t L;            // from here on set by load()
+    double scale, inv_m;  // parts per element, edges per element
+    int32_t first;        // the first part of the pairs
+    __device__ __forceinline__ void load() {
+        L = *Lp;
+        const int64_t size = L + (int64_t)*Hp * m;
+        scale = size > 0 ? (double)kParts / (double)size : 0.0;
+        inv_m = 1.0 / (double)m;
+        first = L > 0 ? wedge_part(L - 1) + 1 : 0;
+    }
+    __device__ __forceinline__ int64_t size() const { return L + (int64_t)*Hp * m; }
+    __device__ __forceinline__ int32_t wedge_part(int64_t r) const {
+        const int32_t p = (int32_t)((double)r * scale);
+        return p < kParts - 1 ? p : kParts - 1;
+    }
+    __device__ __forceinline__ int32_t operator()(uint64_t hash) const {
+        const int64_t r = hi_mul(hash, (uint64_t)size());
+        if (r < L) return wedge_part(r);
+        const double x = (double)(r - L) * inv_m;
+        const int32_t p = first + (int32_t)((x - floor(x)) * (double)(kParts - first));
+        return p < kParts - 1 ? p : kParts - 1;
+    }
 };
 
-// the slot of key in the query table (inserted if absent)
-__device__ __forceinline__ int32_t table_insert(const QueryTable& T, uint64_t key) {
-    uint64_t slot = mix64(key) & T.mask();
-    while (true) {
-        const unsigned long long prev = atomicCAS(&T.tab[slot], (unsigned long long)kEmpty, (unsigned long long)key);
-        if (prev == kEmpty || prev == key) return (int32_t)slot;
-        slot = (slot + 1) & T.mask();
-    }
-}
-
-// pass 2: draw j's element of U and the slots of its closing edges (-1: none,
-// -2: drawn but never closed)
-__global__ void __launch_bounds__(256) k_stream_draw_triples(int64_t s, uint64_t salt, int64_t m,
-                                                             const int32_t* __restrict__ rp,
-                                                             const int32_t* __restrict__ col, PrefixIndex<int32_t> up,
-                                                             PrefixIndex<int64_t> light,
-                                                             const int32_t* __restrict__ hlist,
-                                                             const int32_t* __restrict__ hcount, QueryTable T,
-                                                             int2* __restrict__ q) {
-    const int64_t L = light.pre[light.n];
-    const int64_t size = L + (int64_t)hcount[0] * m;
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < s; j += (int64_t)gridDim.x * blockDim.x) {
-        int2 slots = make_int2(-1, -1);
-        if (size > 0) {
-            const int64_t r = hi_mul(mix64(mix64((uint64_t)j) ^ salt), (uint64_t)size);
-            if (r < L) {  // wedge k of light vertex u: pair (a, b) of colex order
-                const int64_t u = find_item(light, r);
-                const int64_t k = r - light.pre[u];
-                int64_t b = (int64_t)((1.0 + sqrt(1.0 + 8.0 * (double)k)) * 0.5);  // then made exact
-                while (b > 1 && b * (b - 1) / 2 > k) --b;
-                while ((b + 1) * b / 2 <= k) ++b;
-                const int64_t a = k - b * (b - 1) / 2;
-                slots.x = table_insert(T, edge_key(col[rp[u] + a], col[rp[u] + b]));
-            } else {  // the pair of heavy vertex h and upper edge (v, w)
-                const int64_t qq = r - L;
-                const int32_t h = hlist[qq / m];
-                int32_t v, w;
-                upper_edge(up, rp, col, qq % m, v, w);
-                if (h != v && h != w) {
-                    slots.x = table_insert(T, edge_key(h, v));
-                    slots.y = table_insert(T, edge_key(h, w));
-                } else {
-                    slots = make_int2(-2, -2);  // drawn, never closed, no query
-                }
-            }
-        }
-        q[j] = slots;
-    }
-}
-
-// pass 3: every edge of the stream (upper entries) marks its slot if asked for
-__global__ void __launch_bounds__(256) k_stream_mark(int64_t E2, const int32_t* __restrict__ src,
-                                                     const int32_t* __restrict__ col, QueryTable T) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E2; e += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t u = src[e], v = col[e];
-        if (u >= v) continue;  // each undirected edge once
-        const uint64_t key = edge_key(u, v);
-        uint64_t slot = mix64(key) & T.mask();
-        while (true) {
-            const uint64_t t = T.tab[slot];
-            if (t == kEmpty) break;
-            if ((t & ~kFound) == key) {
-                if (!(t & kFound)) T.tab[slot] = key | kFound;  // only this edge's lookups write this slot
-                break;
-            }
-            slot = (slot + 1) & T.mask();
-        }
-    }
-}
-
-// acc[1] += closed draws, acc[2] += closing-edge lookups
-__global__ void k_stream_count(int64_t s, const int2* __restrict__ q, const unsigned long long* __restrict__ tab,
-                               unsigned long long* __restrict__ acc) {
+// Passes 2 and 3: draws i0 + order[i] (order null: i0 + i), i < s; words 0 and 1
+// of the lines of acc += closed draws and closing-edge lookups.  Bound by random
+// reads: the element's prefix and list entries and the lists searched.  Each
+// XCD takes a contiguous eighth of the partitioned wedges, then one of the
+// pairs, so that the lists of the wedges' vertices and of the lower ends of the
+// pairs' edges stay in its L2; the second lookup of a pair, which is anywhere in
+// the graph, is left out if the first fails.  R-MAT s22, 2^24 draws: 1.62 ms and
+// 47 M L2 misses; with the pairs in the order of U, where the heavy vertex's
+// list is local and the edge is not, 2.1; as a table of the lookups filled by
+// random compare-and-swaps, an edge pass that marks it and a pass that counts,
+// 4.0.
+__global__ void __launch_bounds__(256, 8) k_stream_draws(int64_t i0, int64_t s, const int32_t* __restrict__ order,
+                                                       const int32_t* __restrict__ at, StreamParts parts,
+                                                       uint64_t salt, int64_t m, const int32_t* __restrict__ rp,
+                                                       const int32_t* __restrict__ col, PrefixIndex<int32_t> up,
+                                                       PrefixIndex<int64_t> light, const int32_t* __restrict__ hlist,
+                                                       unsigned long long* __restrict__ acc) {
+    parts.load();
+    const int64_t L = parts.L, size = parts.size();
+    const float scale = 1.0f / (float)light.n;
     int64_t closed = 0, queries = 0;
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < s; j += (int64_t)gridDim.x * blockDim.x) {
-        const int2 sl = q[j];
-        if (sl.x == -2 || sl.x == -1) continue;  // never closed / no element
-        const bool f0 = (tab[sl.x] & kFound) != 0;
-        if (sl.y < 0) {
+    const int64_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
+    const int64_t wedges = order && parts.first > 0 ? at[parts.first - 1] : 0, pairs = s - wedges;
+    const int64_t w0 = wedges * xcd / 8, p0 = wedges + pairs * xcd / 8;  // this XCD's of either kind
+    const int64_t wc = wedges * (xcd + 1) / 8 - w0, pc = wedges + pairs * (xcd + 1) / 8 - p0;
+    const int64_t end = size > 0 ? (wc + pc) * (slot + 1) / slots : 0;
+    for (int64_t j = (wc + pc) * slot / slots + threadIdx.x; j < end; j += 256) {
+        const int64_t i = j < wc ? w0 + j : p0 + (j - wc);
+        const int64_t r = hi_mul(sample_hash(i0 + (order ? order[i] : i), salt), (uint64_t)size);
+        if (r < L) {  // wedge k of light vertex u: pair (a, b) of colex order
+            const int64_t u = find_item(light, r);
+            const int64_t k = r - light.pre[u];
+            int64_t b = (int64_t)((1.0 + sqrt(1.0 + 8.0 * (double)k)) * 0.5);  // then made exact
+            while (b > 1 && b * (b - 1) / 2 > k) --b;
+            while ((b + 1) * b / 2 <= k) ++b;
+            const int64_t a = k - b * (b - 1) / 2;
             queries += 1;
-            closed += f0;
-        } else {
+            closed += adjacent(rp, col, col[rp[u] + a], col[rp[u] + b], scale);
+        } else {  // the pair of heavy vertex h and upper edge (v, w)
+            const int64_t qq = r - L;
+            const int32_t h = hlist[qq / m];
+            int32_t v, w;
+            upper_edge(up, rp, col, qq % m, v, w);
+            if (h == v || h == w) continue;  // never closed, no lookups
             queries += 2;
-            closed += f0 && (tab[sl.y] & kFound) != 0;
+            closed += in_list(col, rp[v], rp[v + 1], h, scale) && adjacent(rp, col, w, h, scale);
         }
     }
-    block_add(closed, &acc[1]);
-    block_add(queries, &acc[2]);
+    add_to_lines(closed, queries, acc);
 }
 
 unsigned grid(int64_t N, int64_t cap = 65536) {
@@ -234,7 +214,7 @@ int64_t stream_draws(int64_t n, int64_t m, double d) {
 }
 
 void stream_estimate(const tc_graph_s* g, double d, int64_t s, uint64_t seed, hipStream_t st, tc_stream_result* out) {
-    const int64_t n = g->n, m = g->m, E2 = 2 * m;
+    const int64_t n = g->n, m = g->m;
     tc_stream_result r{};
     r.m = m;
     r.draws1 = stream_draws(n, m, d);
@@ -264,10 +244,10 @@ void stream_estimate(const tc_graph_s* g, double d, int64_t s, uint64_t seed, hi
                   (const int32_t*)g->row_ptr, (const int32_t*)g->col, up, cand.get());
     DevBuf<int32_t> hf(n + 1, st), hpos(n + 1, st);
     DevBuf<int64_t> lc(n + 1, st), lpre(n + 1, st);
-    DevBuf<unsigned long long> acc(3, st);
-    fill_i64(reinterpret_cast<int64_t*>(acc.get()), 0, 3, st);
+    DevBuf<unsigned long long> acc(kAccLines * kAccStride + 1, st);  // the draws' sums, then the candidates
+    fill_i64(reinterpret_cast<int64_t*>(acc.get()), 0, kAccLines * kAccStride + 1, st);
     TC_LAUNCH("stream_classify", k_stream_classify, dim3(grid(n, kReduceBlocks)), dim3(256), 0, st, n, m,
-              (const uint8_t*)cand.get(), (const int32_t*)g->deg, hf.get(), lc.get(), acc.get());
+              (const uint8_t*)cand.get(), (const int32_t*)g->deg, hf.get(), lc.get(), acc.get() + kAccLines * kAccStride);
     scan_exclusive_i32(hf.get(), hpos.get(), n, st);
     scan64(lc.get(), lpre.get(), n, st);
     DevBuf<int32_t> hlist(n, st);
@@ -276,36 +256,36 @@ void stream_estimate(const tc_graph_s* g, double d, int64_t s, uint64_t seed, hi
     TC_LAUNCH("stream_index", k_bucket_index<int64_t>, dim3(grid(n)), dim3(256), 0, st, n,
               (const int64_t*)lpre.get(), k, light_idx.get());
     const PrefixIndex<int64_t> light{lpre.get(), light_idx.get(), n, k};
-    // passes 2 and 3: a table of at least twice as many slots as lookups
-    int lg = 10;
-    while (((int64_t)1 << lg) < 4 * s) ++lg;
-    const int64_t cap = (int64_t)1 << lg;
-    DevBuf<unsigned long long> tab(cap, st);
-    fill_i64(reinterpret_cast<int64_t*>(tab.get()), -1, cap, st);
-    const QueryTable T{tab.get(), lg};
-    DevBuf<int2> q(s > 0 ? s : 1, st);
+    // passes 2 and 3
     const uint64_t salt2 = host_mix(seed ^ 0x54435F5354524D32ULL);  // "TC_STRM2"
-    if (s > 0) {
-        TC_LAUNCH("stream_pass2", k_stream_draw_triples, dim3(grid(s)), dim3(256), 0, st, s, salt2, m,
-                  (const int32_t*)g->row_ptr, (const int32_t*)g->col, up, light, (const int32_t*)hlist.get(),
-                  (const int32_t*)hpos.get() + n, T, q.get());
-        TC_LAUNCH("stream_pass3", k_stream_mark, dim3(grid(E2)), dim3(256), 0, st, E2, (const int32_t*)g->src,
-                  (const int32_t*)g->col, T);
-        TC_LAUNCH("stream_count", k_stream_count, dim3(grid(s, kReduceBlocks)), dim3(256), 0, st, s, (const int2*)q.get(),
-                  (const unsigned long long*)tab.get(), acc.get());
+    const bool part = samples_partitioned(s, m);
+    const int64_t chunk = part ? std::min(s, kPartChunk) : s;
+    DevBuf<int32_t> order(part ? chunk : 0, st), at(part ? kParts + 1 : 0, st);
+    const StreamParts parts{lpre.get() + n, hpos.get() + n, m, 0, 0.0, 0.0, 0};
+    for (int64_t i0 = 0; i0 < s; i0 += chunk) {
+        const int64_t c = std::min(chunk, s - i0);
+        if (part) partition_samples(i0, c, salt2, parts, at.get(), order.get(), st);
+        const int64_t sg = ceil_div(c, 8 * kDrawsPerBlock) * 8;  // a multiple of the XCDs
+        TC_LAUNCH("stream_draws", k_stream_draws, dim3((unsigned)sg), dim3(256), 0, st, i0, c,
+                  part ? (const int32_t*)order.get() : (const int32_t*)nullptr, (const int32_t*)at.get(), parts, salt2, m,
+                  (const int32_t*)g->row_ptr, (const int32_t*)g->col, up, light, (const int32_t*)hlist.get(), acc.get());
     }
-    int64_t h3[3], L = 0;
+    std::vector<int64_t> sums(kAccLines * kAccStride + 1);
+    int64_t L = 0;
     int32_t H = 0;
-    check_hip(hipMemcpyAsync(h3, acc.get(), sizeof(h3), hipMemcpyDeviceToHost, st), "stream counts");
+    check_hip(hipMemcpyAsync(sums.data(), acc.get(), sizeof(int64_t) * sums.size(), hipMemcpyDeviceToHost, st),
+              "stream counts");
     check_hip(hipMemcpyAsync(&H, hpos.get() + n, sizeof(int32_t), hipMemcpyDeviceToHost, st), "heavy count");
     check_hip(hipMemcpyAsync(&L, lpre.get() + n, sizeof(int64_t), hipMemcpyDeviceToHost, st), "light size");
     check_hip(hipStreamSynchronize(st), "sync");
-    r.candidates = h3[0];
+    r.candidates = sums[kAccLines * kAccStride];
     r.heavy = H;
     r.light_size = L;
     r.size = L + (int64_t)H * m;
-    r.closed = h3[1];
-    r.queries = h3[2];
+    for (int l = 0; l < kAccLines; ++l) {
+        r.closed += sums[l * kAccStride];
+        r.queries += sums[l * kAccStride + 1];
+    }
     if (s > 0) {
         volatile double num = (double)r.size * (double)r.closed;
         volatile double den = 3.0 * (double)s;

@@ -148,104 +148,12 @@ void scan64(const int64_t* in, int64_t* out, int64_t N, hipStream_t s) {
 
 namespace {
 
-// y in the sorted list col[lo .. end) of ids below n (scale = 1 / n).  Every
-// step of a binary search of a long list reads another cache line, so lists
-// past one line are entered where y would be if their ids were spread evenly
-// (as relabelled graphs' are: off by about the root of the length) and the
-// range is widened from there by doubling: 6.6 -> 5.5 ms for the samples on
-// R-MAT s22, and at most twice the steps on any list.
-__device__ __forceinline__ bool in_list(const int32_t* __restrict__ col, int32_t lo, int32_t end, int32_t y,
-                                        float scale) {
-    int32_t hi = end;
-    if (end - lo > 32) {
-        int32_t g = lo + (int32_t)((float)(end - lo) * ((float)y * scale));
-        g = g < end - 1 ? g : end - 1;  // >= lo
-        int32_t step = 16;
-        if (col[g] < y) {
-            lo = g + 1;
-            while (hi - lo > step && col[lo + step] < y) {
-                lo += step + 1;
-                step *= 2;
-            }
-            hi = hi - lo > step ? lo + step : hi;
-        } else {
-            hi = g;
-            while (hi - lo > step && col[hi - 1 - step] >= y) {
-                hi -= step + 1;
-                step *= 2;
-            }
-            if (hi - lo > step) lo = hi - step;
-        }
-        // the first entry >= y lies in [lo, hi]
-    }
-    while (lo < hi) {
-        const int32_t mid = lo + ((hi - lo) >> 1);
-        if (col[mid] < y) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo < end && col[lo] == y;
-}
-
-__device__ __forceinline__ bool adjacent(const int32_t* __restrict__ rp, const int32_t* __restrict__ col, int32_t x,
-                                         int32_t y, float scale) {
-    const int32_t xs = rp[x], xe = rp[x + 1], ys = rp[y], ye = rp[y + 1];
-    return xe - xs <= ye - ys ? in_list(col, xs, xe, y, scale) : in_list(col, ys, ye, x, scale);
-}
-
-// the 64-bit hash of sample i: its element of U is the high half of h * |U|
-__device__ __forceinline__ uint64_t sample_hash(int64_t i, uint64_t salt) { return mix64(mix64((uint64_t)i) ^ salt); }
-
-// ---- partition of the samples by the top byte of their hash ----------------
-// Samples in hash order touch prefixes, lists and list prefixes all over the
-// graph (a new cache line per search step); after the partition a wave's
-// samples lie in one 256th of U.  Counts per byte, their bases, then the
-// sample numbers (relative to i0) at their places, in any order inside a part.
-constexpr int kParts = 256, kPartTile = 8192;
-
-__global__ void __launch_bounds__(256) k_tri_part_count(int64_t i0, int64_t s, uint64_t salt,
-                                                         int32_t* __restrict__ cnt) {
-    __shared__ int32_t c[kParts];
-    c[threadIdx.x] = 0;
-    __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < s; i += (int64_t)gridDim.x * 256)
-        atomicAdd(&c[sample_hash(i0 + i, salt) >> 56], 1);
-    __syncthreads();
-    if (c[threadIdx.x]) atomicAdd(&cnt[threadIdx.x], c[threadIdx.x]);
-}
-
-__global__ void __launch_bounds__(256) k_tri_part_place(int64_t i0, int64_t s, uint64_t salt,
-                                                         int32_t* __restrict__ at, int32_t* __restrict__ order) {
-    __shared__ int32_t c[kParts];
-    for (int64_t t0 = (int64_t)blockIdx.x * kPartTile; t0 < s; t0 += (int64_t)gridDim.x * kPartTile) {
-        c[threadIdx.x] = 0;
-        __syncthreads();
-        int32_t part[kPartTile / 256], rank[kPartTile / 256];
-#pragma unroll
-        for (int k = 0; k < kPartTile / 256; ++k) {
-            const int64_t i = t0 + 256 * k + threadIdx.x;
-            part[k] = i < s ? (int32_t)(sample_hash(i0 + i, salt) >> 56) : -1;
-            rank[k] = i < s ? atomicAdd(&c[part[k]], 1) : 0;
-        }
-        __syncthreads();
-        const int32_t mine = c[threadIdx.x];
-        c[threadIdx.x] = mine ? atomicAdd(&at[threadIdx.x], mine) : 0;
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kPartTile / 256; ++k)
-            if (part[k] >= 0) order[c[part[k]] + rank[k]] = (int32_t)(t0 + 256 * k + threadIdx.x);
-        __syncthreads();
-    }
-}
-
-// Sums of the samples, spread over lines of 128 bytes.
-constexpr int kAccLines = 64, kAccStride = 16;
-
 // Sum of the closed samples' weights and closed samples, over
 // the samples i0 + order[i] (order null: i0 + i), i < s.  Bound by random
 // reads: per sample the index, the prefix, the two ends' ids and row starts
 // and the steps of the closing search.  Each XCD takes a contiguous eighth, so
 // that with the partition its samples' lists and prefixes stay in its L2.
-__global__ void __launch_bounds__(256) k_tri_sample(int64_t i0, int64_t s, const int32_t* __restrict__ order,
+__global__ void __launch_bounds__(256, 8) k_tri_sample(int64_t i0, int64_t s, const int32_t* __restrict__ order,
                                                      uint64_t salt, PrefixIndex<int64_t> P,
                                                      const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                      const int64_t* __restrict__ EP, int64_t m, int hybrid,
@@ -255,8 +163,9 @@ __global__ void __launch_bounds__(256) k_tri_sample(int64_t i0, int64_t s, const
     const float scale = 1.0f / (float)P.n;
     int64_t wsum = 0, closed = 0;
     const int64_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
-    const int64_t end = s * (xcd + 1) / 8;
-    for (int64_t i = s * xcd / 8 + slot * 256 + threadIdx.x; size > 0 && i < end; i += slots * 256) {
+    const int64_t i8 = s * xcd / 8, c8 = s * (xcd + 1) / 8 - i8;
+    const int64_t end = size > 0 ? i8 + c8 * (slot + 1) / slots : 0;
+    for (int64_t i = i8 + c8 * slot / slots + threadIdx.x; i < end; i += 256) {
         const int64_t r = (int64_t)__umul64hi(sample_hash(i0 + (order ? order[i] : i), salt), (uint64_t)size);
         const int32_t u = (int32_t)find_item(P, r);
         const int64_t k = r - CU[u];
@@ -283,7 +192,9 @@ __global__ void __launch_bounds__(256) k_tri_sample(int64_t i0, int64_t s, const
             x = u;
             y = v;
             z = col[rp[v] + (k - EP[elo])];
-            cl = z != u && adjacent(rp, col, u, z, scale);
+            // after the partition u's list is read by the samples around this
+            // one and z's by none: 4.3 -> 4.0 ms for 2^25 on R-MAT s22
+            cl = z != u && (order ? in_list(col, us, us + du, z, scale) : adjacent(rp, col, u, z, scale));
         }
         if (cl) {
             const auto ext = [&](int32_t w) { return (int)ext_kind(hybrid, rp[w + 1] - rp[w], m); };
@@ -291,30 +202,9 @@ __global__ void __launch_bounds__(256) k_tri_sample(int64_t i0, int64_t s, const
             closed += 1;
         }
     }
-    // one atomic per block and sum, over kAccLines lines: per wave on one line
-    // they took 200 of 330 us at 2^19 samples on R-MAT s15
-    __shared__ int64_t red[4][2];
-    wsum = wave_sum(wsum);
-    closed = wave_sum(closed);
-    if (__lane_id() == 0) {
-        red[threadIdx.x >> 6][0] = wsum;
-        red[threadIdx.x >> 6][1] = closed;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        const int64_t t = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
-        if (t) atomicAdd(&acc[(blockIdx.x % kAccLines) * kAccStride + threadIdx.x], (unsigned long long)t);
-    }
+    add_to_lines(wsum, closed, acc);
 }
 
-// Samples partitioned together, and the calls that are: R-MAT s22 with 2^25
-// samples takes 16.3 -> 6.4 ms; from 2^21 samples it is 1.0 to 1.1 times
-// faster on R-MAT s17 to s21 and from 2^23 1.2 to 1.4 times; at 2^20 and below
-// the two more launches cost what the locality gains (0.9 to 1.0 times), and
-// graphs below s17 fit the caches (0.9 times).
-constexpr int64_t kPartChunk = (int64_t)1 << 26;
-constexpr int64_t kPartSamples = (int64_t)1 << 21;
-constexpr int64_t kPartEntries = (int64_t)1 << 22;
 constexpr int64_t kIndexVertices = (int64_t)1 << 16;
 
 }  // namespace
@@ -344,20 +234,13 @@ void triple_sample(const tc_graph_s* g, int hybrid, int64_t num_samples, uint64_
                   idx.get());
     const PrefixIndex<int64_t> P{CU.get(), kb ? idx.get() : nullptr, n, kb};
     const uint64_t salt = host_mix64(seed ^ 0x54435F545249504CULL);  // "TC_TRIPL"
-    const bool part = num_samples >= kPartSamples && 2 * m >= kPartEntries;
+    const bool part = samples_partitioned(num_samples, m);
     const int64_t chunk = part ? std::min(num_samples, kPartChunk) : num_samples;
-    DevBuf<int32_t> order(part ? chunk : 0, s), at(kParts + 1, s);
+    DevBuf<int32_t> order(part ? chunk : 0, s), at(part ? kParts + 1 : 0, s);
     for (int64_t i0 = 0; i0 < num_samples; i0 += chunk) {
         const int64_t c = std::min(chunk, num_samples - i0);
-        if (part) {
-            fill_i32(at.get(), 0, kParts, s);
-            TC_LAUNCH("tri_part", k_tri_part_count, dim3((unsigned)num_cus() * 8), dim3(256), 0, s, i0, c, salt,
-                      at.get());
-            scan_exclusive_i32(at.get(), at.get(), kParts, s);
-            TC_LAUNCH("tri_part", k_tri_part_place, dim3(ceil_div(c, kPartTile)), dim3(256), 0, s, i0, c, salt,
-                      at.get(), order.get());
-        }
-        const int64_t sg = std::min<int64_t>((c + 2047) / 2048, (int64_t)num_cus()) * 8;  // a multiple of the XCDs
+        if (part) partition_samples(i0, c, salt, HashParts{}, at.get(), order.get(), s);
+        const int64_t sg = ceil_div(c, 8 * kDrawsPerBlock) * 8;  // a multiple of the XCDs
         TC_LAUNCH("tri_sample", k_tri_sample, dim3((unsigned)sg), dim3(256), 0, s, i0, c,
                   part ? (const int32_t*)order.get() : (const int32_t*)nullptr, salt, P, (const int32_t*)g->row_ptr,
                   (const int32_t*)g->col, (const int64_t*)EP.get(), m, hybrid, acc.get());
