@@ -32,7 +32,8 @@ HBM_PEAK_GBS = 8000.0
 # serving: requests of at most this many pairs (R-MAT scale <= 14 at edge
 # factor 16) are fused with the small requests queued behind them
 FUSE_PAIRS = 1 << 18
-DOMINANT = ("light_small", "light_large")
+# the list kernels of the light closure, by the model their items are counted in
+LIGHT_KERNELS = {"light_small": ("light_small",), "light_large": ("light_bits", "light_large", "light_huge")}
 
 
 def _light_model_bytes(c, large):
@@ -44,7 +45,7 @@ def _light_model_bytes(c, large):
 
 
 COUNT_SOURCES = ("tc_count.hip", "tc_device.h")
-STREAM_SOURCES = ("tc_stream.hip", "tc_device.h")
+STREAM_SOURCES = ("tc_stream.hip", "tc_prefix.h", "tc_device.h")
 
 
 def _source_sha(sources=COUNT_SOURCES):
@@ -538,10 +539,11 @@ def rp_workload(args):
 def stream_workload(args):
     """Semi-streaming three-pass estimate (section 5.2) on R-MAT scale 22 with
     d = 1 and 2^24 pass-2 draws: time per call, draws per second, every
-    pass's kernel time, the estimate against the exact count, and parity of
-    the seed-0 and seed-1 results with the oracle's stored values.  Roofline
-    of pass 3 (the edge pass): 8 B per CSR entry read (its row and column)
-    and 8 B per upper edge looked up in the query table."""
+    kernel's time, the estimate against the exact count, and parity of the
+    seed-0 and seed-1 results with the oracle's stored values.  Roofline of
+    the draws' kernel (passes 2 and 3): per draw its number (4 B) and the
+    prefix entry, the row offset and the list entry that name its element (16
+    B), per lookup a row offset and a list entry (8 B)."""
     import torch
     import synth
     import paper_1011_0468_amd as tc
@@ -569,15 +571,15 @@ def stream_workload(args):
     ms = (time.perf_counter() - t) * 1e3 / args.steps
     tc.profile.enable(False)
     kern = {}
-    for name in ("stream_up", "stream_index", "stream_pass1", "stream_classify", "stream_hlist", "stream_pass2",
-                 "stream_pass3", "stream_count"):
+    for name in ("stream_up", "stream_index", "stream_pass1", "stream_classify", "stream_hlist", "part_count",
+                 "part_place", "stream_draws"):
         tot, cnt = tc.profile.read(name)
         if cnt:
             kern[name] = {"ms_per_call": round(tot / args.steps, 4), "launches_per_call": cnt // args.steps}
     m = info["m"]
-    p3_bytes = 8 * 2 * m + 8 * m
-    p3_ms = kern.get("stream_pass3", {}).get("ms_per_call", 0.0)
-    gbs = p3_bytes / (p3_ms / 1e3) / 1e9 if p3_ms else 0.0
+    draw_bytes = 20 * S + 8 * r["queries"]
+    draw_ms = kern.get("stream_draws", {}).get("ms_per_call", 0.0)
+    gbs = draw_bytes / (draw_ms / 1e3) / 1e9 if draw_ms else 0.0
     exact = golden["exact"] if golden else None
     print(json.dumps({"metric": "semi-streaming estimate, pass-2 draws/sec at R-MAT s22 (d = 1, 2^24 draws)",
                       "value": round(S / (ms / 1e3), 1), "unit": "draws/s", "n_gpus": 1, "steps": args.steps,
@@ -587,8 +589,8 @@ def stream_workload(args):
                       "kernels": kern,
                       "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                    "frac": round(gbs / HBM_PEAK_GBS, 4),
-                                   "traffic": _traffic("stream_pass3", "rmat22", None, STREAM_SOURCES),
-                                   "kernel": "stream_pass3", "model_bytes_per_launch": p3_bytes},
+                                   "traffic": _traffic("stream_draws", "rmat22", None, STREAM_SOURCES),
+                                   "kernel": "stream_draws", "model_bytes_per_launch": draw_bytes},
                       "config": {"workload": "stream_rmat22", "n": info["n"], "m": m, "d": dd, "num_samples": S,
                                  "seed": args.seed}}), flush=True)
 
@@ -720,7 +722,7 @@ def main():
         torch.cuda.synchronize()
         per_call_ms.append(round((time.perf_counter() - t) * 1e3, 3))
 
-    tc.profile.select(list(DOMINANT))
+    tc.profile.select([k for names in LIGHT_KERNELS.values() for k in names])
     tc.profile.reset()
     tc.profile.enable(True)
     torch.cuda.synchronize()
@@ -734,21 +736,20 @@ def main():
     edges = sum(c["m"] for c in res)
     value = edges / (ms_per_step / 1e3)
 
-    # roofline of the dominant kernel: algorithmic bytes / measured launch time
+    # roofline of the dominant kernels: algorithmic bytes / measured launch time
     kern = {}
-    for name in DOMINANT:
-        ms_tot, launches = tc.profile.read(name)
-        large = name == "light_large"
-        model = sum(_light_model_bytes(c, large) for c in res) * args.steps
-        kern[name] = (ms_tot, launches, model)
-    dom = max(DOMINANT, key=lambda k: kern[k][0])
+    for group, names in LIGHT_KERNELS.items():
+        reads = [tc.profile.read(k) for k in names]
+        model = sum(_light_model_bytes(c, group == "light_large") for c in res) * args.steps
+        kern[group] = (sum(r[0] for r in reads), sum(r[1] for r in reads), model)
+    dom = max(kern, key=lambda k: kern[k][0])
     ms_tot, launches, model = kern[dom]
     achieved = (model / (ms_tot / 1e3)) / 1e9 if ms_tot > 0 else 0.0
     traffic = _traffic(dom, args.workload, tunings)
     wedge_bytes = 4 * sum(c["wedges"] for c in res)
     all_light_model = sum(c["model_bytes_small"] + c["model_bytes_large"] for c in res)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": dom,
+                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": "+".join(LIGHT_KERNELS[dom]),
                 "avg_launch_ms": round(ms_tot / max(launches, 1), 4), "launches": launches,
                 "model_bytes_per_launch": int(model / max(launches, 1)),
                 "model": "list bytes of the light closure (per work item the anchor's list and row offsets, "
