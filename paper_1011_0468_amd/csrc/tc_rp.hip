@@ -305,7 +305,8 @@ void rp_trace(const tc_graph_s* g, int32_t k, uint64_t seed, hipStream_t s, int6
     {
         // |q_l| <= sum over entries (i, j) of |Y_il| |Y_jl| <= sum of deg_i deg_j; every q_l and their sum
         // stay exact while k times that is below 2^62 (margin for the double rounding).  A bound from the
-        // degree classes settles most graphs (R-MAT s22: 0.65 -> 0.25 ms); where it does not, the degrees themselves decide.
+        // degree classes settles most graphs (R-MAT s22: 0.65 -> 0.25 ms); where it does not, the degrees
+        // themselves decide.
         unsigned blocks = ceil_div(E2, 256);
         if (blocks > 2048) blocks = 2048;
         DevBuf<double> part(blocks, s);

@@ -73,10 +73,8 @@ __global__ void k_up_deg(int64_t n, const int32_t* __restrict__ rp, const int32_
 __device__ __forceinline__ void upper_edge(const PrefixIndex<int32_t>& P, const int32_t* __restrict__ rp,
                                            const int32_t* __restrict__ col, int64_t r, int32_t& u, int32_t& v) {
     const int64_t x = find_item(P, r);
-    const int32_t deg = rp[x + 1] - rp[x];
-    const int32_t upd = P.pre[x + 1] - P.pre[x];
     u = (int32_t)x;
-    v = col[rp[x] + (deg - upd) + (int32_t)(r - P.pre[x])];
+    v = col[rp[x + 1] - (P.pre[x + 1] - (int32_t)r)];  // its upper entries end the list
 }
 
 // pass 1: the endpoints of s1 drawn edges
@@ -190,7 +188,8 @@ __global__ void __launch_bounds__(256, 8) k_stream_draws(int64_t i0, int64_t s, 
             upper_edge(up, rp, col, qq % m, v, w);
             if (h == v || h == w) continue;  // never closed, no lookups
             queries += 2;
-            closed += in_list(col, rp[v], rp[v + 1], h, scale) && adjacent(rp, col, w, h, scale);
+            const int2 vr = two_at(rp + v);
+            closed += in_list(col, vr.x, vr.y, h, scale) && adjacent(rp, col, w, h, scale);
         }
     }
     add_to_lines(closed, queries, acc);
@@ -247,7 +246,8 @@ void stream_estimate(const tc_graph_s* g, double d, int64_t s, uint64_t seed, hi
     DevBuf<unsigned long long> acc(kAccLines * kAccStride + 1, st);  // the draws' sums, then the candidates
     fill_i64(reinterpret_cast<int64_t*>(acc.get()), 0, kAccLines * kAccStride + 1, st);
     TC_LAUNCH("stream_classify", k_stream_classify, dim3(grid(n, kReduceBlocks)), dim3(256), 0, st, n, m,
-              (const uint8_t*)cand.get(), (const int32_t*)g->deg, hf.get(), lc.get(), acc.get() + kAccLines * kAccStride);
+              (const uint8_t*)cand.get(), (const int32_t*)g->deg, hf.get(), lc.get(),
+              acc.get() + kAccLines * kAccStride);
     scan_exclusive_i32(hf.get(), hpos.get(), n, st);
     scan64(lc.get(), lpre.get(), n, st);
     DevBuf<int32_t> hlist(n, st);
@@ -267,8 +267,9 @@ void stream_estimate(const tc_graph_s* g, double d, int64_t s, uint64_t seed, hi
         if (part) partition_samples(i0, c, salt2, parts, at.get(), order.get(), st);
         const int64_t sg = ceil_div(c, 8 * kDrawsPerBlock) * 8;  // a multiple of the XCDs
         TC_LAUNCH("stream_draws", k_stream_draws, dim3((unsigned)sg), dim3(256), 0, st, i0, c,
-                  part ? (const int32_t*)order.get() : (const int32_t*)nullptr, (const int32_t*)at.get(), parts, salt2, m,
-                  (const int32_t*)g->row_ptr, (const int32_t*)g->col, up, light, (const int32_t*)hlist.get(), acc.get());
+                  part ? (const int32_t*)order.get() : (const int32_t*)nullptr, (const int32_t*)at.get(), parts,
+                  salt2, m, (const int32_t*)g->row_ptr, (const int32_t*)g->col, up, light,
+                  (const int32_t*)hlist.get(), acc.get());
     }
     std::vector<int64_t> sums(kAccLines * kAccStride + 1);
     int64_t L = 0;

@@ -46,3 +46,17 @@ def test_clustered_ids(gpu, where, p):
         a, b = (np.where(x % 2, n - 1 - x, x) for x in (a, b))
     _check(gpu, n, a.astype(np.int32), b.astype(np.int32), 50000, True, p)
     _check(gpu, n, a.astype(np.int32), b.astype(np.int32), 50000, False, p)
+
+
+@pytest.mark.parametrize("samples", [(1 << 18) - 1, 1 << 18, 1 << 20])
+def test_extension_index_threshold(gpu, samples):
+    n, src, dst = synth.rmat(18, 16, seed=2)
+    _check(gpu, n, src, dst, samples, True)
+
+
+@pytest.mark.parametrize("leaves,hubs", [(65536, 1), (70001, 2), (200000, 3)])
+def test_extension_index_of_few_long_lists(gpu, leaves, hubs):
+    ids = np.arange(hubs, hubs + leaves)
+    src = np.concatenate([np.repeat(np.arange(hubs), leaves), ids[:-1:2], np.arange(hubs - 1)]).astype(np.int32)
+    dst = np.concatenate([np.tile(ids, hubs), ids[1::2], np.arange(1, hubs)]).astype(np.int32)
+    _check(gpu, hubs + leaves, src, dst, 1 << 18, True)
