@@ -12,10 +12,10 @@
 //      common members of N+(u) and N+(v).  Only the third edge of a wedge
 //      needs a test (section 4.2).  N+(u) is first sorted into rank order,
 //      so that only its members ranked above v can close (u, v); the test
-//      streams that part of N+(u), or N+(v), whichever is shorter, through an
-//      LDS hash set of the other list: pairs of the first kind are grouped by
-//      v (N+(v) staged once, the parts of its light in-neighbours' lists
-//      streamed), the others by u;
+//      streams that part of N+(u), or N+(v), whichever is shorter, through a
+//      set of the other list in LDS (a hash table, or a bitmap of hub numbers):
+//      pairs of the first kind are grouped by v (N+(v) staged once, the parts
+//      of its light in-neighbours' lists streamed), the others by u;
 //   4. heavy phase: the < 2 m^(1/2) / c heavy vertices, in rank order, form a
 //      strictly upper-triangular 0/1 matrix U; sum((U U) .* U) counts each
 //      all-heavy triangle once (the matrix-multiplication route of Alon,

@@ -90,13 +90,40 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
     return z;
 }
 
+// mix64's first step, linear over xor: fold(a ^ b) = fold(a) ^ fold(b)
+__device__ __forceinline__ uint64_t mix_fold(uint64_t z) { return z ^ (z >> 30); }
+
+// (mix64(x) >> 11) < thr for z = mix_fold(x) and thr <= 2^53.  The top 31 bits
+// of mix64 are those of its last product, whose high word takes three of the
+// four partial products: they decide (*below) unless they equal thr's (true is
+// returned, and folded_below_exact decides).
+__device__ __forceinline__ bool folded_top(uint64_t z, uint64_t thr, bool* below) {
+    z *= 0xBF58476D1CE4E5B9ull;
+    z ^= z >> 27;
+    const uint32_t lo = (uint32_t)z, hi = (uint32_t)(z >> 32);
+    const uint32_t top = (__umulhi(lo, 0x133111EBu) + lo * 0x94D049BBu + hi * 0x133111EBu) >> 1;
+    *below = top < (uint32_t)(thr >> 22);
+    return top == (uint32_t)(thr >> 22);
+}
+
+__device__ __forceinline__ bool folded_below_exact(uint64_t z, uint64_t thr) {
+    z *= 0xBF58476D1CE4E5B9ull;
+    z ^= z >> 27;
+    z *= 0x94D049BB133111EBull;
+    return ((z ^ (z >> 31)) >> 11) < thr;
+}
+
+// The seed-independent part of the coin of edge {u,v}, a hash of (min, max).
+__device__ __forceinline__ uint64_t edge_mix(uint32_t u, uint32_t v) {
+    const uint64_t lo = u < v ? u : v;
+    const uint64_t hi = u < v ? v : u;
+    return mix64((lo << 32) | hi);
+}
+
 // Keep decision of the undirected edge {u,v}: section 3.1's independent coin,
 // realised as a hash of (min, max) salted by the seed.
 __device__ __forceinline__ bool edge_kept(uint32_t u, uint32_t v, uint64_t salt, uint64_t thr) {
-    const uint64_t lo = u < v ? u : v;
-    const uint64_t hi = u < v ? v : u;
-    const uint64_t h = mix64(mix64((lo << 32) | hi) ^ salt);
-    return (h >> 11) < thr;
+    return (mix64(edge_mix(u, v) ^ salt) >> 11) < thr;
 }
 
 // (deg, id) rank order

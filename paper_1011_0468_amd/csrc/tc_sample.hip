@@ -196,56 +196,109 @@ __global__ void __launch_bounds__(256) k_move_staged(int64_t E2, const int32_t* 
 
 // Copy k of the replicated entry space holds g's entries at union positions
 // k * 64 NWp + e (e < E2; the rest of its words are never kept), so that no
-// word of keep bits straddles two copies.  One wave per word of g, for every
-// copy: the entries are read once and the seed-independent first mix of each
-// edge's key is computed once (the coin is mix64(mix64(key) ^ salt) >> 11 <
-// thr, section 3.1's coin as the single-sample kernels compute it).
+// word of keep bits straddles two copies.  A block takes kKeepWords words of g,
+// a wave kKeepWords / 4 of them, for every copy: the entries are read once and
+// the seed-independent first mix of each edge's key is computed once (the coin
+// is mix64(mix64(key) ^ salt) >> 11 < thr, section 3.1's coin as the
+// single-sample kernels compute it).  Bound by the six 32-bit multiplications
+// left per coin: 2.1 G coins (2^25 entries, 64 copies) in 1.32 ms are 9.8 T
+// multiplications/s, what a quarter of the lanes' rate gives; with eight of
+// them, a scalar load of the salt and a branch per coin it took 1.40 to 1.49.
+// 64 copies at a time pass through LDS, where each copy's words lie together,
+// so that one store writes a line of the bits.
+constexpr int kKeepWords = 16;
+
 __global__ void __launch_bounds__(256) k_keep_rep(const int32_t* __restrict__ src, const int32_t* __restrict__ col,
                                                    int64_t E2, int64_t NWp, int32_t K,
                                                    const uint64_t* __restrict__ salts, uint64_t thr,
                                                    uint64_t* __restrict__ bits, int32_t* __restrict__ wcnt) {
+    constexpr int PER = kKeepWords / 4;
+    __shared__ uint64_t tile[64][kKeepWords + 1];
     const int lane = __lane_id();
-    const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
-    for (int64_t w = wave; w < NWp; w += nwaves) {
-        const int64_t e = w * 64 + lane;
-        const bool in = e < E2;
-        uint64_t base = 0;
-        if (in) {
-            const uint32_t u = (uint32_t)src[e], v = (uint32_t)col[e];
-            const uint64_t lo = u < v ? u : v, hi = u < v ? v : u;
-            base = mix64((lo << 32) | hi);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t groups = (NWp + kKeepWords - 1) / kKeepWords;
+    for (int64_t gr = blockIdx.x; gr < groups; gr += gridDim.x) {  // block-uniform
+        uint64_t base[PER];
+        uint64_t in[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t e = (gr * kKeepWords + wid * PER + i) * 64 + lane;
+            in[i] = ballot64(e < E2);
+            base[i] = e < E2 ? mix_fold(edge_mix((uint32_t)src[e], (uint32_t)col[e])) : 0;
         }
-        for (int32_t k = 0; k < K; ++k) {
-            const uint64_t b = ballot64(in && (mix64(base ^ salts[k]) >> 11) < thr);
-            if (lane == 0) {
-                bits[(int64_t)k * NWp + w] = b;
-                wcnt[(int64_t)k * NWp + w] = __popcll(b);
+        for (int32_t k0 = 0; k0 < K; k0 += 64) {
+            const int kc = K - k0 < 64 ? K - k0 : 64;
+            const uint64_t mysalt = lane < kc ? mix_fold(salts[k0 + lane]) : 0;
+            uint64_t mine[PER] = {};
+            for (int k = 0; k < kc; ++k) {
+                const uint64_t salt =
+                    ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mysalt >> 32), k) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mysalt, k);
+                bool below[PER], equal = false;
+#pragma unroll
+                for (int i = 0; i < PER; ++i) equal |= folded_top(base[i] ^ salt, thr, &below[i]);
+                if (__builtin_expect(ballot64(equal) != 0, 0)) {
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) below[i] = folded_below_exact(base[i] ^ salt, thr);
+                }
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    const uint64_t b = ballot64(below[i]) & in[i];
+                    mine[i] = lane == k ? b : mine[i];
+                }
             }
+#pragma unroll
+            for (int i = 0; i < PER; ++i) tile[lane][wid * PER + i] = mine[i];
+            __syncthreads();
+            for (int q = threadIdx.x; q < kc * kKeepWords; q += 256) {
+                const int k = q / kKeepWords, i = q % kKeepWords;
+                const int64_t w = gr * kKeepWords + i;
+                if (w < NWp) {
+                    const uint64_t b = tile[k][i];
+                    bits[(int64_t)(k0 + k) * NWp + w] = b;
+                    wcnt[(int64_t)(k0 + k) * NWp + w] = __popcll(b);
+                }
+            }
+            __syncthreads();
         }
     }
 }
 
-// Row offsets and degrees of the union of samples: union vertex k * npad + x
-// is vertex x of copy k (x >= n: isolated padding).
-__global__ void k_rows_rep(const int32_t* __restrict__ row_ptr, int64_t n, int64_t npad, int64_t E2, int64_t NWp,
-                           int32_t K, const uint64_t* __restrict__ bits, const int32_t* __restrict__ wpre,
-                           int32_t* __restrict__ rp_out, int32_t* __restrict__ deg_out) {
-    const int64_t nU = (int64_t)K * npad;
+// Row offsets and degrees of the union of samples in the padded layout: union
+// vertex k * npad + x is vertex x of copy k (x >= n: isolated padding).  Per
+// word of 64 of them, which lie in one copy: the bits and the number of those
+// of degree min_deg and more, and of those of lower degree above 0.  A wave per
+// word, where a row's end is the next lane's start (64 seeds of Chung-Lu 2^20 at
+// p = 0.05: 0.61 -> 0.49 ms against a thread per vertex and a pass of its own for
+// the bits).
+__global__ void __launch_bounds__(256) k_rows_rep(const int32_t* __restrict__ row_ptr, int64_t n, int64_t npad,
+                                                   int64_t E2, int64_t NWp, int32_t K, int min_deg,
+                                                   const uint64_t* __restrict__ bits, const int32_t* __restrict__ wpre,
+                                                   int32_t* __restrict__ rp_out, int32_t* __restrict__ deg_out,
+                                                   uint64_t* __restrict__ nzb, int32_t* __restrict__ nzc,
+                                                   uint64_t* __restrict__ oneb, int32_t* __restrict__ onec) {
+    const int lane = __lane_id();
+    const uint32_t wpc = (uint32_t)(npad / 64), NV = wpc * (uint32_t)K;  // words per copy, in all
     const int64_t E2U = (int64_t)K * NWp * 64;
-    for (int64_t xu = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; xu <= nU; xu += (int64_t)gridDim.x * blockDim.x) {
-        if (xu == nU) {
-            rp_out[nU] = wpre[K * NWp];
-            continue;
-        }
-        const int64_t k = xu / npad;
-        const int64_t x = xu - k * npad;
+    if (blockIdx.x == 0 && threadIdx.x == 0) rp_out[(int64_t)NV * 64] = wpre[K * NWp];
+    for (uint32_t w = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < NV; w += gridDim.x * 4) {
+        const uint32_t k = w / wpc;
+        const int64_t x = (int64_t)(w - k * wpc) * 64 + lane;
         const int64_t base = k * NWp * 64;
-        const int64_t e0 = base + (x < n ? row_ptr[x] : E2);
-        const int64_t e1 = base + (x < n ? row_ptr[x + 1] : E2);
-        const int32_t a = kept_before(e0, E2U, bits, wpre);
+        const int32_t a = kept_before(base + (x < n ? row_ptr[x] : E2), E2U, bits, wpre);
+        int32_t e = __shfl_down(a, 1, 64);
+        if (lane == 63) e = kept_before(base + (x < n ? row_ptr[x + 1] : E2), E2U, bits, wpre);
+        const int32_t d = e - a;
+        const int64_t xu = (int64_t)w * 64 + lane;
         rp_out[xu] = a;
-        deg_out[xu] = kept_before(e1, E2U, bits, wpre) - a;
+        deg_out[xu] = d;
+        const uint64_t b = ballot64(d >= min_deg), o = ballot64(d > 0 && d < min_deg);
+        if (lane == 0) {
+            nzb[w] = b;
+            nzc[w] = __popcll(b);
+            oneb[w] = o;
+            onec[w] = __popcll(o);
+        }
     }
 }
 
@@ -396,28 +449,6 @@ __global__ void __launch_bounds__(256) k_keep_comp(const int32_t* __restrict__ s
 // off'[k] + nz[k] - 1 in their old order, and off'[k + 1] = off'[k] + nz[k] + 1
 // rounded up to kUnionAlign, so that every component has an unused id.  64
 // seeds of Chung-Lu 2^20 at p = 0.05: 9.5 -> 7.4 ms without the vertices of degree 1.
-
-// one bit per union vertex (degree >= min_deg), one per dropped vertex of
-// degree 1, and the counts of both per word
-__global__ void __launch_bounds__(256) k_nz_bits(int64_t nU, int min_deg, const int32_t* __restrict__ deg,
-                                                  uint64_t* __restrict__ nzb, int32_t* __restrict__ nzc,
-                                                  uint64_t* __restrict__ oneb, int32_t* __restrict__ onec) {
-    const int lane = __lane_id();
-    const int64_t nw = (nU + 63) / 64;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
-    for (int64_t w = wave; w < nw; w += nwaves) {
-        const int64_t x = w * 64 + lane;
-        const int32_t d = x < nU ? deg[x] : 0;
-        const uint64_t b = ballot64(d >= min_deg), o = ballot64(d > 0 && d < min_deg);
-        if (lane == 0) {
-            nzb[w] = b;
-            nzc[w] = __popcll(b);
-            oneb[w] = o;
-            onec[w] = __popcll(o);
-        }
-    }
-}
 
 // new component offsets off2[k] (off2[K] = new n) and unused ids spare[k] (one
 // thread; K is small); mk[k] = edges of component k in the padded layout
@@ -598,21 +629,20 @@ int64_t sample_union_replicas(const tc_graph_s* g, int32_t K, const uint64_t* sa
                   (const int32_t*)out->row_ptr, mk);
         return 0;
     }
-    // 1. keep bits of every copy, their scan, the union's rows in the padded layout
+    // 1. keep bits of every copy and their scan
     DevBuf<uint64_t> bits(NW, s);
     DevBuf<int32_t> wpre(NW + 1, s);
-    TC_LAUNCH("keep_rep", k_keep_rep, dim3(grid_for(NWp, 4)), dim3(256), 0, s, (const int32_t*)g->src,
+    TC_LAUNCH("keep_rep", k_keep_rep, dim3(grid_for(ceil_div(NWp, kKeepWords), 1)), dim3(256), 0, s, (const int32_t*)g->src,
               (const int32_t*)g->col, E2, NWp, K, salts, thr, bits.get(), wpre.get());
     scan_exclusive_i32(wpre.get(), wpre.get(), NW, s);
     DevBuf<int32_t> rp(nU + 1, s), deg(nU, s);
-    TC_LAUNCH("rows_rep", k_rows_rep, dim3(grid_for(nU + 1, 256)), dim3(256), 0, s, (const int32_t*)g->row_ptr, n, npad,
-              E2, NWp, K, (const uint64_t*)bits.get(), (const int32_t*)wpre.get(), rp.get(), deg.get());
-    // 2. the vertices that are kept and the components' new offsets
+    // 2. rows in the padded layout, the vertices that are kept and the components' new offsets
     const int64_t NV = nU / 64;  // nU is a multiple of kUnionAlign
     DevBuf<uint64_t> nzb(NV, s), oneb(NV, s);
     DevBuf<int32_t> nzpre(NV + 1, s), onepre(NV + 1, s), spare(K, s);
-    TC_LAUNCH("nz_bits", k_nz_bits, dim3(grid_for(NV, 4)), dim3(256), 0, s, nU, min_deg, (const int32_t*)deg.get(),
-              nzb.get(), nzpre.get(), oneb.get(), onepre.get());
+    TC_LAUNCH("rows_rep", k_rows_rep, dim3(grid_for(NV, 4)), dim3(256), 0, s, (const int32_t*)g->row_ptr, n, npad, E2,
+              NWp, K, min_deg, (const uint64_t*)bits.get(), (const int32_t*)wpre.get(), rp.get(), deg.get(), nzb.get(),
+              nzpre.get(), oneb.get(), onepre.get());
     int32_t* const both[2] = {nzpre.get(), onepre.get()};
     scan_exclusive_i32_each(both, 2, NV, s);
     TC_LAUNCH("nz_offsets", k_nz_offsets, dim3(1), dim3(64), 0, s, K, npad, (const int32_t*)nzpre.get(),
