@@ -506,6 +506,11 @@ k_csr_sort(K* __restrict__ keys, const int32_t* __restrict__ start, const int32_
                     const int sub = sub_of(key[i]);
                     const int32_t a = cnt[sub], e = cnt[sub + 1];
                     int32_t r = a;  // equal keys keep their order of arrival
+                    // a small multigraph's hub window holds long runs of equal keys:
+                    // four reads in flight (10,007 vertices, 160,000 R-MAT pairs: 54 ->
+                    // 46 us); with 8 items the sub-windows are 3 keys on average
+                    constexpr int U = I == 16 ? 4 : 1;
+#pragma unroll U
                     for (int32_t j = a; j < e; ++j) {
                         const K x = s[j];
                         r += x < key[i] || (x == key[i] && j < at[i]) ? 1 : 0;
