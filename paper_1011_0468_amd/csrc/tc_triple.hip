@@ -63,41 +63,54 @@ __global__ void __launch_bounds__(256) k_tri_counts(int64_t n, const int32_t* __
 }
 
 // extension-kind lists, one block per list: EP[e] = sum of deg(N(u)[i]) over
-// the entries i before e in u's list, and cnt[u] = the whole sum.  A list is a
-// serial chain of prefix sums, and the longest holds 10^5 entries: 8192 of
-// them per round, their gathers all in flight (64 per round, a wave per
-// list, took 2.4 ms on R-MAT s22 where this takes 0.5).
+// the entries i before e in u's list, and cnt[u] = the whole sum (the vertices
+// of a list are distinct: at most 2m, which fits 32 bits as the row offsets
+// do).  A list is a serial chain of prefix sums, and the longest holds 10^5
+// entries: 8192 of them per round, their gathers all in flight (64 per round, a
+// wave per list, took 2.4 ms on R-MAT s22).  A wave takes rows of 64
+// consecutive entries, so that a line is read and written by one access: 0.29
+// ms, where 8 consecutive entries per thread and 64-bit sums took 0.51.
 constexpr int kExtThreads = 1024, kExtItems = 8;
 __global__ void __launch_bounds__(kExtThreads) k_tri_ext(const int32_t* __restrict__ list,
                                                           const int32_t* __restrict__ listed,
                                                           const int32_t* __restrict__ rp,
                                                           const int32_t* __restrict__ col,
                                                           const int32_t* __restrict__ deg, int64_t* __restrict__ cnt,
-                                                          int64_t* __restrict__ EP) {
-    __shared__ int64_t tmp[kExtThreads / 64 + 1];
+                                                          int32_t* __restrict__ EP) {
+    constexpr int NW = kExtThreads / 64;
+    __shared__ int32_t tmp[2][NW];
+    const int lane = __lane_id(), w = threadIdx.x >> 6;
     const int32_t lists = listed[0];
+    int buf = 0;  // a round's sums are read while the next round's are written
     for (int32_t i = blockIdx.x; i < lists; i += gridDim.x) {  // block-uniform
         const int32_t u = list[i];
         const int32_t rs = rp[u], re = rp[u + 1];
-        int64_t carry = 0;
+        int32_t carry = 0;
         for (int64_t e0 = rs; e0 < re; e0 += kExtThreads * kExtItems) {
-            const int64_t e = e0 + (int64_t)threadIdx.x * kExtItems;
-            int32_t v[kExtItems];
-            int64_t sum = 0;
+            const int64_t e = e0 + (int64_t)w * 64 * kExtItems + lane;
+            int32_t v[kExtItems], pre[kExtItems], sum = 0;
 #pragma unroll
-            for (int k = 0; k < kExtItems; ++k) v[k] = e + k < re ? col[e + k] : -1;
+            for (int k = 0; k < kExtItems; ++k) v[k] = e + 64 * k < re ? col[e + 64 * k] : -1;
 #pragma unroll
             for (int k = 0; k < kExtItems; ++k) v[k] = v[k] >= 0 ? deg[v[k]] : 0;
 #pragma unroll
-            for (int k = 0; k < kExtItems; ++k) sum += v[k];
-            int64_t total;
-            int64_t pre = carry + block_exclusive_sum<kExtThreads>(sum, tmp, &total);
-#pragma unroll
             for (int k = 0; k < kExtItems; ++k) {
-                if (e + k < re) EP[e + k] = pre;
-                pre += v[k];
+                const int32_t inc = wave_inclusive_sum(v[k]);
+                pre[k] = sum + inc - v[k];
+                sum += __builtin_amdgcn_readlane(inc, 63);
             }
+            if (lane == 0) tmp[buf][w] = sum;
+            __syncthreads();
+            int32_t before = 0, total = 0;
+            for (int q = 0; q < NW; ++q) {
+                before += q < w ? tmp[buf][q] : 0;
+                total += tmp[buf][q];
+            }
+#pragma unroll
+            for (int k = 0; k < kExtItems; ++k)
+                if (e + 64 * k < re) EP[e + 64 * k] = carry + before + pre[k];
             carry += total;
+            buf ^= 1;
         }
         if (threadIdx.x == 0) cnt[u] = carry;
     }
@@ -149,7 +162,7 @@ void scan64(const int64_t* in, int64_t* out, int64_t N, hipStream_t s) {
 namespace {
 
 // the largest entry e of [lo, hi] with EP[e] <= k (EP[lo] <= k)
-__device__ __forceinline__ int32_t last_entry(const int64_t* __restrict__ EP, int32_t lo, int32_t hi, int64_t k) {
+__device__ __forceinline__ int32_t last_entry(const int32_t* __restrict__ EP, int32_t lo, int32_t hi, int64_t k) {
     while (lo < hi) {
         const int32_t mid = lo + ((hi - lo + 1) >> 1);
         if (EP[mid] <= k) lo = mid;
@@ -164,7 +177,7 @@ __device__ __forceinline__ int32_t last_entry(const int64_t* __restrict__ EP, in
 // entries apart instead of a list of 36000 on R-MAT s22 (2^25 samples:
 // 4.00 -> 3.70 ms, and 0.07 for the index).
 __global__ void __launch_bounds__(256) k_tri_ext_index(PrefixIndex<int64_t> P, const int32_t* __restrict__ rp,
-                                                        const int64_t* __restrict__ EP, int64_t m,
+                                                        const int32_t* __restrict__ EP, int64_t m,
                                                         int32_t* __restrict__ eidx) {
     const uint64_t total = (uint64_t)P.pre[P.n];
     if (total == 0) return;
@@ -187,7 +200,7 @@ __global__ void __launch_bounds__(256) k_tri_ext_index(PrefixIndex<int64_t> P, c
 __global__ void __launch_bounds__(256, 8) k_tri_sample(int64_t i0, int64_t s, const int32_t* __restrict__ order,
                                                      uint64_t salt, PrefixIndex<int64_t> P,
                                                      const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                     const int64_t* __restrict__ EP, const int32_t* __restrict__ eidx,
+                                                     const int32_t* __restrict__ EP, const int32_t* __restrict__ eidx,
                                                      int64_t m, int hybrid, unsigned long long* __restrict__ acc) {
     const int64_t* CU = P.pre;
     const int64_t size = CU[P.n];
@@ -254,8 +267,8 @@ void triple_sample(const tc_graph_s* g, int hybrid, int64_t num_samples, uint64_
     if (n == 0) return;
     // a search of few vertices is short by itself, and its index a launch more
     const int kb = n >= kIndexVertices ? index_bits(n) : 0;
-    DevBuf<int64_t> cnt(n + 1, s), CU(n + 1, s), EP(hybrid ? 2 * m : 0, s);
-    DevBuf<int32_t> idx((size_t)1 << kb, s), list(hybrid ? n : 0, s);
+    DevBuf<int64_t> cnt(n + 1, s), CU(n + 1, s);
+    DevBuf<int32_t> EP(hybrid ? 2 * m : 0, s), idx((size_t)1 << kb, s), list(hybrid ? n : 0, s);
     DevBuf<unsigned long long> acc(kAccLines * kAccStride + 1, s);  // the sums, then the length of list
     fill_i64(reinterpret_cast<int64_t*>(acc.get()), 0, kAccLines * kAccStride + 1, s);
     int32_t* listed = reinterpret_cast<int32_t*>(acc.get() + kAccLines * kAccStride);
@@ -276,7 +289,7 @@ void triple_sample(const tc_graph_s* g, int hybrid, int64_t num_samples, uint64_
     DevBuf<int32_t> eidx(ext_index ? (size_t)1 << kb : 0, s);
     if (ext_index)
         TC_LAUNCH("tri_index", k_tri_ext_index, dim3(ceil_div((int64_t)1 << kb, 256)), dim3(256), 0, s, P,
-                  (const int32_t*)g->row_ptr, (const int64_t*)EP.get(), m, eidx.get());
+                  (const int32_t*)g->row_ptr, (const int32_t*)EP.get(), m, eidx.get());
     const uint64_t salt = host_mix64(seed ^ 0x54435F545249504CULL);  // "TC_TRIPL"
     const bool part = samples_partitioned(num_samples, m);
     const int64_t chunk = part ? std::min(num_samples, kPartChunk) : num_samples;
@@ -287,7 +300,7 @@ void triple_sample(const tc_graph_s* g, int hybrid, int64_t num_samples, uint64_
         const int64_t sg = ceil_div(c, 8 * kDrawsPerBlock) * 8;  // a multiple of the XCDs
         TC_LAUNCH("tri_sample", k_tri_sample, dim3((unsigned)sg), dim3(256), 0, s, i0, c,
                   part ? (const int32_t*)order.get() : (const int32_t*)nullptr, salt, P, (const int32_t*)g->row_ptr,
-                  (const int32_t*)g->col, (const int64_t*)EP.get(), ext_index ? (const int32_t*)eidx.get() : nullptr,
+                  (const int32_t*)g->col, (const int32_t*)EP.get(), ext_index ? (const int32_t*)eidx.get() : nullptr,
                   m, hybrid, acc.get());
     }
     std::vector<int64_t> h(1 + kAccLines * kAccStride);
