@@ -6,6 +6,8 @@
 #include "tc_internal.h"
 #include "tc_device.h"
 
+#include <algorithm>
+
 namespace tc {
 
 namespace {
@@ -232,6 +234,13 @@ constexpr int kAccLines = 64, kAccStride = 16;
 // share when the others end (R-MAT s22, against 2048 blocks striding through
 // all: 2^25 triples 5.5 -> 4.3 ms, 2^24 draws of the stream 2.0 -> 1.6).
 constexpr int64_t kDrawsPerBlock = 256;
+
+// Blocks for c >= 1 samples, a multiple of the XCDs; past 2^28 samples their
+// shares grow (a grid holds fewer than 2^32 threads).
+inline unsigned draw_blocks(int64_t c) {
+    const int64_t per_xcd = (c - 1) / (8 * kDrawsPerBlock) + 1;
+    return 8 * (unsigned)std::min<int64_t>(per_xcd, (int64_t)1 << 17);
+}
 
 // Samples partitioned together, and the calls whose samples are.  Triples: R-MAT
 // s22 with 2^25 samples took 16.3 -> 6.4 ms; from 2^21 samples it is 1.0 to 1.1

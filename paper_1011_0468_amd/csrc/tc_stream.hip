@@ -265,8 +265,8 @@ void stream_estimate(const tc_graph_s* g, double d, int64_t s, uint64_t seed, hi
     for (int64_t i0 = 0; i0 < s; i0 += chunk) {
         const int64_t c = std::min(chunk, s - i0);
         if (part) partition_samples(i0, c, salt2, parts, at.get(), order.get(), st);
-        const int64_t sg = ceil_div(c, 8 * kDrawsPerBlock) * 8;  // a multiple of the XCDs
-        TC_LAUNCH("stream_draws", k_stream_draws, dim3((unsigned)sg), dim3(256), 0, st, i0, c,
+        const unsigned sg = draw_blocks(c);
+        TC_LAUNCH("stream_draws", k_stream_draws, dim3(sg), dim3(256), 0, st, i0, c,
                   part ? (const int32_t*)order.get() : (const int32_t*)nullptr, (const int32_t*)at.get(), parts,
                   salt2, m, (const int32_t*)g->row_ptr, (const int32_t*)g->col, up, light,
                   (const int32_t*)hlist.get(), acc.get());

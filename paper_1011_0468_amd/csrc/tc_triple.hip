@@ -297,8 +297,8 @@ void triple_sample(const tc_graph_s* g, int hybrid, int64_t num_samples, uint64_
     for (int64_t i0 = 0; i0 < num_samples; i0 += chunk) {
         const int64_t c = std::min(chunk, num_samples - i0);
         if (part) partition_samples(i0, c, salt, HashParts{}, at.get(), order.get(), s);
-        const int64_t sg = ceil_div(c, 8 * kDrawsPerBlock) * 8;  // a multiple of the XCDs
-        TC_LAUNCH("tri_sample", k_tri_sample, dim3((unsigned)sg), dim3(256), 0, s, i0, c,
+        const unsigned sg = draw_blocks(c);
+        TC_LAUNCH("tri_sample", k_tri_sample, dim3(sg), dim3(256), 0, s, i0, c,
                   part ? (const int32_t*)order.get() : (const int32_t*)nullptr, salt, P, (const int32_t*)g->row_ptr,
                   (const int32_t*)g->col, (const int32_t*)EP.get(), ext_index ? (const int32_t*)eidx.get() : nullptr,
                   m, hybrid, acc.get());

@@ -6,6 +6,7 @@ import pytest
 
 import oracle
 import synth
+from synth import special
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +61,13 @@ def test_extension_index_of_few_long_lists(gpu, leaves, hubs):
     src = np.concatenate([np.repeat(np.arange(hubs), leaves), ids[:-1:2], np.arange(hubs - 1)]).astype(np.int32)
     dst = np.concatenate([np.tile(ids, hubs), ids[1::2], np.arange(1, hubs)]).astype(np.int32)
     _check(gpu, hubs + leaves, src, dst, 1 << 18, True)
+
+
+def test_more_samples_than_a_grid_holds_threads(gpu):
+    # every wedge of K_n is closed, so the estimate is exact for any samples
+    n, src, dst = special.complete(40)
+    samples = (1 << 32) + 5
+    print("triples", n, samples, flush=True)
+    r = gpu.tc_triple_estimate(gpu.tc_build_csr(n, src, dst), 1.0, samples, hybrid=False)
+    assert (r["closed"], r["weight_sum"]) == (samples, 20 * samples)
+    assert r["estimate"] == 40 * 39 * 38 / 6
