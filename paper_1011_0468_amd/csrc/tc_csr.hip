@@ -587,9 +587,10 @@ __global__ void __launch_bounds__(256) k_big_hist(const K* __restrict__ keys, co
     const int32_t ti = blockIdx.x - g.tile0, T = tiles_of(g.len, kTile);
     cnt[t] = 0;
     __syncthreads();
-    const int32_t j0 = ti * kTile, j1 = j0 + min(kTile, g.len - j0);
-    for (int32_t j = j0 + t; j < j1; j += 256)
-        atomicAdd(&cnt[(uint32_t)(keys[g.start + j] >> shift) & ((1u << bits) - 1)], 1);
+    // places in the tile, not in the window: those of a window of nearly 2^31 keys leave int32 with the last step
+    const int32_t j0 = ti * kTile, count = min(kTile, g.len - j0);
+    for (int32_t j = t; j < count; j += 256)
+        atomicAdd(&cnt[(uint32_t)(keys[g.start + j0 + j] >> shift) & ((1u << bits) - 1)], 1);
     __syncthreads();
     hist[(int64_t)g.tile0 * kRadix + (int64_t)t * T + ti] = cnt[t];
 }
@@ -648,8 +649,8 @@ __global__ void __launch_bounds__(256) k_big_count(const K* __restrict__ keys, c
     const int64_t row0 = (int64_t)g.bin << row_bits;
     int32_t mine = 0, cur = -1, held = 0;  // the row being counted (wave-uniform) and its keys so far
     for (int32_t i = w * per; i < min(count, (w + 1) * per); i += 64) {
-        const int32_t j = j0 + i + lane;
         const bool in = i + lane < count;
+        const int32_t j = in ? j0 + i + lane : 0;
         const K k = in ? keys[g.start + j] : (K)0;
         const bool f = in && (j == 0 || keys[g.start + j - 1] != k);
         const int32_t r = in ? (int32_t)(k >> nb) : -1;
