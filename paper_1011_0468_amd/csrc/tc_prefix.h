@@ -131,13 +131,15 @@ __global__ void __launch_bounds__(256) k_bucket_index(int64_t n, const T* __rest
 // past one line are entered where y would be if their ids were spread evenly
 // (as relabelled graphs' are: off by about the root of the length) and the
 // range is widened from there by doubling: 2^25 triples on R-MAT s22 took 6.6 ->
-// 5.5 ms, and it is at most twice the steps on any list.
-__device__ __forceinline__ bool in_list(const int32_t* __restrict__ col, int32_t lo, int32_t end, int32_t y,
-                                        float scale) {
+// 5.5 ms, and it is at most twice the steps on any list.  Ids: a pointer, or
+// what stands for a list in a check on the host.
+template <typename Ids>
+__host__ __device__ __forceinline__ bool in_list(Ids col, int32_t lo, int32_t end, int32_t y, float scale) {
     int32_t hi = end;
     if (end - lo > 32) {
-        int32_t g = lo + (int32_t)((float)(end - lo) * ((float)y * scale));
-        g = g < end - 1 ? g : end - 1;  // >= lo
+        // the length rounds up past 2^24: held below it before lo, near 2^31 in the largest graphs, is added
+        const int32_t at = (int32_t)((float)(end - lo) * ((float)y * scale));
+        const int32_t g = lo + (at < end - lo - 1 ? at : end - lo - 1);
         int32_t step = 16;
         if (col[g] < y) {
             lo = g + 1;
