@@ -387,12 +387,17 @@ __device__ __forceinline__ void radix_ranks(const K (&key)[I], int32_t (&rk)[I],
 // neighbours'.  Every key then counts the smaller keys of its sub-window: a
 // few LDS reads, where radix passes over all 29 bits took four passes of
 // ranking by ballots (R-MAT s22: 2.97 ms for the windows, this 1.0).  The
-// count is quadratic in a sub-window: past kSubMax keys in one, where a row's
-// neighbours are bunched, the radix passes are the shorter way.  The count's
-// kernel (a block per window) leaves such a window as it is and lists it, and
-// the RADIX kernel's persistent blocks take the list.
+// count is quadratic in a sub-window: past kSubPerPass keys in one for each
+// pass that the radix would take, where a row's neighbours are bunched, the
+// radix passes are the shorter way.  The count's kernel (a block per window)
+// leaves such a window as it is and lists it, and the RADIX kernel's persistent
+// blocks take the list.  Complete bipartite 2000 x 20000 and 1000 x 30000, 15
+// rest bits, sub-windows of 64 and 128 keys: builds of 4.7 and 3.2 ms with
+// 128 allowed whatever the passes, 2.6 and 2.5 with 24 a pass; 2^20 vertices with
+// 16 pairs each among the next 40, 25 bits: 1.9 ms with 16 allowed in all, 1.3
+// with 16 to 28 a pass.
 constexpr int kGroupBits = 8;
-constexpr int32_t kSubMax = 128;
+constexpr int32_t kSubPerPass = 24;
 // counters: half the keys, one more per group, as whole rounds of 1024
 constexpr int sub_windows(int items) { return items * 512 + 1024; }
 
@@ -489,7 +494,7 @@ k_csr_sort(K* __restrict__ keys, const int32_t* __restrict__ start, const int32_
             __syncthreads();
             int32_t top = most[0];
             for (int i = 1; i < NW; ++i) top = max(top, most[i]);
-            if (top > kSubMax) {  // block-uniform
+            if (top > kSubPerPass * ((rest + kDigit - 1) / kDigit)) {  // block-uniform
                 if (t == 0) list[atomicAdd(listed, 1)] = bin;
                 return;
             }
