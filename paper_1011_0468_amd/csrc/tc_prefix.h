@@ -94,15 +94,37 @@ __device__ __forceinline__ int64_t find_item(const PrefixIndex<T>& P, int64_t r)
 // idx of a prefix: every bucket start lies in exactly one non-empty range, and
 // the item of that range writes it.  Items with at most 8 buckets write their
 // own; the wave writes those of longer ranges together, one item at a time.
+// The range of a hub can hold nearly all of the buckets: groups of kIndexGroup
+// buckets that lie in one range are left to the first `gblocks` blocks, a thread
+// per group, which searches its item (one wave for all 2^20 buckets of a star of
+// 2^20 vertices took 500 us).
+constexpr int64_t kIndexGroup = 256;
+
 template <typename T>
-__global__ void __launch_bounds__(256) k_bucket_index(int64_t n, const T* __restrict__ pre, int k,
+__global__ void __launch_bounds__(256) k_bucket_index(int64_t n, const T* __restrict__ pre, int k, int gblocks,
                                                       int32_t* __restrict__ idx) {
     const uint64_t total = (uint64_t)pre[n];
     if (total == 0) return;
     const Buckets bs(total, k);
     const int lane = __lane_id();
-    const int64_t step = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t u0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); u0 < n; u0 += step) {
+    if ((int)blockIdx.x < gblocks) {  // block-uniform
+        const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x, groups = ((int64_t)1 << k) / kIndexGroup;
+        int64_t u = 0;
+        bool whole = false;
+        if (g < groups) {
+            u = find_item(PrefixIndex<T>{pre, nullptr, n, k}, (int64_t)bs.start((uint64_t)(g * kIndexGroup)));
+            whole = bs.start((uint64_t)(g * kIndexGroup + kIndexGroup - 1)) < (uint64_t)pre[u + 1];
+        }
+        for (uint64_t rest = ballot64(whole); rest; rest &= rest - 1) {
+            const int src = __builtin_ctzll(rest);
+            const int64_t b0 = (g - lane + src) * kIndexGroup;
+            const int32_t v = __shfl((int32_t)u, src, 64);
+            for (int64_t b = b0 + lane; b < b0 + kIndexGroup; b += 64) idx[b] = v;
+        }
+        return;
+    }
+    const int64_t step = (int64_t)(gridDim.x - gblocks) * blockDim.x;
+    for (int64_t u0 = (int64_t)(blockIdx.x - gblocks) * blockDim.x + (threadIdx.x & ~63); u0 < n; u0 += step) {
         // u0 is the wave's first item (wave-uniform), u this lane's
         const int64_t u = u0 + lane;
         int64_t b0 = 0, b1 = 0;
@@ -121,9 +143,21 @@ __global__ void __launch_bounds__(256) k_bucket_index(int64_t n, const T* __rest
             const int src = __ffsll((long long)longs) - 1;
             longs &= longs - 1;
             const int64_t lb0 = __shfl(b0, src, 64), lb1 = __shfl(b1, src, 64);
-            for (int64_t b = lb0 + lane; b < lb1; b += 64) idx[b] = (int32_t)(u0 + src);
+            int64_t g0 = (lb0 + kIndexGroup - 1) / kIndexGroup * kIndexGroup, g1 = lb1 / kIndexGroup * kIndexGroup;
+            if (!gblocks || g0 >= g1) g0 = g1 = lb1;  // [g0, g1): whole groups, written above
+            for (int64_t b = lb0 + lane; b < g0; b += 64) idx[b] = (int32_t)(u0 + src);
+            for (int64_t b = g1 + lane; b < lb1; b += 64) idx[b] = (int32_t)(u0 + src);
         }
     }
+}
+
+// The index idx of the prefix pre of n items, 2^k buckets (k >= 10).  Below 2^16
+// buckets one wave writes the longest range in the time of a group's search.
+template <typename T>
+inline void bucket_index(const char* name, int64_t n, const T* pre, int k, int32_t* idx, hipStream_t s) {
+    const int gblocks = k >= 16 ? (int)(((int64_t)1 << k) / kIndexGroup / 256) : 0;
+    const unsigned items = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 65536));
+    TC_LAUNCH(name, k_bucket_index<T>, dim3(gblocks + items), dim3(256), 0, s, n, pre, k, gblocks, idx);
 }
 
 // y in the sorted list col[lo .. end) of ids below n (scale = 1 / n).  Every

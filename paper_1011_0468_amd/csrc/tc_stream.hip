@@ -231,8 +231,7 @@ void stream_estimate(const tc_graph_s* g, double d, int64_t s, uint64_t seed, hi
     const int k = index_bits(n);
     const int64_t B = (int64_t)1 << k;
     DevBuf<int32_t> up_idx(B, st), light_idx(B, st);
-    TC_LAUNCH("stream_index", k_bucket_index<int32_t>, dim3(grid(n)), dim3(256), 0, st, n,
-              (const int32_t*)upre.get(), k, up_idx.get());
+    bucket_index("stream_index", n, (const int32_t*)upre.get(), k, up_idx.get(), st);
     const PrefixIndex<int32_t> up{upre.get(), up_idx.get(), n, k};
     // pass 1
     DevBuf<uint8_t> cand(n, st);
@@ -253,8 +252,7 @@ void stream_estimate(const tc_graph_s* g, double d, int64_t s, uint64_t seed, hi
     DevBuf<int32_t> hlist(n, st);
     TC_LAUNCH("stream_hlist", k_stream_hlist, dim3(grid(n)), dim3(256), 0, st, n, (const int32_t*)hf.get(),
               (const int32_t*)hpos.get(), hlist.get());
-    TC_LAUNCH("stream_index", k_bucket_index<int64_t>, dim3(grid(n)), dim3(256), 0, st, n,
-              (const int64_t*)lpre.get(), k, light_idx.get());
+    bucket_index("stream_index", n, (const int64_t*)lpre.get(), k, light_idx.get(), st);
     const PrefixIndex<int64_t> light{lpre.get(), light_idx.get(), n, k};
     // passes 2 and 3
     const uint64_t salt2 = host_mix(seed ^ 0x54435F5354524D32ULL);  // "TC_STRM2"

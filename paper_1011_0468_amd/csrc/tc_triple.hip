@@ -256,7 +256,12 @@ __global__ void __launch_bounds__(256, 8) k_tri_sample(int64_t i0, int64_t s, co
     add_to_lines(wsum, closed, acc);
 }
 
+// Vertices from which, and vertices a sample up to which, the prefix gets an index,
+// which costs a pass over the vertices.  Without and with it, uniform graphs: 2^22
+// vertices with 10^4 samples 137 and 180 us, with 2^20 472 and 386; 2^23 with 2^20
+// 527 and 465; R-MAT s24 with 2^20, simple, 697 and 825.
 constexpr int64_t kIndexVertices = (int64_t)1 << 16;
+constexpr int64_t kIndexVerticesPerSample = 8;
 
 }  // namespace
 
@@ -266,9 +271,14 @@ void triple_sample(const tc_graph_s* g, int hybrid, int64_t num_samples, uint64_
     *size = *wsum = *closed = 0;
     if (n == 0) return;
     // a search of few vertices is short by itself, and its index a launch more
-    const int kb = n >= kIndexVertices ? index_bits(n) : 0;
+    const int kb = n >= kIndexVertices && num_samples >= n / kIndexVerticesPerSample ? index_bits(n) : 0;
     DevBuf<int64_t> cnt(n + 1, s), CU(n + 1, s);
-    DevBuf<int32_t> EP(hybrid ? 2 * m : 0, s), idx((size_t)1 << kb, s), list(hybrid ? n : 0, s);
+    DevBuf<int32_t> EP, list, idx, eidx, order, at;  // a call of few samples is also its allocations
+    if (hybrid) {
+        EP.reset(2 * m, s);
+        list.reset(n, s);
+    }
+    if (kb) idx.reset((size_t)1 << kb, s);
     DevBuf<unsigned long long> acc(kAccLines * kAccStride + 1, s);  // the sums, then the length of list
     fill_i64(reinterpret_cast<int64_t*>(acc.get()), 0, kAccLines * kAccStride + 1, s);
     int32_t* listed = reinterpret_cast<int32_t*>(acc.get() + kAccLines * kAccStride);
@@ -280,20 +290,22 @@ void triple_sample(const tc_graph_s* g, int hybrid, int64_t num_samples, uint64_
                   dim3(kExtThreads), 0, s, (const int32_t*)list.get(), (const int32_t*)listed,
                   (const int32_t*)g->row_ptr, (const int32_t*)g->col, (const int32_t*)g->deg, cnt.get(), EP.get());
     scan64(cnt.get(), CU.get(), n, s);
-    if (kb)
-        TC_LAUNCH("tri_index", k_bucket_index<int64_t>, dim3(vg), dim3(256), 0, s, n, (const int64_t*)CU.get(), kb,
-                  idx.get());
+    if (kb) bucket_index("tri_index", n, (const int64_t*)CU.get(), kb, idx.get(), s);
     const PrefixIndex<int64_t> P{CU.get(), kb ? idx.get() : nullptr, n, kb};
     // the lists' index pays for itself from about a sample per bucket
     const bool ext_index = hybrid && kb && num_samples >= (int64_t)1 << kb;
-    DevBuf<int32_t> eidx(ext_index ? (size_t)1 << kb : 0, s);
-    if (ext_index)
+    if (ext_index) {
+        eidx.reset((size_t)1 << kb, s);
         TC_LAUNCH("tri_index", k_tri_ext_index, dim3(ceil_div((int64_t)1 << kb, 256)), dim3(256), 0, s, P,
                   (const int32_t*)g->row_ptr, (const int32_t*)EP.get(), m, eidx.get());
+    }
     const uint64_t salt = host_mix64(seed ^ 0x54435F545249504CULL);  // "TC_TRIPL"
     const bool part = samples_partitioned(num_samples, m);
     const int64_t chunk = part ? std::min(num_samples, kPartChunk) : num_samples;
-    DevBuf<int32_t> order(part ? chunk : 0, s), at(part ? kParts + 1 : 0, s);
+    if (part) {
+        order.reset(chunk, s);
+        at.reset(kParts + 1, s);
+    }
     for (int64_t i0 = 0; i0 < num_samples; i0 += chunk) {
         const int64_t c = std::min(chunk, num_samples - i0);
         if (part) partition_samples(i0, c, salt, HashParts{}, at.get(), order.get(), s);
