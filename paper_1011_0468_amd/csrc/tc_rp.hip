@@ -11,7 +11,7 @@
 //             (per batch of 64 entries: a 64 x 64 bit transpose, then one masked
 //             popcount per lane and run of one row)
 //   rp_dot  : q[b]    = sum over CSR entries (i, j) of Y[i][b] * Y[j][b]
-//                     = 2 * sum over the entries with j > i
+//                     = 2 * sum over one entry of each edge (see k_rp_dot)
 //
 // Both sweeps are edge-parallel: wave w owns CSR entries [w L, (w+1) L), so a
 // hub row is split over many waves.  rp_dot is a plain sum over entries.  In
@@ -22,6 +22,7 @@
 #include "tc_internal.h"
 #include "tc_device.h"
 
+#include <algorithm>
 #include <vector>
 
 namespace tc {
@@ -145,22 +146,18 @@ __global__ void __launch_bounds__(256) k_rp_clear_ends(int64_t E2, const int32_t
     Y[(int64_t)src[e1 - 1] * 64 + lane] = 0;
 }
 
-// The neighbour's degree class of entry e: stored with a graph of
-// tc_build_csr, gathered from the class array (a byte per vertex) otherwise.
-template <bool NCLS>
-__device__ __forceinline__ uint32_t rp_class(const uint8_t* __restrict__ cls, const uint8_t* __restrict__ ncls,
-                                             int64_t e, int32_t j) {
-    return NCLS ? (uint32_t)ncls[e] : (uint32_t)cls[j];
-}
-
 // q[b] = sum over CSR entries (i, j) of Y[i][b] Y[j][b] = 2 * the sum over one
 // entry of each undirected edge (A is symmetric without loops): the one in the
-// row of the end with the smaller (degree class, id).  Bound by the 256-byte
+// row of the end with the smaller (degree class, id) in a graph that stores its
+// entries' neighbour classes (CLASSES), with the smaller id otherwise.  Bound by the 256-byte
 // gathers of Y[j], one per edge: pointing every edge at its end of larger
 // degree sends them to the few rows of the hubs, which the L2s and the
 // Infinity Cache hold, where the order of the ids alone sends half of them to
 // rows that only memory holds.  R-MAT s22 (64 M edges, 16 GB of rows a
-// sweep): 2.40 -> 1.72 ms a sweep with the queue below.
+// sweep): 2.40 -> 1.72 ms a sweep with the queue below.  A sample stores no
+// classes, and gathering them costs more than the order gains (s22 at p = 0.9: by
+// id without and with the queue 2.18 and 1.85 ms, by gathered class 2.44; uniform
+// 2^22: 2.76, 2.43 and 3.54).
 // The entries that count are queued per wave in LDS, so that the gathers run
 // over full batches of 64 without a branch per entry, kRpUnroll in flight.
 // Y below 4 GiB is read with buffer loads, whose scalar offset is the row's
@@ -202,7 +199,7 @@ __device__ __forceinline__ void rp_batch(const int32_t* __restrict__ Y, __amdgpu
     cur = __builtin_amdgcn_readlane(vi, FULL ? 63 : cnt - 1);
 }
 
-template <bool NCLS, bool WIDE>
+template <bool CLASSES, bool WIDE>
 __global__ void __launch_bounds__(256) k_rp_dot(int64_t E2, const int32_t* __restrict__ src,
                                                  const int32_t* __restrict__ col, const uint8_t* __restrict__ cls,
                                                  const uint8_t* __restrict__ ncls, const int32_t* __restrict__ Y,
@@ -226,7 +223,7 @@ __global__ void __launch_bounds__(256) k_rp_dot(int64_t E2, const int32_t* __res
             const bool in = el < e1;
             const int32_t vi = in ? src[el] : 0;
             const int32_t vj = in ? col[el] : 0;
-            const uint32_t ci = in ? cls[vi] : 0u, cj = in ? rp_class<NCLS>(cls, ncls, el, vj) : 0u;
+            const uint32_t ci = CLASSES && in ? cls[vi] : 0u, cj = CLASSES && in ? ncls[el] : 0u;
             const bool up = in && (ci < cj || (ci == cj && vi < vj));
             const uint64_t U = ballot64(up);
             if (up) Q[(head + held + __popcll(U & lanes_below())) & (kRpQueue - 1)] = make_int2(vi, vj);
@@ -256,18 +253,15 @@ __global__ void __launch_bounds__(256) k_rp_dot(int64_t E2, const int32_t* __res
 
 // An upper bound of the sum over CSR entries (i, j) of deg_i * deg_j: deg_j
 // taken as the largest degree of its class (at most 1/8 too large), which is
-// read in order or from a table of a byte per vertex instead of gathered per
-// entry.  One partial per block, summed on the host.
-template <bool NCLS>
+// stored with the entry instead of gathered.  One partial per block, summed on
+// the host.
 __global__ void __launch_bounds__(256) k_rp_class_bound(const int32_t* __restrict__ src,
-                                                         const int32_t* __restrict__ col,
                                                          const int32_t* __restrict__ deg,
-                                                         const uint8_t* __restrict__ cls,
                                                          const uint8_t* __restrict__ ncls, int64_t E2,
                                                          double* __restrict__ part) {
     double s = 0.0;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E2; e += (int64_t)gridDim.x * blockDim.x)
-        s += (double)deg[src[e]] * (double)class_max_degree(rp_class<NCLS>(cls, ncls, e, NCLS ? 0 : col[e]));
+        s += (double)deg[src[e]] * (double)class_max_degree(ncls[e]);
     s = wave_sum(s);
     __shared__ double red[4];
     if (__lane_id() == 0) red[threadIdx.x >> 6] = s;
@@ -300,18 +294,21 @@ void rp_trace(const tc_graph_s* g, int32_t k, uint64_t seed, hipStream_t s, int6
     const int64_t n = g->n, E2 = 2 * g->m;
     for (int32_t l = 0; l < k; ++l) q_host[l] = 0;
     if (n == 0 || E2 == 0) return;
-    DevBuf<uint8_t> cls(n, s);
-    degree_classes(n, g->deg, cls.get(), s);
+    const uint8_t* ncls = g->ncls;
+    DevBuf<uint8_t> cls;
+    if (ncls) {
+        cls.reset(n, s);
+        degree_classes(n, g->deg, cls.get(), s);
+    }
     {
         // |q_l| <= sum over entries (i, j) of |Y_il| |Y_jl| <= sum of deg_i deg_j; every q_l and their sum
         // stay exact while k times that is below 2^62 (margin for the double rounding).  A bound from the
-        // degree classes settles most graphs (R-MAT s22: 0.65 -> 0.25 ms); where it does not, the degrees
-        // themselves decide.
-        unsigned blocks = ceil_div(E2, 256);
-        if (blocks > 2048) blocks = 2048;
-        DevBuf<double> part(blocks, s);
-        std::vector<double> hpart(blocks);
-        auto total = [&] {
+        // stored degree classes settles most built graphs (R-MAT s22: 0.65 -> 0.25 ms); where it does not, and
+        // in samples (gathered classes: 0.59 -> 0.77 ms on s22 at p = 0.9), the degrees themselves decide.
+        constexpr unsigned kClassBlocks = 2048, kBlocks = 1024;
+        DevBuf<double> part(std::min(ceil_div(E2, 256), kClassBlocks), s);
+        auto total = [&](unsigned blocks) {
+            std::vector<double> hpart(blocks);
             check_hip(hipMemcpyAsync(hpart.data(), part.get(), sizeof(double) * blocks, hipMemcpyDeviceToHost, s),
                       "bound");
             check_hip(hipStreamSynchronize(s), "sync");
@@ -320,13 +317,18 @@ void rp_trace(const tc_graph_s* g, int32_t k, uint64_t seed, hipStream_t s, int6
             return t * (double)k;
         };
         const double limit = 4.611686018427387904e18;
-        TC_LAUNCH("rp_bound", g->ncls ? k_rp_class_bound<true> : k_rp_class_bound<false>, dim3(blocks), dim3(256), 0, s,
-                  (const int32_t*)g->src, (const int32_t*)g->col, (const int32_t*)g->deg, (const uint8_t*)cls.get(),
-                  (const uint8_t*)g->ncls, E2, part.get());
-        if (!(total() * (1.0 + 1e-9) < limit)) {
+        bool settled = false;
+        if (ncls) {
+            const unsigned blocks = std::min(ceil_div(E2, 256), kClassBlocks);
+            TC_LAUNCH("rp_bound", k_rp_class_bound, dim3(blocks), dim3(256), 0, s, (const int32_t*)g->src,
+                      (const int32_t*)g->deg, ncls, E2, part.get());
+            settled = total(blocks) * (1.0 + 1e-9) < limit;
+        }
+        if (!settled) {
+            const unsigned blocks = std::min(ceil_div(E2, 256), kBlocks);
             TC_LAUNCH("rp_bound", k_rp_bound, dim3(blocks), dim3(256), 0, s, (const int32_t*)g->src,
                       (const int32_t*)g->col, (const int32_t*)g->deg, E2, part.get());
-            if (2.0 * total() >= limit)
+            if (2.0 * total(blocks) >= limit)
                 fail(TC_ERR_OVERFLOW, "k * sum deg_i deg_j reaches 2^62: q could overflow int64");
         }
     }
@@ -341,15 +343,15 @@ void rp_trace(const tc_graph_s* g, int32_t k, uint64_t seed, hipStream_t s, int6
     const int64_t waves = (E2 + kRpRange - 1) / kRpRange;
     const unsigned wblocks = (unsigned)((waves + 3) / 4);
     const bool wide = n * 256 >= ((int64_t)1 << 32);  // rows past the reach of a buffer load's offset
-    const auto dot = wide ? (g->ncls ? k_rp_dot<true, true> : k_rp_dot<false, true>)
-                          : (g->ncls ? k_rp_dot<true, false> : k_rp_dot<false, false>);
+    const auto dot = wide ? (ncls ? k_rp_dot<true, true> : k_rp_dot<false, true>)
+                          : (ncls ? k_rp_dot<true, false> : k_rp_dot<false, false>);
     for (int32_t c = 0; c < nchunks; ++c) {
         fill_i64(qd.get(), 0, 64, s);
         TC_LAUNCH("rp_clear", k_rp_clear_ends, dim3(wblocks), dim3(256), 0, s, E2, (const int32_t*)g->src, Y.get());
         TC_LAUNCH("rp_spmm", k_rp_spmm, dim3(wblocks), dim3(256), 0, s, E2, (const int32_t*)g->row_ptr,
                   (const int32_t*)g->src, (const int32_t*)g->col, (uint64_t)c, salt, Y.get());
         TC_LAUNCH("rp_dot", dot, dim3(wblocks), dim3(256), 0, s, E2, (const int32_t*)g->src, (const int32_t*)g->col,
-                  (const uint8_t*)cls.get(), (const uint8_t*)g->ncls, (const int32_t*)Y.get(), (uint32_t)(n * 256),
+                  (const uint8_t*)cls.get(), ncls, (const int32_t*)Y.get(), (uint32_t)(n * 256),
                   qd.get());
         int64_t hq[64];
         check_hip(hipMemcpyAsync(hq, qd.get(), sizeof(hq), hipMemcpyDeviceToHost, s), "q");
