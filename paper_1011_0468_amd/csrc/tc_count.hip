@@ -659,6 +659,72 @@ __device__ __forceinline__ void append_rows(uint64_t mask, int64_t x0, int lane,
     if ((mask >> lane) & 1ull) L[base + (int32_t)__popcll(mask & lanes_below())] = (int32_t)(x0 + lane);
 }
 
+// Lists that nothing sorts (heavy vertices', lists of one entry): their entries'
+// hub numbers where hubs are numbered, empty descriptors where v-major pairs are
+// placed by partition.
+__device__ __forceinline__ void plain_entry(int32_t e, const int4* __restrict__ rowQ, const int32_t* __restrict__ colO,
+                                            uint16_t* __restrict__ colH, int2* __restrict__ packU, const int2* packD) {
+    if (colH) colH[e] = (uint16_t)rowQ[colO[e]].w;
+    if (!packD) packU[e] = make_int2(0, 0);
+}
+
+// Two of the lists in mask at a time, two entries of each a lane, so that four
+// chains of gathers are in flight: a dense graph's windows are all such lists
+// (one list at a time and in one chain, the long ones here as well: K_1000 454 us,
+// 184 now).
+__device__ __forceinline__ void plain_lists(uint64_t mask, const int4& q, int lane, const int4* __restrict__ rowQ,
+                                            const int32_t* __restrict__ colO, uint16_t* __restrict__ colH,
+                                            int2* __restrict__ packU, const int2* packD) {
+    while (mask) {  // wave-uniform
+        const int a = __builtin_ctzll(mask);
+        mask &= mask - 1;
+        const int b = mask ? __builtin_ctzll(mask) : a;
+        const int32_t rs[2] = {__builtin_amdgcn_readlane(q.x, a), __builtin_amdgcn_readlane(q.x, b)};
+        const int32_t len[2] = {~__builtin_amdgcn_readlane(q.y, a), mask ? ~__builtin_amdgcn_readlane(q.y, b) : 0};
+        mask &= mask - 1;
+        int32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = (k & 1) * 64 + lane < len[k >> 1] ? colO[rs[k >> 1] + (k & 1) * 64 + lane] : -1;
+        if (colH) {
+            int32_t h[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) h[k] = v[k] >= 0 ? rowQ[v[k]].w : 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (v[k] >= 0) colH[rs[k >> 1] + (k & 1) * 64 + lane] = (uint16_t)h[k];
+        }
+        if (!packD) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (v[k] >= 0) packU[rs[k >> 1] + (k & 1) * 64 + lane] = make_int2(0, 0);
+        }
+    }
+}
+
+// One long list of this kind, by one wave.
+__device__ __forceinline__ void plain_list(int32_t rs, int32_t len, int lane, const int4* __restrict__ rowQ,
+                                           const int32_t* __restrict__ colO, uint16_t* __restrict__ colH,
+                                           int2* __restrict__ packU, const int2* packD) {
+    for (int32_t k0 = 0; k0 < len; k0 += 512) {
+        int32_t v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = k0 + 64 * k + lane < len ? colO[rs + k0 + 64 * k + lane] : -1;
+        if (colH) {
+            int32_t h[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) h[k] = v[k] >= 0 ? rowQ[v[k]].w : 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (v[k] >= 0) colH[rs + k0 + 64 * k + lane] = (uint16_t)h[k];
+        }
+        if (!packD) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (v[k] >= 0) packU[rs + k0 + 64 * k + lane] = make_int2(0, 0);
+        }
+    }
+}
+
 // Anchor work of the light sources with d+ <= 128: each wave takes 64
 // consecutive vertices per step, sorts their lists of up to 64 entries in lane
 // groups of 4 to 64 and those of 65 to 128 entries in two registers per lane,
@@ -670,8 +736,8 @@ __device__ __forceinline__ void append_rows(uint64_t mask, int64_t x0, int lane,
 // has fewer windows than the chip has waves, and one wave's chain through all
 // classes took 23 us of a count of 16384 vertices.  Where
 // hubs are numbered (colH) or v-major pairs are placed later (packD null) it
-// also writes the numbers and the empty descriptors of the other vertices'
-// lists (heavy, or of one entry), which nothing sorts.
+// also has the other vertices' lists (heavy, or of one entry) plain, see
+// plain_lists: up to 128 entries here, the longer ones by k_work_wide.
 __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __restrict__ rowQ,
                                                      int32_t* __restrict__ colO, uint16_t* __restrict__ colH,
                                                      int32_t vcap, int2* __restrict__ packU,
@@ -691,19 +757,10 @@ __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __res
         const int4 q = x < n ? rowQ[x] : make_int4(0, 0, 0, 0);
         const int32_t d = q.y;
         if ((mine & 0x40u) && x < n && !(d >= 2 && d <= 128)) Wu[x] = 0;
-        if ((mine & 0x40u) && (colH || !packD)) {
-            auto other = [&](int32_t e) {  // entry e of such a list
-                if (colH) colH[e] = (uint16_t)rowQ[colO[e]].w;
-                if (!packD) packU[e] = make_int2(0, 0);
-            };
-            if (d == ~1) other(q.x);
-            uint64_t rest = ballot64(d < ~1);
-            while (rest) {
-                const int l = __builtin_ctzll(rest);
-                rest &= rest - 1;
-                const int32_t rs = __builtin_amdgcn_readlane(q.x, l), len = ~__builtin_amdgcn_readlane(q.y, l);
-                for (int32_t k = lane; k < len; k += 64) other(rs + k);
-            }
+        if (colH || !packD) {
+            if ((mine & 0x40u) && d == ~1) plain_entry(q.x, rowQ, colO, colH, packU, packD);
+            const uint64_t deal = split ? 0x1111111111111111ull << wv : ~0ull;
+            plain_lists(ballot64(d < ~1 && ~d <= 128) & deal, q, lane, rowQ, colO, colH, packU, packD);
         }
         const auto lists = [&](int bit, int32_t lo, int32_t hi) {
             return ballot64((mine >> bit & 1u) && d > lo && d <= hi);
@@ -715,9 +772,10 @@ __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __res
         work_groups<64>(lists(4, 32, 64), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
         work_wide_lists<2>(lists(5, 64, 128), q, x0, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
         if (!(mine & 0x40u)) continue;
-        append_rows(ballot64(!one_class && d > 128 && d <= 256), x0, lane, wide + 1);
-        append_rows(ballot64(!one_class && d > 256 && d <= 512), x0, lane, wide + (n + 1) + 1);
-        append_rows(ballot64(d > (one_class ? 128 : 512)), x0, lane, wide + 2 * (n + 1) + 1);
+        const int32_t len = d < 0 && (colH || !packD) ? ~d : d;
+        append_rows(ballot64(!one_class && len > 128 && len <= 256), x0, lane, wide + 1);
+        append_rows(ballot64(!one_class && len > 256 && len <= 512), x0, lane, wide + (n + 1) + 1);
+        append_rows(ballot64(len > (one_class ? 128 : 512)), x0, lane, wide + 2 * (n + 1) + 1);
     }
     if (!Gx) add_gather(gsum, acc);
 }
@@ -725,7 +783,8 @@ __global__ void __launch_bounds__(256) k_work_lanes(int64_t n, const int4* __res
 // Anchor work of the light sources with 32 R < d+ <= 64 R (R = 16: every
 // d+ > 512), one wave per list, over the vertex list L (count at L[-1]) that
 // k_work_lanes appended; one instantiation per register class, so that the
-// shorter classes keep their occupancy.  Writes Wu of its lists.
+// shorter classes keep their occupancy.  Writes Wu of its lists.  Also takes the
+// plain lists of those lengths.
 template <int R>
 __global__ void __launch_bounds__(256) k_work_wide(const int32_t* __restrict__ L, const int4* __restrict__ rowQ,
                                                     int32_t* __restrict__ colO, uint16_t* __restrict__ colH,
@@ -741,6 +800,10 @@ __global__ void __launch_bounds__(256) k_work_wide(const int32_t* __restrict__ L
          i += gridDim.x * 4) {
         const int32_t x = L[i];
         const int4 q = rowQ[x];  // wave-uniform
+        if (q.y < 0) {
+            plain_list(q.x, ~q.y, lane, rowQ, colO, colH, packU, packD);
+            continue;
+        }
         work_wide_lists<R>(1ull, q, x, lane, rowQ, colO, colH, vcap, packU, packD, cw, Wu, Gx, gsum);
     }
     if (!Gx) add_gather(gsum, acc);
