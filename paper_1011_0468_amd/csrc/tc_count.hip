@@ -870,20 +870,80 @@ __global__ void __launch_bounds__(kVThreads) k_vmajor_part(const int32_t* __rest
     }
 }
 
-// cw and packD of one part's vertices from its records.
-__global__ void __launch_bounds__(1024) k_vmajor_place(int64_t n, int vbits, const int32_t* __restrict__ rpD,
+// Records of a part from which it is `big`: twice the mean over the parts, and more
+// than a block places in some 20 us.
+constexpr int32_t kVBig = 1 << 15, kVChunk = 8192;
+__device__ __forceinline__ int32_t vmajor_big(int32_t mp, int parts) { return max(2 * (mp / parts), kVBig); }
+
+// cw and packD of one part's vertices from its records, a block per part.  Where
+// the first ids are the hubs a few parts hold most records: those are dealt in
+// chunks to the blocks past the parts, which claim the slots of a chunk's records in
+// cw (it holds the first slots), one returning atomic per vertex and chunk.  2^22
+// vertices with 16 pairs each to ids of density i^-3/4, 13 M records in one part: the
+// count 23.5 ms with one block for it, 12.5 with a claim per pair and no partition,
+// 6.2 so.
+__global__ void __launch_bounds__(1024, 8) k_vmajor_place(int64_t n, int vbits, int parts,
+                                                        const int32_t* __restrict__ mp_dev,
+                                                        const int32_t* __restrict__ rpD,
                                                         const int32_t* __restrict__ taken,
                                                         const int2* __restrict__ rec, int2* __restrict__ packD,
                                                         unsigned long long* __restrict__ cw) {
     __shared__ unsigned long long c[1 << kVBits];
+    const int t = threadIdx.x;
+    const int32_t big = vmajor_big(mp_dev[0], parts);
+    if ((int)blockIdx.x >= parts) {
+        __shared__ int32_t first[kVParts], tmp[17];  // the parts' first chunks
+        const int32_t mine = t < parts ? taken[t * kVLine] : 0;
+        int32_t chunks;
+        const int32_t pre = block_exclusive_sum<1024>(mine > big ? (mine - 1) / kVChunk + 1 : 0, tmp, &chunks);
+        if (t < parts) first[t] = pre;
+        __syncthreads();
+        for (int32_t ch = blockIdx.x - parts; ch < chunks; ch += gridDim.x - parts) {
+            int lo = 0, hi = parts - 1;  // the last part whose chunks start at or before this one
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (first[mid] <= ch) lo = mid;
+                else hi = mid - 1;
+            }
+            const int32_t j0 = (ch - first[lo]) * kVChunk, cnt = min(kVChunk, taken[lo * kVLine] - j0);
+            const int64_t v0 = (int64_t)lo << vbits;
+            const int32_t nv = (int32_t)min((int64_t)1 << vbits, n - v0);
+            const int2* R = rec + rpD[v0] + j0;
+            constexpr int U = kVChunk / 1024;
+            int2 r[U];
+            int32_t rank[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) r[k] = t + 1024 * k < cnt ? R[t + 1024 * k] : make_int2(0, 0);
+            for (int32_t i = t; i < nv; i += 1024) c[i] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t len = ((uint32_t)r[k].y >> kVBits) & (kVCap - 1);
+                if (t + 1024 * k < cnt)
+                    rank[k] = (int32_t)(atomicAdd(&c[r[k].y & ((1 << kVBits) - 1)], (1ull << 32) | len) >> 32);
+            }
+            __syncthreads();
+            for (int32_t i = t; i < nv; i += 1024)
+                if (c[i]) c[i] = atomicAdd(&cw[v0 + i], c[i]) >> 32;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (t + 1024 * k < cnt)
+                    packD[(int64_t)c[r[k].y & ((1 << kVBits) - 1)] + rank[k]] =
+                        make_int2(r[k].x, (int32_t)(((uint32_t)r[k].y >> kVBits) & (kVCap - 1)));
+            __syncthreads();
+        }
+        return;
+    }
     const int64_t v0 = (int64_t)blockIdx.x << vbits;
     const int32_t nv = (int32_t)min((int64_t)1 << vbits, n - v0);
-    for (int32_t i = threadIdx.x; i < nv; i += 1024) c[i] = (unsigned long long)(uint32_t)rpD[v0 + i] << 32;
+    const int32_t cnt = taken[blockIdx.x * kVLine];
+    if (cnt > big) return;  // block-uniform
+    for (int32_t i = t; i < nv; i += 1024) c[i] = (unsigned long long)(uint32_t)rpD[v0 + i] << 32;
     __syncthreads();
     const int2* R = rec + rpD[v0];
-    const int32_t cnt = taken[blockIdx.x * kVLine];
     constexpr int U = 4;
-    for (int32_t i0 = threadIdx.x; i0 < cnt; i0 += 1024 * U) {
+    for (int32_t i0 = t; i0 < cnt; i0 += 1024 * U) {
         int2 r[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) r[k] = i0 + 1024 * k < cnt ? R[i0 + 1024 * k] : make_int2(0, 0);
@@ -896,7 +956,7 @@ __global__ void __launch_bounds__(1024) k_vmajor_place(int64_t n, int vbits, con
         }
     }
     __syncthreads();
-    for (int32_t i = threadIdx.x; i < nv; i += 1024) cw[v0 + i] = c[i];
+    for (int32_t i = t; i < nv; i += 1024) cw[v0 + i] = c[i];
 }
 
 __device__ __forceinline__ int32_t items_of(int64_t w, int32_t len) {
@@ -2650,8 +2710,9 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
                       dim3((unsigned)std::min<int64_t>(ceil_div(g->m, kVTile), (int64_t)num_cus() * 64)),
                       dim3(kVThreads), 0, s, mp_dev, (const int2*)packU.get(), vbits, n, (const int32_t*)rpD.get(),
                       taken.get(), rec.get());
-            TC_LAUNCH("vmajor_place", k_vmajor_place, dim3((unsigned)(((n - 1) >> vbits) + 1)), dim3(1024), 0, s, n,
-                      vbits, (const int32_t*)rpD.get(), (const int32_t*)taken.get(), (const int2*)rec.get(),
+            const int parts = (int)((n - 1) >> vbits) + 1;
+            TC_LAUNCH("vmajor_place", k_vmajor_place, dim3((unsigned)(parts + num_cus())), dim3(1024), 0, s, n, vbits,
+                      parts, mp_dev, (const int32_t*)rpD.get(), (const int32_t*)taken.get(), (const int2*)rec.get(),
                       packD.get(), cwp);
         }
         // item counts of the bins, then their prefixes in place
