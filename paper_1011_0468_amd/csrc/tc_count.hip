@@ -71,8 +71,11 @@ constexpr int kHubTail = 8;
 // us faster than three launches, 210000 edges of R-MAT 30 us slower.
 constexpr int64_t kSmallEdges = 5 << 15;
 // Heavy vertices (bound) and vertices up to which one block counts the heavy
-// triangles: 50 KB of LDS for their adjacency bits.
-constexpr int64_t kHeavySmall = 640, kHeavySmallN = 1 << 16;
+// triangles: 54 KB of LDS for their adjacency bits.  The block takes 12 us for a
+// graph of 16384 vertices and 95000 edges, a bound of 617 and 28 heavy vertices;
+// where all of a graph may be heavy, 34, 60 and 147 for cliques of 200, 300 and 450,
+// and past kHeavyDense vertices the launches it saves (40 us) are the shorter way.
+constexpr int64_t kHeavySmall = 640, kHeavySmallN = 1 << 16, kHeavyDense = 256;
 // Edges per vertex of the counted graph from which hubs are numbered.
 constexpr double kBitDegree = 6.0;
 // Edges of the counted graph from which v-major pairs are placed by partition
@@ -2224,24 +2227,30 @@ __global__ void __launch_bounds__(256) k_heavy_mfma(const uint8_t* __restrict__ 
     if (lane == 0 && total) atomicAdd((unsigned long long*)&acc[kTH], (unsigned long long)total);
 }
 
+// Words of an adjacency row of hmax heavy vertices, at most, in LDS.
+__host__ __device__ __forceinline__ int64_t small_pitch(int64_t hmax) { return ((hmax + 31) / 32) | 1; }
+
 // The heavy phase of a small graph, and the end of its count, in one block: the
 // adjacency bits of the heavy vertices (numbered by hpos, the prefix of their
 // flags) in LDS, then for every heavy pair u -> v the common bits of their
-// rows.  Seven launches for a few hundred vertices took 40 of the 210 us of a
+// rows: bound by the latency of its gathers while the heavy vertices are few, by
+// LDS reads (a word per lane, 2 cycles a wave) where hundreds are joined to each
+// other: K_450 711 us with a pair per half wave and a row's gathers in one chain,
+// 147 so.  Seven launches for a few hundred vertices took 40 of the 210 us of a
 // count of 16384 vertices and 95000 edges; with this, the scans of one launch,
 // one class of long lists and the anchor work of a window dealt to four waves
-// it takes 165.
+// it takes 163.
 __global__ void __launch_bounds__(1024) k_heavy_small(int64_t n, const int32_t* __restrict__ hpos, int32_t hmax,
                                                        const int32_t* __restrict__ rpO,
                                                        const int32_t* __restrict__ colO, const int32_t* mp,
                                                        const int64_t* __restrict__ part, int32_t nparts, int64_t* acc) {
-    extern __shared__ uint32_t small_bits[];  // hmax rows of W words, then hmax vertices
+    extern __shared__ uint32_t small_bits[];  // hmax rows of P words, then hmax vertices
     const int t = threadIdx.x, w = t >> 6, lane = __lane_id();
     const int32_t h = heavy_count(hpos + n, hmax);
-    const int32_t W = (h + 31) / 32;
-    int32_t* list = reinterpret_cast<int32_t*>(small_bits + (size_t)hmax * ((hmax + 31) / 32));
+    const int32_t W = (h + 31) / 32, P = W | 1;  // odd: 64 rows' words of one column in as many banks
+    int32_t* list = reinterpret_cast<int32_t*>(small_bits + (size_t)hmax * small_pitch(hmax));
     if (t == 0 && hpos[n] > hmax) acc[kHeavyOverflow] = 1;
-    for (int32_t i = t; i < h * W; i += 1024) small_bits[i] = 0;
+    for (int32_t i = t; i < h * P; i += 1024) small_bits[i] = 0;
     for (int64_t x0 = t; x0 < n; x0 += 8 * 1024) {
         int32_t a[8], b[8];
 #pragma unroll
@@ -2255,28 +2264,58 @@ __global__ void __launch_bounds__(1024) k_heavy_small(int64_t n, const int32_t* 
             if (x0 + 1024 * k < n && b[k] > a[k] && a[k] < hmax) list[a[k]] = (int32_t)(x0 + 1024 * k);
     }
     __syncthreads();
-    for (int32_t i = w; i < h; i += 16) {
-        const int32_t x = list[i];
-        for (int32_t q = rpO[x] + lane; q < rpO[x + 1]; q += 64) {
-            const int32_t j = hpos[colO[q]];  // every vertex above a heavy one is heavy
-            if (j < h) atomicOr(&small_bits[i * W + (j >> 5)], 1u << (j & 31));
+    // wave w has the rows w, w + 16, ..: lane r the ends of row w + 16 r; four rows at a
+    // time, two entries of each a lane, so that eight chains of gathers are in flight.
+    // A lane's entries of a row are neighbours, and those of a wave spread over it:
+    // 64 neighbouring entries of a dense row are bits of two or three words, whose
+    // atomics would follow one another.
+    const int32_t rows = (h - w + 15) / 16;  // <= 40
+    int32_t re = 0, rs = 0;
+    if (lane < rows) {
+        const int32_t x = list[w + 16 * lane];
+        rs = rpO[x];
+        re = rpO[x + 1];
+    }
+    for (int32_t r0 = 0; r0 < rows; r0 += 4) {
+        int32_t s[4], len[4], per[4], most = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            s[q] = __builtin_amdgcn_readlane(rs, r0 + q);  // lanes past the rows hold (0, 0)
+            len[q] = __builtin_amdgcn_readlane(re, r0 + q) - s[q];
+            per[q] = (len[q] + 63) / 64;
+            most = max(most, per[q]);
+        }
+        for (int32_t k0 = 0; k0 < most; k0 += 2) {
+            int32_t v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int q = e >> 1, k = k0 + (e & 1), at = lane * per[q] + k;
+                v[e] = k < per[q] && at < len[q] ? colO[s[q] + at] : -1;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = v[e] >= 0 ? hpos[v[e]] : h;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)  // every vertex above a heavy one is heavy
+                if (v[e] < h) atomicOr(&small_bits[(w + 16 * (r0 + (e >> 1))) * P + (v[e] >> 5)], 1u << (v[e] & 31));
         }
     }
     __syncthreads();
+    // row i against the rows of its bits, a row per lane, 64 at a time: row i is held a
+    // word per lane and read by lane number, the others' words lie in different banks
     int64_t total = 0;
-    const int l = lane & 31;
     for (int32_t i = w; i < h; i += 16) {
-        for (int32_t k = 0; k < W; ++k) {
-            uint32_t rest = small_bits[i * W + k];  // wave-uniform
-            while (rest) {  // two of u's out-neighbours at a time, one per half wave
-                const int j0 = __builtin_ctz(rest);
-                rest &= rest - 1;
-                const int j1 = rest ? __builtin_ctz(rest) : -1;
-                rest &= rest - 1;
-                const int j = lane < 32 ? j0 : j1;
-                for (int32_t b = l; j >= 0 && b < W; b += 32)
-                    total += __builtin_popcount(small_bits[i * W + b] & small_bits[(32 * k + j) * W + b]);
-            }
+        const int32_t mine = lane < W ? (int32_t)small_bits[i * P + lane] : 0;
+        for (int32_t k0 = 0; k0 < W; k0 += 2) {
+            const uint64_t set = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(mine, k0 + 1) << 32 |
+                                 (uint32_t)__builtin_amdgcn_readlane(mine, k0);
+            if (!set) continue;  // wave-uniform
+            const bool on = (set >> lane) & 1;
+            const uint32_t* row = small_bits + (on ? 32 * k0 + lane : 0) * P;
+            int32_t sum = 0;
+#pragma unroll 4
+            for (int32_t k = 0; k < W; ++k)
+                sum += __builtin_popcount((uint32_t)__builtin_amdgcn_readlane(mine, k) & row[k]);
+            total += on ? sum : 0;
         }
     }
     total = wave_sum(total);
@@ -2560,7 +2599,7 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     if (!un && hp_max * hp_max > ((int64_t)16 << 30))
         fail(TC_ERR_OVERFLOW, "heavy block bound exceeds 16 GiB: raise the heavy threshold");
     const int64_t items_max = 2 * n + E2 / kJL + 2;
-    const bool heavy_small = !un && hmax <= kHeavySmall && n <= kHeavySmallN;
+    const bool heavy_small = !un && hmax <= kHeavySmall && n <= kHeavySmallN && (hmax < n || n <= kHeavyDense);
 
     // 1. the counted graph: the input CSR, or its sample compacted into buffers
     //    sized for the full graph (section 3.1 coin), so that every later pass
@@ -2815,7 +2854,7 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
         {
             PhaseScope ph_finish(heavy_small ? "heavy" : "finish");
             if (heavy_small) {
-                const size_t lds = sizeof(uint32_t) * (size_t)(hmax * ((hmax + 31) / 32) + hmax);
+                const size_t lds = sizeof(uint32_t) * (size_t)(hmax * small_pitch(hmax) + hmax);
                 TC_LAUNCH("heavy_small", k_heavy_small, dim3(1), dim3(1024), lds, s, n, (const int32_t*)hpos.get(),
                           (int32_t)hmax, (const int32_t*)rpO.get(), (const int32_t*)colO.get(), mp_dev,
                           (const int64_t*)cpart.get(), (int32_t)cgrid, acc);
