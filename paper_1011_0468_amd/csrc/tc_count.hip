@@ -70,12 +70,15 @@ constexpr int kHubTail = 8;
 // Edges up to which one launch takes all long lists: 95000 to 150000 edges 4 to 8
 // us faster than three launches, 210000 edges of R-MAT 30 us slower.
 constexpr int64_t kSmallEdges = 5 << 15;
-// Heavy vertices (bound) and vertices up to which one block counts the heavy
-// triangles: 54 KB of LDS for their adjacency bits.  The block takes 12 us for a
-// graph of 16384 vertices and 95000 edges, a bound of 617 and 28 heavy vertices;
-// where all of a graph may be heavy, 34, 60 and 147 for cliques of 200, 300 and 450,
-// and past kHeavyDense vertices the launches it saves (40 us) are the shorter way.
-constexpr int64_t kHeavySmall = 640, kHeavySmallN = 1 << 16, kHeavyDense = 256;
+// Heavy vertices (bound) and vertices up to which one launch counts the heavy
+// triangles: 54 KB of LDS for their adjacency bits.  It takes 12 us for a graph of
+// 16384 vertices and 95000 edges, a bound of 617 and 28 heavy vertices; where all of
+// a graph may be heavy, 21, 31, 54 and 112 for cliques of 200, 300, 450 and 640, and
+// past kHeavyDense vertices the launches it saves (40 to 50 us) are the shorter way.
+// Each of its blocks holds all the bits and takes a share of the rows' pairs (one
+// block: 34, 60, 147 and 300 us).
+constexpr int64_t kHeavySmall = 640, kHeavySmallN = 1 << 16, kHeavyDense = 448;
+constexpr int kHeavyBlocks = 16;
 // Edges per vertex of the counted graph from which hubs are numbered.
 constexpr double kBitDegree = 6.0;
 // Edges of the counted graph from which v-major pairs are placed by partition
@@ -2230,16 +2233,16 @@ __global__ void __launch_bounds__(256) k_heavy_mfma(const uint8_t* __restrict__ 
 // Words of an adjacency row of hmax heavy vertices, at most, in LDS.
 __host__ __device__ __forceinline__ int64_t small_pitch(int64_t hmax) { return ((hmax + 31) / 32) | 1; }
 
-// The heavy phase of a small graph, and the end of its count, in one block: the
+// The heavy phase of a small graph, and the end of its count, in one launch: the
 // adjacency bits of the heavy vertices (numbered by hpos, the prefix of their
 // flags) in LDS, then for every heavy pair u -> v the common bits of their
 // rows: bound by the latency of its gathers while the heavy vertices are few, by
 // LDS reads (a word per lane, 2 cycles a wave) where hundreds are joined to each
-// other: K_450 711 us with a pair per half wave and a row's gathers in one chain,
-// 147 so.  Seven launches for a few hundred vertices took 40 of the 210 us of a
-// count of 16384 vertices and 95000 edges; with this, the scans of one launch,
-// one class of long lists and the anchor work of a window dealt to four waves
-// it takes 163.
+// other: K_450 in one block 711 us with a pair per half wave and a row's gathers in
+// one chain, 147 so, 54 in 16 blocks.  Seven launches for a few hundred vertices
+// took 40 of the 210 us of a count of 16384 vertices and 95000 edges; with this, the
+// scans of one launch, one class of long lists and the anchor work of a window dealt
+// to four waves it takes 165.
 __global__ void __launch_bounds__(1024) k_heavy_small(int64_t n, const int32_t* __restrict__ hpos, int32_t hmax,
                                                        const int32_t* __restrict__ rpO,
                                                        const int32_t* __restrict__ colO, const int32_t* mp,
@@ -2303,7 +2306,7 @@ __global__ void __launch_bounds__(1024) k_heavy_small(int64_t n, const int32_t* 
     // row i against the rows of its bits, a row per lane, 64 at a time: row i is held a
     // word per lane and read by lane number, the others' words lie in different banks
     int64_t total = 0;
-    for (int32_t i = w; i < h; i += 16) {
+    for (int32_t i = blockIdx.x * 16 + w; i < h; i += 16 * gridDim.x) {
         const int32_t mine = lane < W ? (int32_t)small_bits[i * P + lane] : 0;
         for (int32_t k0 = 0; k0 < W; k0 += 2) {
             const uint64_t set = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(mine, k0 + 1) << 32 |
@@ -2320,7 +2323,7 @@ __global__ void __launch_bounds__(1024) k_heavy_small(int64_t n, const int32_t* 
     }
     total = wave_sum(total);
     if (lane == 0 && total) atomicAdd((unsigned long long*)&acc[kTH], (unsigned long long)total);
-    finish_stats(mp, hpos + n, part, nparts, acc);
+    if (blockIdx.x == 0) finish_stats(mp, hpos + n, part, nparts, acc);  // block-uniform
 }
 
 // ---- heavy blocks of a union of components --------------------------------
@@ -2855,7 +2858,7 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
             PhaseScope ph_finish(heavy_small ? "heavy" : "finish");
             if (heavy_small) {
                 const size_t lds = sizeof(uint32_t) * (size_t)(hmax * small_pitch(hmax) + hmax);
-                TC_LAUNCH("heavy_small", k_heavy_small, dim3(1), dim3(1024), lds, s, n, (const int32_t*)hpos.get(),
+                TC_LAUNCH("heavy_small", k_heavy_small, dim3(kHeavyBlocks), dim3(1024), lds, s, n, (const int32_t*)hpos.get(),
                           (int32_t)hmax, (const int32_t*)rpO.get(), (const int32_t*)colO.get(), mp_dev,
                           (const int64_t*)cpart.get(), (int32_t)cgrid, acc);
             } else if (!un)

@@ -1,5 +1,5 @@
-"""GPU: the heavy phase of one block at the limits of its rule (the bound of 640
-heavy vertices, 256 vertices that may all be heavy), against the oracle, with its
+"""GPU: the heavy phase of one launch at the limits of its rule (the bound of 640
+heavy vertices, 448 vertices that may all be heavy), against the oracle, with its
 launch asserted."""
 import numpy as np
 import pytest
@@ -45,7 +45,7 @@ def test_sparse_bound(gpu, m, split, small):
     assert got["m"] == m and got["n_heavy"] > 0
 
 
-@pytest.mark.parametrize("n,small", [(2, 1), (33, 1), (255, 1), (256, 1), (257, 0), (640, 0)])
+@pytest.mark.parametrize("n,small", [(2, 1), (33, 1), (256, 1), (448, 1), (449, 0), (640, 0)])
 def test_all_may_be_heavy(gpu, n, small):
     for split in ((1, 1), (0, 1)):
         _check(gpu, special.complete(n), split, small)
