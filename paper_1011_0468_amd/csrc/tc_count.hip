@@ -67,8 +67,10 @@ constexpr int kHubs = 65535;
 constexpr int32_t kNoHub = 65535;
 constexpr int64_t kHubChunk = 4096;  // vertices per block of the pass that numbers them
 constexpr int kHubTail = 8;
-// Edges up to which one launch takes all long lists: 95000 to 150000 edges 4 to 8
-// us faster than three launches, 210000 edges of R-MAT 30 us slower.
+// Edges up to which one launch takes all long lists, if they would be three (their
+// lengths reach the largest degree): 95000 to 150000 edges 4 to 8 us faster than
+// three launches, 210000 edges of R-MAT 30 us slower; uniform 1000 vertices and 90000
+// edges, whose one launch is the shortest class's, 12 us in it and 45 in the last.
 constexpr int64_t kSmallEdges = 5 << 15;
 // Heavy vertices (bound) and vertices up to which one launch counts the heavy
 // triangles: 54 KB of LDS for their adjacency bits.  It takes 12 us for a graph of
@@ -2716,7 +2718,7 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
         // v-major descriptors, rpD[v].. for vertex v: a slot per edge at its upper end, also of the edges whose
         // lower end a union leaves out
         DevBuf<int2> packD(vcap > 0 ? (un ? un->m_all : g->m) : 1, s);
-        const bool one_class = g->m <= kSmallEdges;  // few long lists: one launch for all of them
+        const bool one_class = g->m <= kSmallEdges && g->max_deg > 512;  // few long lists: one launch for three
         int2* claims = defer ? nullptr : packD.get();  // where the anchor work places v-major pairs itself
         const bool split = n <= (int64_t)num_cus() * 64 * 4;  // windows in waves would leave SIMDs idle
         TC_LAUNCH("work", k_work_lanes, dim3(grid_for(n, split ? 64 : 256)), dim3(256), 0, s, n,
