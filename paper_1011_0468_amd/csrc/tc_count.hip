@@ -81,13 +81,17 @@ constexpr int64_t kSmallEdges = 5 << 15;
 // block: 34, 60, 147 and 300 us).
 constexpr int64_t kHeavySmall = 640, kHeavySmallN = 1 << 16, kHeavyDense = 448;
 constexpr int kHeavyBlocks = 16;
-// Edges per vertex of the counted graph from which hubs are numbered.
-constexpr double kBitDegree = 6.0;
+// Edges per vertex of the counted graph, and largest degree over the mean of the
+// whole one, from which hubs are numbered.
+constexpr double kBitDegree = 6.0, kBitSkew = 4.0;
 // Edges of the counted graph from which v-major pairs are placed by partition
 // (three more launches): without and with it R-MAT s16 to s17 of 0.9 to 1.0 M
 // edges take 522 and 466, 495 and 447 us, samples of 0.45 to 0.5 M edges 353
-// and 352, 342 and 341, and smaller ones 5 to 10% longer with it.
-constexpr double kDeferPairs = 3 << 18;
+// and 352, 342 and 341, and smaller ones 5 to 10% longer with it.  Sparse graphs
+// without hubs have few such pairs: below kDeferDegree edges a vertex, a path of 2^22
+// vertices 345 and 372 us, uniform 2^20 of 1.6 M edges 392 and 412; with a degree of
+// kDeferSkew times the mean, R-MAT s22 of 8 M edges, 1310 and 1215.
+constexpr double kDeferPairs = 3 << 18, kDeferDegree = 2.0, kDeferSkew = 16.0;
 
 // ---------------------------------------------------------------------------
 // orientation
@@ -2652,14 +2656,21 @@ static void count_impl(const tc_graph_s* g, int sampled, uint64_t thr, uint64_t 
     // too few to pay for it.  A count of R-MAT s22 without and with hubs: p = 1
     // 10.4 and 7.9 ms, p = 0.5 4.7 and 4.2, p = 0.25 2.37 and 2.38, p = 0.1 1.36
     // and 1.41; of s20: p = 1 2.26 and 1.84, p = 0.5 1.23 and 1.22, p = 0.25
-    // 0.81 and 0.82.
+    // 0.81 and 0.82.  Where no degree is far above the mean a class holds more
+    // vertices than there are numbers (70000 vertices of degree 230 +- 15 at p = 0.5:
+    // 715 and 737 us), and where all vertices may be heavy they usually are, so that
+    // neither hubs nor the partition below find any pairs (K_4000 265 and 290 us).
     const LightPlan plan = light_plan(un ? un->m_all : g->m, g->max_deg, cfg);
     const double kept = sampled ? (double)thr / 9007199254740992.0 : 1.0;
-    const bool bits = !un && plan.dcap_lds && hub_lists_fit(n, g->m, cfg) &&
-                      (n <= kHubs || kept * (double)g->m >= kBitDegree * (double)n);
+    const bool all_heavy = hmax >= n;
+    const double skew = (double)g->max_deg * (double)n / (2.0 * (double)g->m);  // the largest degree over the mean
+    const bool bits = !un && !all_heavy && plan.dcap_lds && hub_lists_fit(n, g->m, cfg) &&
+                      (n <= kHubs || (skew >= kBitSkew && kept * (double)g->m >= kBitDegree * (double)n));
     const bool numbered = bits && n > kHubs;
     // v-major pairs placed by partition: see k_vmajor_part
-    const bool defer = !un && kept * (double)g->m >= kDeferPairs && vmajor_parts_fit(n, g->m, g->max_deg, cfg);
+    const bool defer = !un && !all_heavy && kept * (double)g->m >= kDeferPairs &&
+                       (skew >= kDeferSkew || kept * (double)g->m >= kDeferDegree * (double)n) &&
+                       vmajor_parts_fit(n, g->m, g->max_deg, cfg);
     DevBuf<uint16_t> num(numbered ? n : 0, s);
     if (numbered) {
         DevBuf<int32_t> hist(257, s);

@@ -32,6 +32,32 @@ def _check(gpu, graph, split, expect, p=1.0):
     assert {k: ran[k] for k in expect} == expect
 
 
+def _uniform_and_hub(n, pairs, leaves, seed):
+    _, a, b = synth.uniform_pairs(n, pairs, seed)
+    hub = np.random.RandomState(seed).permutation(n)[:leaves + 1].astype(np.int32)
+    return n, np.concatenate([a, np.full(leaves, hub[0], np.int32)]), np.concatenate([b, hub[1:]])
+
+
+@pytest.mark.parametrize("hub,numbered", [(40, 0), (1200, 1)])
+@pytest.mark.parametrize("p", [1.0, 0.9])
+def test_skew(gpu, hub, numbered, p):
+    """66000 vertices of degree 90 or so: hubs are numbered if one has four times the mean."""
+    _check(gpu, _uniform_and_hub(66000, 3000000, hub, 1), (1, 1), dict(hub_ids=numbered, light_bits=numbered), p)
+
+
+@pytest.mark.parametrize("pairs,hub,placed", [(870000, 1, 0), (870000, 1000, 1), (1600000, 1, 1)])
+def test_sparse(gpu, pairs, hub, placed):
+    """Past 786432 edges: below two a vertex the pairs are placed by partition only in a skewed graph."""
+    _check(gpu, _uniform_and_hub(600000, pairs, hub, 2), (1, 1), dict(vmajor_place=placed))
+
+
+@pytest.mark.parametrize("split", [(1, 1), (0, 1), (2, 1)])
+def test_all_may_be_heavy(gpu, split):
+    """K_1300, more edges than the partition's limit: no hubs and no partition where all vertices may be heavy."""
+    on = 1 if split == (2, 1) else 0  # a bound of 920
+    _check(gpu, special.complete(1300), split, dict(light_bits=on, vmajor_place=on))
+
+
 @pytest.mark.parametrize("n,pairs,w4,w16", [(1000, 90000, 1, 0), (300, 90000, 1, 0), (700, 190000, 1, 0)])
 def test_long_lists_of_one_class(gpu, n, pairs, w4, w16):
     """No degree above 512: the shorter classes' launches, whatever the edges."""
