@@ -1840,7 +1840,7 @@ __global__ void __launch_bounds__(256) k_light_large(const int2* __restrict__ it
 // vector and scalar instructions per 64 probes (hash, 16-byte read, four
 // compares into wave masks, the owners of the positions); 4.9 ms with bitmaps
 // over 4-byte entries, bound by the 34 GB of list lines that miss the L2s
-// (7 TB/s); 3.0 ms with the 2-byte numbers, and 0.8 ms for the anchors past the
+// (7 TB/s); 3.5 ms with the 2-byte numbers, and 0.45 ms for the anchors past the
 // hubs, which keep the tables.
 constexpr int kBitLanes = 4;
 constexpr int kBitDepth = 2;
@@ -2968,7 +2968,10 @@ static int64_t heavy_phase_bytes(int64_t n, int64_t m, const CountConfig& cfg) {
 }
 
 // Whether the hub numbers fit the memory that a count takes anyhow: the heavy
-// phase's, which is not in use during the light one.
+// phase's, which is not in use during the light one, so that no reservation and no
+// allocation-free call grows.  That memory shrinks with c^2, and past it the anchors
+// keep the hash tables: R-MAT s22 takes the numbers up to c = 2 (c = 1 7.8 ms, c = 4,
+// without them, 13.0).
 static bool hub_lists_fit(int64_t n, int64_t m, const CountConfig& cfg) {
     return region_bytes(2 * (m + kHubTail)) <= heavy_phase_bytes(n, m, cfg);
 }
@@ -2990,8 +2993,10 @@ static int64_t item_bytes(int64_t n, int64_t m, int32_t maxd, bool hubs, const C
 static int64_t vmajor_part_bytes(int64_t m) { return region_bytes(8 * m) + region_bytes(4 * kVParts * kVLine); }
 
 // Whether the v-major pairs can be placed by partition: the records hold what
-// they must, and what they take beyond the item lists' place fits the memory
-// that the heavy phase takes anyhow, next to the hub numbers.
+// they must (at most 2^22 vertices), and what they take beyond the item lists'
+// place fits the memory that the heavy phase takes anyhow, next to the hub numbers.
+// Otherwise the anchor work claims their slots: R-MAT s22 at c = 2 9.4 ms, s24 at c = 1
+// 76 ms, both without the partition.
 static bool vmajor_parts_fit(int64_t n, int64_t m, int32_t maxd, const CountConfig& cfg) {
     if (cfg.vmajor_cap < 1 || cfg.vmajor_cap > kVCap || n > ((int64_t)kVParts << kVBits)) return false;
     const int64_t over = std::max<int64_t>(0, vmajor_part_bytes(m) - item_bytes(n, m, maxd, false, cfg));

@@ -9,7 +9,9 @@
 //   2. part   : the keys scattered to their windows, in any order, by one
 //               pass over the pairs (W <= 8), or by one over the top W - 8
 //               bits and one over the next 8.  A key leaves its window's bits
-//               behind, so for n <= 2^23 the windows hold 4-byte keys;
+//               behind, and the windows hold 4-byte keys where 2 nb - W <= 32 (W
+//               grows with the pairs: R-MAT s22 29 bits; 2^20 vertices and 30000
+//               pairs 33);
 //   3. sort   : each window sorted and made unique in LDS, its rows' degrees
 //               stored;
 //   4. big    : windows of more than kWindowCap keys (the hubs' windows of a
@@ -19,7 +21,7 @@
 //
 // All of it is bound by memory: every pass reads and writes each key once, and
 // here that is 40 bytes a key where six LSD passes over 8-byte keys, flags and
-// positions took 160.  R-MAT s22 (2^26 pairs): 10.2 -> 4.2 ms.
+// positions took 160.  R-MAT s22 (2^26 pairs): 10.5 -> 4.4 ms.
 #include "tc_internal.h"
 #include "tc_device.h"
 
